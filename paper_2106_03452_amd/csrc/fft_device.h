@@ -162,12 +162,29 @@ __device__ __forceinline__ void fft_sync() {
   else __syncthreads();
 }
 
-template <int L, int R, int NS, int DIR, bool IN_REG, bool OUT_REG, bool WS = false>
+// x, but of unknown value to the compiler (uniform, or per lane). A kernel
+// with several transforms computes the same LDS addresses, twiddles and wave
+// numbers in each; left to itself the compiler keeps them all in registers
+// from the first to the last (181 VGPRs for three length-256 transforms, 2
+// waves per SIMD). With the line index and the table offset taken anew by
+// every stage they are recomputed, a few instructions each: 96 VGPRs, so LDS
+// and not registers sets the occupancy.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+__device__ __forceinline__ int opaque_v(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+template <int L, int R, int NS, int DIR, bool IN_REG, bool OUT_REG, bool WS = false, bool LEAN = false>
 __device__ __forceinline__ void stage(cf* reg, cf* line, int lt, const cf* __restrict__ tw, int swz) {
   constexpr int E = plan_E(L), TPL = plan_TPL(L);
   static_assert(!WS || 64 % TPL == 0, "a wavefront-synchronous line lies within one wavefront");
   constexpr int NB = E / R;
   constexpr int STRIDE = L / R;
+  if constexpr (LEAN) lt = opaque_v(lt);
   cf a[NB][R];
 #pragma unroll
   for (int u = 0; u < NB; ++u) {
@@ -201,34 +218,35 @@ __device__ __forceinline__ void stage(cf* reg, cf* line, int lt, const cf* __res
 
 // Whole length-L transform. IN_REG / OUT_REG select where the first stage
 // reads and the last stage writes (canonical registers or the LDS line).
-template <int L, int DIR, bool IN_REG, bool OUT_REG, bool WS = false>
+template <int L, int DIR, bool IN_REG, bool OUT_REG, bool WS = false, bool LEAN = false>
 __device__ __forceinline__ void fft(cf* reg, cf* line, int lt, const cf* __restrict__ tw, int swz = 0) {
+  if constexpr (LEAN) tw += opaque(0);
   if constexpr (L == 4) {
-    stage<4, 4, 1, DIR, IN_REG, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<4, 4, 1, DIR, IN_REG, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   } else if constexpr (L == 8) {
-    stage<8, 8, 1, DIR, IN_REG, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<8, 8, 1, DIR, IN_REG, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   } else if constexpr (L == 16) {
-    stage<16, 16, 1, DIR, IN_REG, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<16, 16, 1, DIR, IN_REG, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   } else if constexpr (L == 32) {
-    stage<32, 8, 1, DIR, IN_REG, false, WS>(reg, line, lt, tw, swz);
-    stage<32, 4, 8, DIR, false, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<32, 8, 1, DIR, IN_REG, false, WS, LEAN>(reg, line, lt, tw, swz);
+    stage<32, 4, 8, DIR, false, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   } else if constexpr (L == 64) {
-    stage<64, 8, 1, DIR, IN_REG, false, WS>(reg, line, lt, tw, swz);
-    stage<64, 8, 8, DIR, false, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<64, 8, 1, DIR, IN_REG, false, WS, LEAN>(reg, line, lt, tw, swz);
+    stage<64, 8, 8, DIR, false, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   } else if constexpr (L == 128) {
-    stage<128, 16, 1, DIR, IN_REG, false, WS>(reg, line, lt, tw, swz);
-    stage<128, 8, 16, DIR, false, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<128, 16, 1, DIR, IN_REG, false, WS, LEAN>(reg, line, lt, tw, swz);
+    stage<128, 8, 16, DIR, false, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   } else if constexpr (L == 256) {
-    stage<256, 16, 1, DIR, IN_REG, false, WS>(reg, line, lt, tw, swz);
-    stage<256, 16, 16, DIR, false, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<256, 16, 1, DIR, IN_REG, false, WS, LEAN>(reg, line, lt, tw, swz);
+    stage<256, 16, 16, DIR, false, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   } else if constexpr (L == 512) {
-    stage<512, 8, 1, DIR, IN_REG, false, WS>(reg, line, lt, tw, swz);
-    stage<512, 8, 8, DIR, false, false, WS>(reg, line, lt, tw, swz);
-    stage<512, 8, 64, DIR, false, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<512, 8, 1, DIR, IN_REG, false, WS, LEAN>(reg, line, lt, tw, swz);
+    stage<512, 8, 8, DIR, false, false, WS, LEAN>(reg, line, lt, tw, swz);
+    stage<512, 8, 64, DIR, false, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   } else if constexpr (L == 1024) {
-    stage<1024, 16, 1, DIR, IN_REG, false, WS>(reg, line, lt, tw, swz);
-    stage<1024, 16, 16, DIR, false, false, WS>(reg, line, lt, tw, swz);
-    stage<1024, 4, 256, DIR, false, OUT_REG, WS>(reg, line, lt, tw, swz);
+    stage<1024, 16, 1, DIR, IN_REG, false, WS, LEAN>(reg, line, lt, tw, swz);
+    stage<1024, 16, 16, DIR, false, false, WS, LEAN>(reg, line, lt, tw, swz);
+    stage<1024, 4, 256, DIR, false, OUT_REG, WS, LEAN>(reg, line, lt, tw, swz);
   }
 }
 

@@ -313,26 +313,55 @@ __device__ __forceinline__ void fill_rows(cf* rows, const PointRec* __restrict__
 }
 
 // Separable Gaussian of main Eq. 3: g(k) = g1(k0) g1(k1) g1(k2) with
-// g1(k) = exp(-2 sigma^2 kappa(k)^2 / r^2); one table of RES floats per
-// workgroup in LDS (the Nyquist index keeps kappa^2 = (r/2)^2).
+// g1(k) = exp(-2 sigma^2 kappa(k)^2 / r^2), even in kappa: one table of
+// RES / 2 + 1 floats per workgroup in LDS (index |kappa|).
 template <int RES, int BLOCK>
 __device__ __forceinline__ void gauss_table(float* g1, float sigma) {
   constexpr float inv_r2 = 1.0f / ((float)RES * (float)RES);
-  for (int e = threadIdx.x; e < RES; e += BLOCK) {
-    const float q = kappa_of(e, RES);
+  for (int e = threadIdx.x; e <= RES / 2; e += BLOCK) {
+    const float q = (float)e;
     g1[e] = expf(-2.0f * sigma * sigma * q * q * inv_r2);
   }
 }
-
-// F(k) = g(k) / (-2 pi |kappa|^2) / N, and 0 at k = 0 (the inverse's 1/N folded in).
 template <int RES>
-__device__ __forceinline__ float spectral_F(const float* g1, int k0, float g12, float q12) {
-  const float q0 = kappa_of(k0, RES);
+__device__ __forceinline__ float gauss_at(const float* g1, int k) {
+  return g1[k <= RES / 2 ? k : RES - k];
+}
+
+// Wave numbers of the canonical register elements k = lt + TPL v of a line
+// (lt < TPL, TPL E = RES): which half k lies in depends on v alone, so each is
+// one addition of a constant, and only one v can meet the Nyquist index or 0.
+template <int RES, bool LEAN = false>
+struct LineK {
+  static constexpr int TPL = plan_TPL(RES), E = plan_E(RES);
+  int lt;
+  float f;
+  // LEAN: nothing is shared with (and held in registers for) other users
+  __device__ __forceinline__ explicit LineK(int l) : lt(LEAN ? opaque_v(l) : l), f((float)lt) {}
+  __device__ __forceinline__ int k(int v) const { return lt + TPL * v; }
+  __device__ __forceinline__ float of(int v) const { return f + (float)(TPL * v - (v >= E / 2 ? RES : 0)); }
+  __device__ __forceinline__ float odd(int v) const { return v == E / 2 && lt == 0 ? 0.0f : of(v); }
+};
+
+// out = kappa_odd(k) in, for the canonical registers of a line
+template <int RES, bool LEAN = false>
+__device__ __forceinline__ void scale_odd(cf* out, const cf* in, int lt) {
+  const LineK<RES, LEAN> k(lt);
+#pragma unroll
+  for (int v = 0; v < LineK<RES>::E; ++v) out[v] = cscale(in[v], k.odd(v));
+}
+
+// F(k) = g(k) / (-2 pi |kappa|^2) / N, and 0 at k = 0 (the inverse's 1/N folded
+// in), at element v of the line along axis 0.
+template <int RES, bool LEAN>
+__device__ __forceinline__ float spectral_F(const float* g1, const LineK<RES, LEAN>& k0, int v, float g12, float q12) {
+  const float q0 = k0.of(v);
   const float K2 = q0 * q0 + q12;
   constexpr float c = -1.0f / (6.283185307179586f * (float)RES * (float)RES * (float)RES);
   // the hardware reciprocal (1 ulp) instead of a full-precision division:
   // it is per element of the j0 passes, where VALU time is half the kernel
-  return K2 == 0.0f ? 0.0f : (g1[k0] * g12 * c) * __builtin_amdgcn_rcpf(K2);
+  const float F = (g1[v < LineK<RES>::E / 2 ? k0.k(v) : RES - k0.k(v)] * g12 * c) * __builtin_amdgcn_rcpf(K2);
+  return v == 0 && K2 == 0.0f ? 0.0f : F;
 }
 
 template <typename Tv>

@@ -579,15 +579,16 @@ __device__ __forceinline__ void b_splat_r2c(const PointRec* __restrict__ sorted,
 // Load TC lines stored transposed (element n of line l at src[n * stride_n +
 // l], two lines per 16-byte load) into the LDS lines rows[l * LS + pidx(n)].
 // All global loads are issued before the LDS writes; ends with a barrier.
-template <int RES, int TC>
+template <int RES, int TC, bool LEAN>
 __device__ __forceinline__ void load_transposed(cf* rows, const cf* __restrict__ src, int64_t stride_n,
                                                 const cf* __restrict__ src2 = nullptr) {
   constexpr int BC = TC * plan_TPL(RES), LS = lstride(RES);
   constexpr int NV = RES * (TC / 2), IT = (NV + BC - 1) / BC;
+  const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
   float4 buf[IT];
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    const int e = threadIdx.x + it * BC;
+    const int e = t + it * BC;
     if (e < NV) {
       const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
       buf[it] = *reinterpret_cast<const float4*>(src + n * stride_n + l2);
@@ -596,7 +597,7 @@ __device__ __forceinline__ void load_transposed(cf* rows, const cf* __restrict__
   if (src2) {  // the sum of two channels (uniform)
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-      const int e = threadIdx.x + it * BC;
+      const int e = t + it * BC;
       if (e < NV) {
         const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
         const float4 y = *reinterpret_cast<const float4*>(src2 + n * stride_n + l2);
@@ -606,7 +607,7 @@ __device__ __forceinline__ void load_transposed(cf* rows, const cf* __restrict__
   }
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    const int e = threadIdx.x + it * BC;
+    const int e = t + it * BC;
     if (e < NV) {
       const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
       rows[l2 * LS + pidx(n)] = cf{buf[it].x, buf[it].y};
@@ -620,15 +621,16 @@ __device__ __forceinline__ void load_transposed(cf* rows, const cf* __restrict__
 // every element n of every line l, two lines per 16-byte store; with masks,
 // only the elements n with keep[n] != 0 and the line pairs with a line whose
 // keep_line is set.
-template <int RES, int TC = tile_cols(RES)>
+template <int RES, int TC, bool LEAN>
 __device__ __forceinline__ void store_transposed(cf* rows, const cf* reg, cf* __restrict__ dst, int64_t stride_n,
-                                                 int l, int lt, const int* keep = nullptr,
+                                                 int l, int lt, const uint8_t* keep = nullptr,
                                                  const int* keep_line = nullptr) {
   constexpr int BC = TC * plan_TPL(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
+  if constexpr (LEAN) lt = opaque_v(lt);
 #pragma unroll
   for (int v = 0; v < E; ++v) rows[l * LS + pidx(lt + TPL * v)] = reg[v];
   __syncthreads();
-  for (int e = threadIdx.x; e < RES * (TC / 2); e += BC) {
+  for (int e = LEAN ? opaque_v(threadIdx.x) : threadIdx.x; e < RES * (TC / 2); e += BC) {
     const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
     if (keep && !keep[n]) continue;
     if (keep_line && !keep_line[l2] && !keep_line[l2 + 1]) continue;
@@ -650,6 +652,7 @@ __device__ __forceinline__ void b_axis1_fwd(const cf* __restrict__ in, cf* __res
                                             int bid) {
   constexpr int H = RES / 2 + 1, TC = tile_cols(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
   constexpr int64_t CH = (int64_t)H * RES * RES;  // elements per channel
+  constexpr bool LEAN = MERGE && RES >= 512;  // see opaque()
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
   stage_table<cols_block(RES)>(stw, tw + RES, RES);
@@ -681,21 +684,22 @@ __device__ __forceinline__ void b_axis1_fwd(const cf* __restrict__ in, cf* __res
     cf acc[E];
 #pragma unroll
     for (int v = 0; v < E; ++v) reg[v] = seg(v) ? src[2 * CH + lt + TPL * v] : cf{0.0f, 0.0f};
-    fft<RES, -1, true, true>(reg, rows + l * LS, lt, stw);
+    fft<RES, -1, true, true, false, LEAN>(reg, rows + l * LS, lt, stw);
     const float k2f = kappa_odd(k2, RES);
 #pragma unroll
     for (int v = 0; v < E; ++v) {
       acc[v] = cf{k2f * reg[v].x, k2f * reg[v].y};
       reg[v] = seg(v) ? src[CH + lt + TPL * v] : cf{0.0f, 0.0f};
     }
-    fft<RES, -1, true, true>(reg, rows + l * LS, lt, stw);
+    fft<RES, -1, true, true, false, LEAN>(reg, rows + l * LS, lt, stw);
+    const LineK<RES, LEAN> k1(lt);
 #pragma unroll
     for (int v = 0; v < E; ++v) {
-      const float k1f = kappa_odd(lt + TPL * v, RES);
+      const float k1f = k1.odd(v);
       reg[v] = cf{acc[v].x + k1f * reg[v].x, acc[v].y + k1f * reg[v].y};
     }
   }
-  store_transposed<RES>(rows, reg, out + ((int64_t)c * H + k2) * RES * RES + a0, (int64_t)RES, l, lt, nullptr,
+  store_transposed<RES, TC, LEAN>(rows, reg, out + ((int64_t)c * H + k2) * RES * RES + a0, (int64_t)RES, l, lt, nullptr,
                         SKIP ? line_live : nullptr);
 }
 
@@ -706,14 +710,14 @@ __device__ __forceinline__ void b_axis1_fwd(const cf* __restrict__ in, cf* __res
 // a plane pass, IN_C) -> C[1][j0][k2][k1].
 // ---------------------------------------------------------------------------
 
-template <int RES, bool IN_C, bool SKIP>
+template <int RES, bool IN_C, bool SKIP, bool LEAN>
 __device__ __forceinline__ void b_fwd_axis0(const cf* __restrict__ in, cf* __restrict__ out,
                                             const cf* __restrict__ tw, float sigma,
                                             const uint32_t* __restrict__ livebits, int bid) {
   constexpr int H = RES / 2 + 1, TC = tile_j0(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
-  __shared__ float g1[RES];
+  __shared__ float g1[RES / 2 + 1];
   stage_table<j0_block(RES)>(stw, tw + RES, RES);
   gauss_table<RES, j0_block(RES)>(g1, sigma);
   const int tb = bid % (RES / TC);
@@ -728,13 +732,12 @@ __device__ __forceinline__ void b_fwd_axis0(const cf* __restrict__ in, cf* __res
   // were not written by P2
   if constexpr (IN_C) {
     const cf* src = in + (int64_t)k2 * RES + a0;  // element j0 of line k1 at src[j0 H RES + l]
-    load_transposed<RES, TC>(rows, src, (int64_t)H * RES);
-    fft<RES, -1, false, true>(reg, rows + l * LS, lt, stw);
-#pragma unroll
-    for (int v = 0; v < E; ++v) acc[v] = cscale(reg[v], kappa_odd(lt + TPL * v, RES));
+    load_transposed<RES, TC, LEAN>(rows, src, (int64_t)H * RES);
+    fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
+    scale_odd<RES, LEAN>(acc, reg, lt);
     // W = kappa_1 v~_1 + kappa_2 v~_2, summed on load
-    load_transposed<RES, TC>(rows, src + CH, (int64_t)H * RES, src + 2 * CH);
-    fft<RES, -1, false, true>(reg, rows + l * LS, lt, stw);
+    load_transposed<RES, TC, LEAN>(rows, src + CH, (int64_t)H * RES, src + 2 * CH);
+    fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
   } else {
     const cf* src = in + ((int64_t)k2 * RES + k1) * RES;
     cf nxt[E];  // W's line is loaded under the first transform
@@ -751,26 +754,25 @@ __device__ __forceinline__ void b_fwd_axis0(const cf* __restrict__ in, cf* __res
     // line until store_transposed's barrier): the tables get a barrier of
     // their own, after the line loads are in flight
     __syncthreads();
-    fft<RES, -1, true, true, true>(reg, rows + l * LS, lt, stw);
+    fft<RES, -1, true, true, true, LEAN>(reg, rows + l * LS, lt, stw);
+    scale_odd<RES, LEAN>(acc, reg, lt);
 #pragma unroll
-    for (int v = 0; v < E; ++v) {
-      acc[v] = cscale(reg[v], kappa_odd(lt + TPL * v, RES));
-      reg[v] = nxt[v];
-    }
-    fft<RES, -1, true, true, true>(reg, rows + l * LS, lt, stw);
+    for (int v = 0; v < E; ++v) reg[v] = nxt[v];
+    fft<RES, -1, true, true, true, LEAN>(reg, rows + l * LS, lt, stw);
   }
   {
-    const float g12 = g1[k1] * g1[k2];
+    const float g12 = gauss_at<RES>(g1, k1) * g1[k2];
     const float q12 = kappa_of(k1, RES) * kappa_of(k1, RES) + kappa_of(k2, RES) * kappa_of(k2, RES);
+    const LineK<RES, LEAN> kk(lt);
 #pragma unroll
     for (int v = 0; v < E; ++v) {
-      const float F = spectral_F<RES>(g1, lt + TPL * v, g12, q12);
+      const float F = spectral_F<RES>(g1, kk, v, g12, q12);
       const cf a{acc[v].x + reg[v].x, acc[v].y + reg[v].y};
       reg[v] = cf{-F * a.y, F * a.x};  // i F sum
     }
   }
-  fft<RES, +1, true, true, !IN_C>(reg, rows + l * LS, lt, stw);
-  store_transposed<RES, TC>(rows, reg, out + (int64_t)k2 * RES + a0, (int64_t)H * RES, l, lt);
+  fft<RES, +1, true, true, !IN_C, LEAN>(reg, rows + l * LS, lt, stw);
+  store_transposed<RES, TC, LEAN>(rows, reg, out + (int64_t)k2 * RES + a0, (int64_t)H * RES, l, lt);
 }
 
 // B3: FFT along j0 of H^, then the conjugate operator -i F kappa_d H^ and the
@@ -779,15 +781,15 @@ __device__ __forceinline__ void b_fwd_axis0(const cf* __restrict__ in, cf* __res
 // unscaled channel U = IFFT_k0(-i F H^) serves both (kappa_1 is applied in
 // the k1 pass, kappa_2 in the k2 pass). B[1][k2][k1][j0] (or C[1][j0][k2][k1],
 // IN_C) -> C[2][j0][k2][k1].
-template <int RES, bool IN_C>
+template <int RES, bool IN_C, bool LEAN>
 __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __restrict__ out,
                                             const cf* __restrict__ tw, float sigma, const int* __restrict__ off,
                                             int bid) {
   constexpr int H = RES / 2 + 1, TC = tile_j0(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
-  __shared__ float g1[RES];
-  __shared__ int live[RES];  // planes some point reaches: the only ones the next passes read
+  __shared__ float g1[RES / 2 + 1];
+  __shared__ uint8_t live[RES];  // planes some point reaches: the only ones the next passes read
   stage_table<j0_block(RES)>(stw, tw + RES, RES);
   gauss_table<RES, j0_block(RES)>(g1, sigma);
   for (int e = threadIdx.x; e < RES; e += j0_block(RES)) live[e] = plane_live<RES>(off, e);
@@ -798,8 +800,8 @@ __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __res
   const int k1 = a0 + l;
   cf h[E], reg[E];
   if constexpr (IN_C) {
-    load_transposed<RES, TC>(rows, in + (int64_t)k2 * RES + a0, (int64_t)H * RES);
-    fft<RES, -1, false, true>(h, rows + l * LS, lt, stw);
+    load_transposed<RES, TC, LEAN>(rows, in + (int64_t)k2 * RES + a0, (int64_t)H * RES);
+    fft<RES, -1, false, true, false, LEAN>(h, rows + l * LS, lt, stw);
   } else {
     const cf* src = in + ((int64_t)k2 * RES + k1) * RES;
 #pragma unroll
@@ -807,22 +809,22 @@ __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __res
     // wavefront-synchronous line transforms, as in P3: the tables and the
     // live flags get a barrier of their own
     __syncthreads();
-    fft<RES, -1, true, true, true>(h, rows + l * LS, lt, stw);
+    fft<RES, -1, true, true, true, LEAN>(h, rows + l * LS, lt, stw);
   }
-  const float g12 = g1[k1] * g1[k2];
+  const float g12 = gauss_at<RES>(g1, k1) * g1[k2];
   const float q12 = kappa_of(k1, RES) * kappa_of(k1, RES) + kappa_of(k2, RES) * kappa_of(k2, RES);
+  const LineK<RES, LEAN> kk(lt);
 #pragma unroll
   for (int v = 0; v < E; ++v) {
-    const float F = spectral_F<RES>(g1, lt + TPL * v, g12, q12);
+    const float F = spectral_F<RES>(g1, kk, v, g12, q12);
     h[v] = cf{F * h[v].y, -F * h[v].x};  // -i F H^
-    const float k0f = kappa_odd(lt + TPL * v, RES);
-    reg[v] = cf{k0f * h[v].x, k0f * h[v].y};
+    reg[v] = cscale(h[v], kk.odd(v));
   }
-  fft<RES, +1, true, true, !IN_C>(reg, rows + l * LS, lt, stw);
-  store_transposed<RES, TC>(rows, reg, out + (int64_t)k2 * RES + a0, (int64_t)H * RES, l, lt, live);
+  fft<RES, +1, true, true, !IN_C, LEAN>(reg, rows + l * LS, lt, stw);
+  store_transposed<RES, TC, LEAN>(rows, reg, out + (int64_t)k2 * RES + a0, (int64_t)H * RES, l, lt, live);
   __syncthreads();
-  fft<RES, +1, true, true, !IN_C>(h, rows + l * LS, lt, stw);
-  store_transposed<RES, TC>(rows, h, out + ((int64_t)RES * H + k2) * RES + a0, (int64_t)H * RES, l, lt, live);
+  fft<RES, +1, true, true, !IN_C, LEAN>(h, rows + l * LS, lt, stw);
+  store_transposed<RES, TC, LEAN>(rows, h, out + ((int64_t)RES * H + k2) * RES + a0, (int64_t)H * RES, l, lt, live);
 }
 
 // ---------------------------------------------------------------------------
@@ -853,6 +855,7 @@ __device__ __forceinline__ void b_axis1_inv(const cf* __restrict__ in, cf* __res
   const int j0 = tb * TC + l;
   const cf* src = in + c * CH + ((int64_t)j0 * H + k2) * RES;
   cf* dst = out + c * CH + ((int64_t)k2 * RES + j0) * RES;
+  constexpr bool LEAN = SPLIT && RES >= 512;  // see opaque()
   cf reg[E];
   if constexpr (!SPLIT) {
 #pragma unroll
@@ -882,17 +885,15 @@ __device__ __forceinline__ void b_axis1_inv(const cf* __restrict__ in, cf* __res
     } else {
       cf u[E];
 #pragma unroll
-      for (int v = 0; v < E; ++v) {
-        u[v] = live ? src[lt + TPL * v] : cf{0.0f, 0.0f};
-        reg[v] = cscale(u[v], kappa_odd(lt + TPL * v, RES));
-      }
-      fft<RES, +1, true, true>(reg, rows + l * LS, lt, stw);
+      for (int v = 0; v < E; ++v) u[v] = live ? src[lt + TPL * v] : cf{0.0f, 0.0f};
+      scale_odd<RES, LEAN>(reg, u, lt);
+      fft<RES, +1, true, true, false, LEAN>(reg, rows + l * LS, lt, stw);
 #pragma unroll
       for (int v = 0; v < E; ++v) {
         const int j1 = lt + TPL * v;
         if (live && tile_live[l * NT + j1 / TR]) dst[j1] = reg[v];
       }
-      fft<RES, +1, true, true>(u, rows + l * LS, lt, stw);
+      fft<RES, +1, true, true, false, LEAN>(u, rows + l * LS, lt, stw);
 #pragma unroll
       for (int v = 0; v < E; ++v) {
         const int j1 = lt + TPL * v;
@@ -1084,6 +1085,7 @@ struct Plane {
   // waves per SIMD asked of the register allocator: two workgroups per CU
   // where LDS allows it (at most 128 VGPRs then)
   static constexpr int WPE = RES == 256 ? 4 : 2;
+  static constexpr bool LEAN = RES == 128;  // see opaque()
   static_assert(plan_E(RES) == 16 && plan_E(M) == 16, "plane passes hold 16 elements per thread");
   static_assert(NCHUNK * RC == RES && RES / KP == RC, "chunks and parts tile the plane");
 };
@@ -1125,7 +1127,8 @@ __device__ __forceinline__ bool pf_rows(cf* rows, const cf* stw, const PointRec*
   fill_rows<RES, RC, BLOCK, MODE>(rows, sorted, R, gin, sqa, j0, a0, ch);
   {
     cf reg[16];
-    fft<M, -1, false, false>(reg, rows + (t / PL::TPR) * LSR, t % PL::TPR, stw, row_swz(M, t / PL::TPR));
+    fft<M, -1, false, false, false, PL::LEAN>(reg, rows + (t / PL::TPR) * LSR, t % PL::TPR, stw,
+                                              row_swz(M, t / PL::TPR));
   }
   return true;
 }
@@ -1205,11 +1208,10 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
       }
       __syncthreads();  // the rows are overwritten next
     }
-    fft<RES, -1, true, true>(reg, buf + col * LSC, lt, ctw);
+    fft<RES, -1, true, true, false, PL::LEAN>(reg, buf + col * LSC, lt, ctw);
   }
   if (set == 1 && kk != 0) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) reg[v] = cscale(reg[v], kappa_odd(lt + TPL * v, RES));
+    scale_odd<RES>(reg, reg, lt);
   }
   if (set == 2) {
     // kappa_2(k2); zero in the packed column (kappa_2^odd vanishes at k2 = 0 and M)
@@ -1325,10 +1327,7 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
 #pragma unroll
       for (int v = 0; v < 16; ++v) reg[v] = src[(int64_t)kk * RES + lt + TPL * v];
     }
-    if (MODE == PI_BWD && c == 1) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) reg[v] = cscale(reg[v], kappa_odd(lt + TPL * v, RES));
-    }
+    if (MODE == PI_BWD && c == 1) scale_odd<RES>(reg, reg, lt);
     if (MODE == PI_BWD && c == 2) {
       const float k2f = kk == 0 ? 0.0f : kappa_odd(kk, RES);
 #pragma unroll
@@ -1340,7 +1339,7 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
     // flight (P45 48.4 -> 47.4 us; at 64 and 128 the workgroup barriers cost
     // less than the extra ones here)
     if (WS && rd == 0) __syncthreads();
-    fft<RES, +1, true, true, WS>(reg, buf + col * LSC, lt, ctw);
+    fft<RES, +1, true, true, WS, PL::LEAN>(reg, buf + col * LSC, lt, ctw);
 #pragma unroll
     for (int w2 = 0; w2 < VK; ++w2) {
       cf x = reg[w2];
@@ -1408,7 +1407,7 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
   __syncthreads();
   {
     cf reg[16];
-    fft<M, +1, false, false, WS>(reg, buf + (t / TPR) * LSR, t % TPR, stw, row_swz(M, t / TPR));
+    fft<M, +1, false, false, WS, PL::LEAN>(reg, buf + (t / TPR) * LSR, t % TPR, stw, row_swz(M, t / TPR));
   }
   if constexpr (WS) __syncthreads();  // the rows are read below across wavefronts
   // rows now hold real lines, sample n of row l at float slot 2 rpos(l, n/2) + (n&1)
@@ -1816,18 +1815,22 @@ __global__ __launch_bounds__(cols_block(RES)) void k_axis1_fwd(const Batch<MAXJ>
   b_axis1_fwd<RES, MERGE, SKIP>(w.X, w.Y, B.tw, sv.hdr->tlive, bid);
 }
 
+// Whether the j0 passes (three transforms) hold down their registers: where
+// the grid has more workgroups than run at once (256 and 512, batches).
+__host__ __device__ constexpr bool j0_lean(int res, int maxj) { return res >= 256 || maxj > 1; }
+
 template <int RES, bool SKIP, int MAXJ>
 __global__ __launch_bounds__(j0_block(RES)) void k_fwd_axis0(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   constexpr bool SK = SKIP && !use_plane(RES);
-  b_fwd_axis0<RES, use_plane(RES), SK>(w.Y, w.X, B.tw, J.sigma, SK ? sv.hdr->live : nullptr, bid);
+  b_fwd_axis0<RES, use_plane(RES), SK, j0_lean(RES, MAXJ)>(w.Y, w.X, B.tw, J.sigma, SK ? sv.hdr->live : nullptr, bid);
 }
 
 template <int RES, int MAXJ>
 __global__ __launch_bounds__(j0_block(RES)) void k_bwd_axis0(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   PSR_BWD_GUARD(RES);
-  b_bwd_axis0<RES, use_plane(RES)>(w.Y, w.X, B.tw, J.sigma, sv.off, bid);
+  b_bwd_axis0<RES, use_plane(RES), j0_lean(RES, MAXJ)>(w.Y, w.X, B.tw, J.sigma, sv.off, bid);
 }
 
 template <int RES, bool SPLIT, int MAXJ>

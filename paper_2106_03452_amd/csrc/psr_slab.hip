@@ -37,6 +37,9 @@ namespace psr {
 namespace {
 
 constexpr int kScanBlock = 1024;
+// Waves per SIMD asked of the register allocator for S1: two of its 512-thread
+// workgroups fit a CU by LDS from 128 on, which needs at most 128 VGPRs.
+constexpr int slab_rows_waves(int res) { return res >= 128 ? 4 : 2; }
 
 // Ranges of sorted points whose corners reach rows [a0, a0 + TR) of plane j0:
 // points sorted by bin b0 * RES + b1, floor planes j0 - 1 and j0, floor rows
@@ -74,13 +77,14 @@ __device__ __forceinline__ Ranges slab_ranges(const int* __restrict__ off, int j
 // Load a column tile of TC lines into LDS: element n of lines l, l + 1 (l
 // even) from one 16-byte load at addr(n) + l; lines at or past nvalid read as
 // zero. Ends with a barrier.
-template <int RES, int TC, typename Addr>
+template <int RES, int TC, bool LEAN, typename Addr>
 __device__ __forceinline__ void load_cols(cf* rows, Addr addr, int nvalid) {
   constexpr int BC = TC * plan_TPL(RES), LS = lstride(RES), NV = RES * (TC / 2), IT = (NV + BC - 1) / BC;
   float4 buf[IT];
+  const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    const int e = threadIdx.x + it * BC;
+    const int e = t + it * BC;
     buf[it] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (e < NV) {
       const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
@@ -92,7 +96,7 @@ __device__ __forceinline__ void load_cols(cf* rows, Addr addr, int nvalid) {
   }
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    const int e = threadIdx.x + it * BC;
+    const int e = t + it * BC;
     if (e < NV) {
       const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
       rows[l2 * LS + pidx(n)] = cf{buf[it].x, buf[it].y};
@@ -107,9 +111,10 @@ __device__ __forceinline__ void load_cols(cf* rows, Addr addr, int nvalid) {
 // are not stored (the padding slot of a pair is written, it is never read as
 // data). The LDS lines must be free (the transform's last stage ended with a
 // barrier).
-template <int RES, int TC, typename Addr>
+template <int RES, int TC, bool LEAN, typename Addr>
 __device__ __forceinline__ void store_cols(cf* rows, const cf* reg, int l, int lt, Addr addr, int nvalid) {
   constexpr int BC = TC * plan_TPL(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
+  if constexpr (LEAN) lt = opaque_v(lt);
 #pragma unroll
   for (int v = 0; v < E; ++v) rows[l * LS + pidx(lt + TPL * v)] = reg[v];
   __syncthreads();
@@ -249,7 +254,8 @@ __global__ __launch_bounds__(256) void k_slab_scatter(SlabArgs a) {
 // field) -> r2c FFT along j2 -> A_g[c][j0 - g s], k2-tiled rows of r/2 + 1.
 // ---------------------------------------------------------------------------
 template <int RES, bool LOAD>
-__global__ __launch_bounds__(slab_rows_block(RES)) void k_slab_rows_fwd(const SlabArgs a, int g) {
+__global__ __launch_bounds__(slab_rows_block(RES)) __attribute__((amdgpu_waves_per_eu(slab_rows_waves(RES))))
+void k_slab_rows_fwd(const SlabArgs a, int g) {
   constexpr int M = RES / 2, H = M + 1, HP = slab_hp(RES), TR = slab_rows(RES), NT = RES / TR;
   constexpr int BR = slab_rows_block(RES), TPL = plan_TPL(M), E = plan_E(M), LS = row_ls(M);
   __shared__ __align__(16) cf rows[TR * LS];
@@ -300,7 +306,8 @@ __global__ __launch_bounds__(slab_rows_block(RES)) void k_slab_rows_fwd(const Sl
 // 1 and 2); element k1 goes to block (k1 / q, g): [2][s][nt][q][tc].
 // ---------------------------------------------------------------------------
 template <int RES>
-__global__ __launch_bounds__(slab_cols_block(RES)) void k_slab_fft_j1(const SlabArgs a, const BlockPtrs dst, int g) {
+__global__ __launch_bounds__(slab_cols_block(RES)) __attribute__((amdgpu_waves_per_eu(4)))
+void k_slab_fft_j1(const SlabArgs a, const BlockPtrs dst, int g) {
   constexpr int H = RES / 2 + 1, HP = slab_hp(RES), TC = slab_cols(RES), NKT = HP / TC;
   constexpr int TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES), BC = slab_cols_block(RES);
   __shared__ cf rows[TC * LS];
@@ -321,24 +328,25 @@ __global__ __launch_bounds__(slab_cols_block(RES)) void k_slab_fft_j1(const Slab
   const cf* src = a.A + ((int64_t)3 * g * s + j0l) * RES * HP + (int64_t)kt * RES * TC;
   cf reg[E];
   if (oc == 0) {
-    load_cols<RES, TC>(rows, [&](int n) { return src + (int64_t)n * TC; }, nvalid);
-    fft<RES, -1, false, true>(reg, rows + l * LS, lt, stw);
+    load_cols<RES, TC, true>(rows, [&](int n) { return src + (int64_t)n * TC; }, nvalid);
+    fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
   } else {
     cf acc[E];
-    load_cols<RES, TC>(rows, [&](int n) { return src + 2 * CH + (int64_t)n * TC; }, nvalid);
-    fft<RES, -1, false, true>(reg, rows + l * LS, lt, stw);
+    load_cols<RES, TC, true>(rows, [&](int n) { return src + 2 * CH + (int64_t)n * TC; }, nvalid);
+    fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
     const float k2f = kappa_odd(k2a + l, RES);
 #pragma unroll
     for (int v = 0; v < E; ++v) acc[v] = cscale(reg[v], k2f);
-    load_cols<RES, TC>(rows, [&](int n) { return src + CH + (int64_t)n * TC; }, nvalid);
-    fft<RES, -1, false, true>(reg, rows + l * LS, lt, stw);
+    load_cols<RES, TC, true>(rows, [&](int n) { return src + CH + (int64_t)n * TC; }, nvalid);
+    fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
+    const LineK<RES, true> k1(lt);
 #pragma unroll
     for (int v = 0; v < E; ++v) {
-      const float k1f = kappa_odd(lt + TPL * v, RES);
+      const float k1f = k1.odd(v);
       reg[v] = cf{acc[v].x + k1f * reg[v].x, acc[v].y + k1f * reg[v].y};
     }
   }
-  store_cols<RES, TC>(
+  store_cols<RES, TC, true>(
       rows, reg, l, lt,
       [&](int n) { return dp[n >> lq] + (((int64_t)(oc * s + j0l) * NKT + kt) * q + (n & (q - 1))) * TC; },
       nvalid);
@@ -351,21 +359,17 @@ __global__ __launch_bounds__(slab_cols_block(RES)) void k_slab_fft_j1(const Slab
 // [s][nt][q][tc].
 // ---------------------------------------------------------------------------
 template <int RES>
-__global__ __launch_bounds__(slab_cols_block(RES)) void k_slab_pencil_j0(const SlabArgs a, const BlockPtrs src,
-                                                                         const BlockPtrs dst, int h) {
+__global__ __launch_bounds__(slab_cols_block(RES)) __attribute__((amdgpu_waves_per_eu(4)))
+void k_slab_pencil_j0(const SlabArgs a, const BlockPtrs src, const BlockPtrs dst, int h) {
   constexpr int M = RES / 2, H = M + 1, HP = slab_hp(RES), TC = slab_cols(RES), NKT = HP / TC;
   constexpr int TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES), BC = slab_cols_block(RES);
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
-  __shared__ float g1[RES];
-  __shared__ cf* sp[kMaxSlabs];
-  __shared__ cf* dp[kMaxSlabs];
+  __shared__ float g1[M + 1];  // the Gaussian is even in k
+  __shared__ cf* bp[kMaxSlabs];  // the blocks read, then the blocks written
   stage_table<BC>(stw, a.tw + RES, RES);
   gauss_table<RES, BC>(g1, a.sigma);
-  for (int e = threadIdx.x; e < a.G; e += BC) {
-    sp[e] = src.p[e];
-    dp[e] = dst.p[e];
-  }
+  for (int e = threadIdx.x; e < a.G; e += BC) bp[e] = src.p[e];
   __syncthreads();  // the block tables are read by the first loads
   const int s = RES / a.G, q = s, ls = ilog2(s);
   const int kt = blockIdx.x % NKT, k1l = blockIdx.x / NKT;
@@ -373,29 +377,30 @@ __global__ __launch_bounds__(slab_cols_block(RES)) void k_slab_pencil_j0(const S
   const int k1 = h * q + k1l;
   const int l = threadIdx.x / TPL, lt = threadIdx.x % TPL;
   cf acc[E], reg[E];
-  load_cols<RES, TC>(
-      rows, [&](int n) { return sp[n >> ls] + (((int64_t)(n & (s - 1)) * NKT + kt) * q + k1l) * TC; }, nvalid);
-  fft<RES, -1, false, true>(reg, rows + l * LS, lt, stw);
-#pragma unroll
-  for (int v = 0; v < E; ++v) acc[v] = cscale(reg[v], kappa_odd(lt + TPL * v, RES));
-  load_cols<RES, TC>(
-      rows, [&](int n) { return sp[n >> ls] + (((int64_t)(s + (n & (s - 1))) * NKT + kt) * q + k1l) * TC; },
+  load_cols<RES, TC, true>(
+      rows, [&](int n) { return bp[n >> ls] + (((int64_t)(n & (s - 1)) * NKT + kt) * q + k1l) * TC; }, nvalid);
+  fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
+  scale_odd<RES, true>(acc, reg, lt);
+  load_cols<RES, TC, true>(
+      rows, [&](int n) { return bp[n >> ls] + (((int64_t)(s + (n & (s - 1))) * NKT + kt) * q + k1l) * TC; },
       nvalid);
-  fft<RES, -1, false, true>(reg, rows + l * LS, lt, stw);
+  for (int e = threadIdx.x; e < a.G; e += BC) bp[e] = dst.p[e];  // the loads are done; seen after the next barrier
+  fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
   {
     const int k2 = imin(k2a + l, M);  // padding lines are zero; any finite factor will do
-    const float g12 = g1[k1] * g1[k2];
+    const float g12 = gauss_at<RES>(g1, k1) * g1[k2];
     const float q12 = kappa_of(k1, RES) * kappa_of(k1, RES) + kappa_of(k2, RES) * kappa_of(k2, RES);
+    const LineK<RES, true> k0(lt);
 #pragma unroll
     for (int v = 0; v < E; ++v) {
-      const float F = spectral_F<RES>(g1, lt + TPL * v, g12, q12);
+      const float F = spectral_F<RES>(g1, k0, v, g12, q12);
       const cf x{acc[v].x + reg[v].x, acc[v].y + reg[v].y};
       reg[v] = cf{-F * x.y, F * x.x};  // i F sum
     }
   }
-  fft<RES, +1, true, true>(reg, rows + l * LS, lt, stw);
-  store_cols<RES, TC>(
-      rows, reg, l, lt, [&](int n) { return dp[n >> ls] + (((int64_t)(n & (s - 1)) * NKT + kt) * q + k1l) * TC; },
+  fft<RES, +1, true, true, false, true>(reg, rows + l * LS, lt, stw);
+  store_cols<RES, TC, true>(
+      rows, reg, l, lt, [&](int n) { return bp[n >> ls] + (((int64_t)(n & (s - 1)) * NKT + kt) * q + k1l) * TC; },
       nvalid);
 }
 
@@ -417,11 +422,11 @@ __global__ __launch_bounds__(slab_cols_block(RES)) void k_slab_ifft_k1(const Sla
   const int k2a = kt * TC, nvalid = H - k2a;
   const int l = threadIdx.x / TPL, lt = threadIdx.x % TPL;
   cf reg[E];
-  load_cols<RES, TC>(
+  load_cols<RES, TC, false>(
       rows, [&](int n) { return sp[n >> lq] + (((int64_t)j0l * NKT + kt) * q + (n & (q - 1))) * TC; }, nvalid);
   fft<RES, +1, false, true>(reg, rows + l * LS, lt, stw);
   cf* const y = a.A + (int64_t)(g * s + j0l) * RES * HP + (int64_t)kt * RES * TC;
-  store_cols<RES, TC>(rows, reg, l, lt, [&](int n) { return y + (int64_t)n * TC; }, nvalid);
+  store_cols<RES, TC, false>(rows, reg, l, lt, [&](int n) { return y + (int64_t)n * TC; }, nvalid);
 }
 
 // ---------------------------------------------------------------------------
