@@ -163,6 +163,7 @@ psr::SlabArgs slab_args(psr_ctx* ctx, const psr::SlabLayout& L, void* ws, int64_
   a.counts = reinterpret_cast<int*>(b + L.counts);
   a.off = reinterpret_cast<int*>(b + L.off);
   a.bsum = reinterpret_cast<int*>(b + L.bsum);
+  a.live = reinterpret_cast<uint64_t*>(b + L.live);
   a.tmp = reinterpret_cast<psr::PointRec*>(b + L.tmp);
   a.colrank = reinterpret_cast<int2*>(b + L.colrank);
   a.sorted = reinterpret_cast<psr::PointRec*>(b + L.sorted);

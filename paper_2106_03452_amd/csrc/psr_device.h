@@ -180,12 +180,12 @@ __device__ __forceinline__ void stage_table(cf* dst, const cf* __restrict__ src,
 // gin; the -Q delta_0 term is applied at the points from the point-source
 // table, see b_bwd_point_finalize); KIND 2: rows of v_ch from gin. Ends with a
 // barrier.
-template <int RES, int NROWS, int BLOCK, int KIND>
+template <int RES, int NROWS, int BLOCK, int KIND, bool LEAN = false>
 __device__ __forceinline__ void fill_rows(cf* rows, const PointRec* __restrict__ sorted, const Ranges& R,
                                           const float* __restrict__ gin, float3 sqa, int j0, int a0, int ch) {
   constexpr int M = RES / 2;
   constexpr int64_t N3 = (int64_t)RES * RES * RES;
-  const int t = threadIdx.x;
+  const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
   // the NROWS rows are one contiguous run of NROWS * RES floats
   constexpr int NV = NROWS * M / 2;  // float4 = two complex slots
   constexpr int IT = (NV + BLOCK - 1) / BLOCK;

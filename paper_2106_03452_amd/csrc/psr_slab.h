@@ -25,7 +25,7 @@ constexpr int kSlabMaxRes = 1024;  // the packed floor vertex of a point record 
 
 // Row passes of a slab (splat + r2c along j2, c2r along k2): slab_rows(res)
 // consecutive j1 rows of one plane per workgroup, plan_TPL(res/2) threads
-// per row.
+// per row (at most 64 row tiles per plane: one bit each in SlabArgs::live).
 __host__ __device__ constexpr int slab_rows(int res) { return imin(res, PSR_ROW_THREADS / plan_TPL(res / 2)); }
 __host__ __device__ constexpr int slab_rows_block(int res) { return slab_rows(res) * plan_TPL(res / 2); }
 // Column passes (FFT along j1, j0 and k1): slab_cols(res) neighbouring k2
@@ -60,7 +60,7 @@ struct SlabResult {
 };
 
 struct SlabLayout {
-  size_t hdr, counts, off, bsum, tmp, colrank, sorted, val, red, A, X, Z, halo, total;
+  size_t hdr, counts, off, bsum, live, tmp, colrank, sorted, val, red, A, X, Z, halo, total;
 };
 
 // Spectra are k2-tiled: k2 in tiles of tc = slab_cols(r) values, nt = hp / tc
@@ -84,6 +84,8 @@ __host__ __device__ inline SlabLayout slab_layout(int res, int64_t P, int G) {
   o += align256((bins + 1) * 4);
   L.bsum = o;
   o += align256(1024 * 4);
+  L.live = o;
+  o += align256((size_t)res * 8);
   L.tmp = o;
   o += align256((size_t)P * sizeof(PointRec));
   L.colrank = o;
@@ -123,6 +125,7 @@ struct SlabArgs {
   int* counts;
   int* off;
   int* bsum;
+  uint64_t* live;          // per plane, bit i: some point's corners reach row tile i
   PointRec* tmp;
   int2* colrank;
   PointRec* sorted;

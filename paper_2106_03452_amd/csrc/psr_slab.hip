@@ -40,6 +40,9 @@ constexpr int kScanBlock = 1024;
 // Waves per SIMD asked of the register allocator for S1: two of its 512-thread
 // workgroups fit a CU by LDS from 128 on, which needs at most 128 VGPRs.
 constexpr int slab_rows_waves(int res) { return res >= 128 ? 4 : 2; }
+// workgroups of S1 (two fit a CU): four times what runs at once, so that the
+// live tiles, which crowd together, spread evenly
+constexpr int kRowGrid = 2048;
 
 // Ranges of sorted points whose corners reach rows [a0, a0 + TR) of plane j0:
 // points sorted by bin b0 * RES + b1, floor planes j0 - 1 and j0, floor rows
@@ -75,10 +78,13 @@ __device__ __forceinline__ Ranges slab_ranges(const int* __restrict__ off, int j
 }
 
 // Load a column tile of TC lines into LDS: element n of lines l, l + 1 (l
-// even) from one 16-byte load at addr(n) + l; lines at or past nvalid read as
-// zero. Ends with a barrier.
-template <int RES, int TC, bool LEAN, typename Addr>
-__device__ __forceinline__ void load_cols(cf* rows, Addr addr, int nvalid) {
+// even) from one 16-byte load at addr(n) + l; lines at or past nvalid, and
+// elements whose keep(n) is false, are zero and not read. Ends with a barrier.
+struct KeepAll {
+  __device__ __forceinline__ bool operator()(int) const { return true; }
+};
+template <int RES, int TC, bool LEAN, typename Addr, typename Keep = KeepAll>
+__device__ __forceinline__ void load_cols(cf* rows, Addr addr, int nvalid, Keep keep = Keep()) {
   constexpr int BC = TC * plan_TPL(RES), LS = lstride(RES), NV = RES * (TC / 2), IT = (NV + BC - 1) / BC;
   float4 buf[IT];
   const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
@@ -88,7 +94,7 @@ __device__ __forceinline__ void load_cols(cf* rows, Addr addr, int nvalid) {
     buf[it] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (e < NV) {
       const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
-      if (l2 < nvalid) {
+      if (l2 < nvalid && keep(n)) {
         buf[it] = *reinterpret_cast<const float4*>(addr(n) + l2);
         if (l2 + 1 >= nvalid) buf[it].z = buf[it].w = 0.0f;
       }
@@ -242,7 +248,18 @@ __global__ __launch_bounds__(kScanBlock) void k_slab_scan_add(SlabArgs a, int n)
   if (i < n) a.off[i] += a.bsum[blockIdx.x];
 }
 
+// Also the row-tile bitmaps of the planes (the offsets are complete here):
+// one wavefront per plane, lane = row tile.
+template <int RES>
 __global__ __launch_bounds__(256) void k_slab_scatter(SlabArgs a) {
+  constexpr int TR = slab_rows(RES), NT = RES / TR;
+  static_assert(NT <= 64, "one bit per row tile");
+  const int lane = threadIdx.x & 63;
+  for (int j0 = blockIdx.x * 4 + (threadIdx.x >> 6); j0 < RES; j0 += gridDim.x * 4) {
+    const bool on = lane < NT && slab_ranges<RES, TR>(a.off, j0, (lane < NT ? lane : 0) * TR).total > 0;
+    const uint64_t m = __ballot(on);
+    if (lane == 0) a.live[j0] = m;
+  }
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= a.P) return;
   const int2 cr = a.colrank[i];
@@ -252,6 +269,11 @@ __global__ __launch_bounds__(256) void k_slab_scatter(SlabArgs a) {
 // ---------------------------------------------------------------------------
 // S1: rows of one plane of slab g (one channel) -> LDS splat (or the test
 // field) -> r2c FFT along j2 -> A_g[c][j0 - g s], k2-tiled rows of r/2 + 1.
+// Row tiles that no point reaches are zero: they are not written, and S2 does
+// not read them (65 % of the 1M-point scene's tiles at 1024^3: S1 4.35 -> 2.76
+// ms, S2 5.63 -> 4.04 ms). A workgroup takes every gridDim.x-th (tile, channel)
+// item, so a dead item costs one test of the bitmap instead of a workgroup that
+// holds its LDS for a memory latency.
 // ---------------------------------------------------------------------------
 template <int RES, bool LOAD>
 __global__ __launch_bounds__(slab_rows_block(RES)) __attribute__((amdgpu_waves_per_eu(slab_rows_waves(RES))))
@@ -261,51 +283,73 @@ void k_slab_rows_fwd(const SlabArgs a, int g) {
   __shared__ __align__(16) cf rows[TR * LS];
   __shared__ cf stw[M];      // FFT table of length M
   __shared__ cf rtw[M + 1];  // W_RES^k, k in [0, M], for the r2c post-processing
-  const int s = RES / a.G;
-  const int T = blockIdx.x % (s * NT), c = blockIdx.x / (s * NT);
-  const int j0l = T / NT, a0 = (T % NT) * TR, j0 = g * s + j0l;
+  const int s = RES / a.G, items = 3 * s * NT;
   constexpr int TC = slab_cols(RES);
-  // k2-tiled plane: element (j1, k2) at ((k2 / TC) RES + j1) TC + k2 % TC; the
-  // loops below run tile by tile, so each tile's TR rows are one contiguous run
-  cf* const out = a.A + ((int64_t)(3 * g + c) * s + j0l) * RES * HP + (int64_t)a0 * TC;
-  const int t = threadIdx.x;
-  Ranges R{};
-  if constexpr (!LOAD) {
-    R = slab_ranges<RES, TR>(a.off, j0, a0);
-    if (R.total == 0) {  // no point reaches these rows: their spectra are zero
-      for (int e = t; e < TR * HP; e += BR) {
-        const int kk = e % TC, l = (e / TC) % TR, kt = e / (TC * TR);
-        if (kt * TC + kk < H) out[((int64_t)kt * RES + l) * TC + kk] = cf{0.0f, 0.0f};
-      }
-      return;
-    }
-  }
   stage_table<BR>(stw, a.tw + M, M);
   stage_table<BR>(rtw, a.tw + RES, M + 1);
-  fill_rows<RES, TR, BR, LOAD ? 2 : 0>(rows, a.sorted, R, a.field, make_float3(1.0f, 0.0f, 1.0f), j0, a0, c);
-  {
-    cf reg[E];
-    const int l = t / TPL;
-    fft<M, -1, false, false>(reg, rows + l * LS, t % TPL, stw, row_swz(M, l));
-  }
-  // X[k] = E_k + W_r^k O_k with E = (Z_k + Z*_{M-k})/2, O = (Z_k - Z*_{M-k})/(2i)
-  for (int e = t; e < TR * HP; e += BR) {
-    const int kk = e % TC, l = (e / TC) % TR, kt = e / (TC * TR), k = kt * TC + kk;
-    if (k >= H) continue;
-    const cf zk = rows[rpos<M>(l, k == M ? 0 : k)];
-    const cf zm = rows[rpos<M>(l, k == 0 ? 0 : M - k)];
-    const cf Ee{0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y)};
-    const cf Oo{0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x)};
-    out[((int64_t)kt * RES + l) * TC + kk] = cadd(Ee, cmul(rtw[k], Oo));
+  for (int it = blockIdx.x; it < items; it += gridDim.x) {
+    // the three channels of a tile 8 items apart, so on one XCD (the grid is
+    // a multiple of 8 wherever it is smaller than the items): its L2 serves
+    // their reads of the tile's point records
+    int T, c;
+    if ((s * NT) % 8 == 0) {
+      c = (it >> 3) % 3;
+      T = (it >> 3) / 3 * 8 + (it & 7);
+    } else {
+      T = it % (s * NT);
+      c = it / (s * NT);
+    }
+    const int j0l = T / NT, a0 = (T % NT) * TR, j0 = g * s + j0l;
+    Ranges R{};
+    if constexpr (!LOAD) {
+      if (!((a.live[j0] >> (T % NT)) & 1)) continue;
+      R = slab_ranges<RES, TR>(a.off, j0, a0);
+    }
+    // k2-tiled plane: element (j1, k2) at ((k2 / TC) RES + j1) TC + k2 % TC; the
+    // loops below run tile by tile, so each tile's TR rows are one contiguous run
+    cf* const out = a.A + ((int64_t)(3 * g + c) * s + j0l) * RES * HP + (int64_t)a0 * TC;
+    // everything per item is computed anew (LEAN): hoisted out of the item
+    // loop the addresses spilled, and each transform waited on 40 reloads
+    // (10.5 us of an item's 31 instead of 3)
+    fill_rows<RES, TR, BR, LOAD ? 2 : 0, true>(rows, a.sorted, R, a.field, make_float3(1.0f, 0.0f, 1.0f), j0, a0, c);
+    const int t = opaque_v(threadIdx.x);
+    {
+      cf reg[E];
+      const int l = t / TPL;
+      fft<M, -1, false, false, false, true>(reg, rows + l * LS, t % TPL, stw, row_swz(M, l));
+    }
+    // X[k] = E_k + W_r^k O_k with E = (Z_k + Z*_{M-k})/2, O = (Z_k - Z*_{M-k})/(2i);
+    // k and k + 1 (k even) per thread, one 16-byte store (of a last pair k = M,
+    // M + 1 only k = M is data; the slot beside it is padding)
+    for (int e = t; e < TR * HP / 2; e += BR) {
+      const int kk = 2 * (e % (TC / 2)), l = (e / (TC / 2)) % TR, kt = e / (TC / 2 * TR), k = kt * TC + kk;
+      if (k >= H) continue;
+      float o[4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int kh = k + h <= M ? k + h : M;
+        const cf zk = rows[rpos<M>(l, kh == M ? 0 : kh)];
+        const cf zm = rows[rpos<M>(l, kh == 0 ? 0 : M - kh)];
+        const cf Ee{0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y)};
+        const cf Oo{0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x)};
+        const cf X = cadd(Ee, cmul(rtw[kh], Oo));
+        o[2 * h] = X.x;
+        o[2 * h + 1] = X.y;
+      }
+      *reinterpret_cast<float4*>(out + ((int64_t)kt * RES + l) * TC + kk) = make_float4(o[0], o[1], o[2], o[3]);
+    }
+    __syncthreads();  // the rows are zeroed for the next item
   }
 }
 
 // ---------------------------------------------------------------------------
 // S2: FFT along j1 of slab g. Output channel 0 = v~_0, channel 1 =
 // W = kappa_1(k1) v~_1 + kappa_2(k2) v~_2 (all the j0 pass needs of channels
-// 1 and 2); element k1 goes to block (k1 / q, g): [2][s][nt][q][tc].
+// 1 and 2); element k1 goes to block (k1 / q, g): [2][s][nt][q][tc]. Row tiles
+// that no point reaches were not written by S1 (SKIP): they are zero, and a
+// plane with none else is written as zeros without its transforms.
 // ---------------------------------------------------------------------------
-template <int RES>
+template <int RES, bool SKIP>
 __global__ __launch_bounds__(slab_cols_block(RES)) __attribute__((amdgpu_waves_per_eu(4)))
 void k_slab_fft_j1(const SlabArgs a, const BlockPtrs dst, int g) {
   constexpr int H = RES / 2 + 1, HP = slab_hp(RES), TC = slab_cols(RES), NKT = HP / TC;
@@ -327,17 +371,30 @@ void k_slab_fft_j1(const SlabArgs a, const BlockPtrs dst, int g) {
   // the tile of channel 0 (k2-tiled planes: one contiguous RES x TC block)
   const cf* src = a.A + ((int64_t)3 * g * s + j0l) * RES * HP + (int64_t)kt * RES * TC;
   cf reg[E];
+  constexpr int TR = slab_rows(RES);
+  const uint64_t live = SKIP ? a.live[g * s + j0l] : ~(uint64_t)0;
+  auto keep = [&](int n) { return !SKIP || ((live >> (n / TR)) & 1); };
+  if (SKIP && live == 0) {
+    __syncthreads();  // the block table
+    for (int e = threadIdx.x; e < RES * (TC / 2); e += BC) {
+      const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
+      if (l2 < nvalid)
+        *reinterpret_cast<float4*>(dp[n >> lq] + (((int64_t)(oc * s + j0l) * NKT + kt) * q + (n & (q - 1))) * TC + l2) =
+            make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    return;
+  }
   if (oc == 0) {
-    load_cols<RES, TC, true>(rows, [&](int n) { return src + (int64_t)n * TC; }, nvalid);
+    load_cols<RES, TC, true>(rows, [&](int n) { return src + (int64_t)n * TC; }, nvalid, keep);
     fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
   } else {
     cf acc[E];
-    load_cols<RES, TC, true>(rows, [&](int n) { return src + 2 * CH + (int64_t)n * TC; }, nvalid);
+    load_cols<RES, TC, true>(rows, [&](int n) { return src + 2 * CH + (int64_t)n * TC; }, nvalid, keep);
     fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
     const float k2f = kappa_odd(k2a + l, RES);
 #pragma unroll
     for (int v = 0; v < E; ++v) acc[v] = cscale(reg[v], k2f);
-    load_cols<RES, TC, true>(rows, [&](int n) { return src + CH + (int64_t)n * TC; }, nvalid);
+    load_cols<RES, TC, true>(rows, [&](int n) { return src + CH + (int64_t)n * TC; }, nvalid, keep);
     fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
     const LineK<RES, true> k1(lt);
 #pragma unroll
@@ -447,9 +504,28 @@ __global__ __launch_bounds__(slab_rows_block(RES)) void k_slab_rows_inv(const Sl
   stage_table<BR>(rtw, a.tw + RES, M + 1);
   constexpr int TC = slab_cols(RES);
   const cf* in = a.A + (int64_t)(g * s + j0l) * RES * HP + (int64_t)a0 * TC;  // k2-tiled plane
-  for (int e = t; e < TR * HP; e += BR) {
-    const int kk = e % TC, l = (e / TC) % TR, kt = e / (TC * TR), k = kt * TC + kk;
-    if (k < H) rows[rpos<M>(l, k)] = in[((int64_t)kt * RES + l) * TC + kk];
+  {
+    // two elements (k, k + 1) per 16-byte load, every load in flight before the
+    // first LDS write (read one by one these
+    // loads were two thirds of the pass: 1024^3 2.73 -> 1.58 ms, 5.5 TB/s)
+    constexpr int NV = TR * HP / 2, IT = (NV + BR - 1) / BR;
+    float4 buf[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int e = t + it * BR;
+      const int kk = 2 * (e % (TC / 2)), l = (e / (TC / 2)) % TR, kt = e / (TC / 2 * TR);
+      if (e < NV && kt * TC + kk < H)
+        buf[it] = *reinterpret_cast<const float4*>(in + ((int64_t)kt * RES + l) * TC + kk);
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int e = t + it * BR;
+      const int kk = 2 * (e % (TC / 2)), l = (e / (TC / 2)) % TR, kt = e / (TC / 2 * TR), k = kt * TC + kk;
+      if (e < NV && k < H) {
+        rows[rpos<M>(l, k)] = cf{buf[it].x, buf[it].y};
+        if (k + 1 < H) rows[rpos<M>(l, k + 1)] = cf{buf[it].z, buf[it].w};
+      }
+    }
   }
   __syncthreads();
   // Hermitian half-spectrum X[0..M] -> packed spectrum Z[0..M) of the
@@ -484,13 +560,14 @@ __global__ __launch_bounds__(slab_rows_block(RES)) void k_slab_rows_inv(const Sl
   float* const dst = a.chi + ((int64_t)j0 * RES + a0) * RES;
   float* const hal = j0l == 0 ? a.halo + (int64_t)((g + a.G - 1) & (a.G - 1)) * RES * RES + (int64_t)a0 * RES
                               : nullptr;
-  for (int e = t; e < TR * M; e += BR) {
-    const int l = e / M, mm = e % M;
-    const cf z = rows[rpos<M>(l, mm)];
-    const float2 v = make_float2(z.x, z.y);
-    *reinterpret_cast<float2*>(dst + (int64_t)l * RES + 2 * mm) = v;
-    if (hal) *reinterpret_cast<float2*>(hal + (int64_t)l * RES + 2 * mm) = v;
-    if (j0 == 0 && a0 == 0 && e == 0) a.hdr->chi0 = (double)z.x;
+#pragma unroll 4
+  for (int e = t; e < TR * M / 2; e += BR) {
+    const int l = e / (M / 2), mm = 2 * (e % (M / 2));
+    const cf z0 = rows[rpos<M>(l, mm)], z1 = rows[rpos<M>(l, mm + 1)];
+    const float4 v = make_float4(z0.x, z0.y, z1.x, z1.y);
+    *reinterpret_cast<float4*>(dst + (int64_t)l * RES + 2 * mm) = v;
+    if (hal) *reinterpret_cast<float4*>(hal + (int64_t)l * RES + 2 * mm) = v;
+    if (j0 == 0 && a0 == 0 && e == 0) a.hdr->chi0 = (double)z0.x;
   }
 }
 
@@ -596,14 +673,15 @@ int slab_sequence(Exec& x, const SlabArgs& a) {
     hipLaunchKernelGGL(k_slab_scan_blocks, dim3(nsb), dim3(kScanBlock), 0, st, a, nbins);
     hipLaunchKernelGGL(k_slab_scan_tops, dim3(1), dim3(kScanBlock), 0, st, a, nsb, nbins);
     hipLaunchKernelGGL(k_slab_scan_add, dim3(nsb), dim3(kScanBlock), 0, st, a, nbins);
-    hipLaunchKernelGGL(k_slab_scatter, dim3(pb), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_slab_scatter<RES>, dim3(pb), dim3(256), 0, st, a);
   }
   x.end(STAGE_SLAB_BIN);
 
   x.begin(STAGE_S1);
+  const unsigned rb = (unsigned)imin(3 * s * NT, kRowGrid);
   for (int g = 0; g < G; ++g) {
-    if (load) hipLaunchKernelGGL((k_slab_rows_fwd<RES, true>), dim3(3 * s * NT), dim3(BR), 0, st, a, g);
-    else hipLaunchKernelGGL((k_slab_rows_fwd<RES, false>), dim3(3 * s * NT), dim3(BR), 0, st, a, g);
+    if (load) hipLaunchKernelGGL((k_slab_rows_fwd<RES, true>), dim3(rb), dim3(BR), 0, st, a, g);
+    else hipLaunchKernelGGL((k_slab_rows_fwd<RES, false>), dim3(rb), dim3(BR), 0, st, a, g);
   }
   x.end(STAGE_S1);
 
@@ -611,7 +689,8 @@ int slab_sequence(Exec& x, const SlabArgs& a) {
   for (int g = 0; g < G; ++g) {
     BlockPtrs d{};
     for (int h = 0; h < G; ++h) d.p[h] = a.X + (int64_t)(h * G + g) * blkX;
-    hipLaunchKernelGGL(k_slab_fft_j1<RES>, dim3(2 * s * NKT), dim3(BC), 0, st, a, d, g);
+    if (load) hipLaunchKernelGGL((k_slab_fft_j1<RES, false>), dim3(2 * s * NKT), dim3(BC), 0, st, a, d, g);
+    else hipLaunchKernelGGL((k_slab_fft_j1<RES, true>), dim3(2 * s * NKT), dim3(BC), 0, st, a, d, g);
   }
   x.end(STAGE_S2);
 
