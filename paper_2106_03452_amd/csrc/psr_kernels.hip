@@ -13,7 +13,7 @@
 //   P5       complex-to-real inverse FFT along j2, write chi', and the
 //            trilinear gather of chi' at the points (value + gradient)
 //   reduce   FP64 mean at the points, scale c (main Eq. 4), normalise chi
-// At 64^3 and 128^3 the plane passes P12 (= P1 + P2) and P45 (= P4 + P5) run
+// From 32^3 to 128^3 the plane passes P12 (= P1 + P2) and P45 (= P4 + P5) run
 // two axes per kernel with a whole j0 plane on chip; at 256^3 only P45 does.
 // The backward runs the adjoint of every step (FP64 sums of G and G*chi, the
 // cotangent H, conjugate operator, 3 inverse channels, gather of dL/dv), with
@@ -576,46 +576,52 @@ __device__ __forceinline__ void b_splat_r2c(const PointRec* __restrict__ sorted,
   }
 }
 
-// Load TC lines stored transposed (element n of line l at src[n * stride_n +
-// l], two lines per 16-byte load) into the LDS lines rows[l * LS + pidx(n)].
-// All global loads are issued before the LDS writes; ends with a barrier.
+// TC lines stored transposed (element n of line l at src[n * stride_n + l],
+// two lines per 16-byte load), fetched into registers and then put into the LDS
+// lines rows[l * LS + pidx(n)]; put() ends with a barrier.
 template <int RES, int TC, bool LEAN>
-__device__ __forceinline__ void load_transposed(cf* rows, const cf* __restrict__ src, int64_t stride_n,
-                                                const cf* __restrict__ src2 = nullptr) {
-  constexpr int BC = TC * plan_TPL(RES), LS = lstride(RES);
-  constexpr int NV = RES * (TC / 2), IT = (NV + BC - 1) / BC;
-  const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
+struct Transposed {
+  static constexpr int BC = TC * plan_TPL(RES), LS = lstride(RES);
+  static constexpr int NV = RES * (TC / 2), IT = (NV + BC - 1) / BC;
   float4 buf[IT];
-#pragma unroll
-  for (int it = 0; it < IT; ++it) {
-    const int e = t + it * BC;
-    if (e < NV) {
-      const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
-      buf[it] = *reinterpret_cast<const float4*>(src + n * stride_n + l2);
-    }
-  }
-  if (src2) {  // the sum of two channels (uniform)
+  __device__ __forceinline__ void fetch(const cf* __restrict__ src, int64_t stride_n) {
+    const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const int e = t + it * BC;
       if (e < NV) {
         const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
-        const float4 y = *reinterpret_cast<const float4*>(src2 + n * stride_n + l2);
+        buf[it] = *reinterpret_cast<const float4*>(src + n * stride_n + l2);
+      }
+    }
+  }
+  // plus the same elements of another channel
+  __device__ __forceinline__ void fetch_add(const cf* __restrict__ src, int64_t stride_n) {
+    const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int e = t + it * BC;
+      if (e < NV) {
+        const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
+        const float4 y = *reinterpret_cast<const float4*>(src + n * stride_n + l2);
         buf[it] = make_float4(buf[it].x + y.x, buf[it].y + y.y, buf[it].z + y.z, buf[it].w + y.w);
       }
     }
   }
+  __device__ __forceinline__ void put(cf* rows) const {
+    const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
 #pragma unroll
-  for (int it = 0; it < IT; ++it) {
-    const int e = t + it * BC;
-    if (e < NV) {
-      const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
-      rows[l2 * LS + pidx(n)] = cf{buf[it].x, buf[it].y};
-      rows[(l2 + 1) * LS + pidx(n)] = cf{buf[it].z, buf[it].w};
+    for (int it = 0; it < IT; ++it) {
+      const int e = t + it * BC;
+      if (e < NV) {
+        const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
+        rows[l2 * LS + pidx(n)] = cf{buf[it].x, buf[it].y};
+        rows[(l2 + 1) * LS + pidx(n)] = cf{buf[it].z, buf[it].w};
+      }
     }
+    __syncthreads();
   }
-  __syncthreads();
-}
+};
 
 // Store the canonical registers of TC lines transposed: out[n][a0 + l] for
 // every element n of every line l, two lines per 16-byte store; with masks,
@@ -732,11 +738,22 @@ __device__ __forceinline__ void b_fwd_axis0(const cf* __restrict__ in, cf* __res
   // were not written by P2
   if constexpr (IN_C) {
     const cf* src = in + (int64_t)k2 * RES + a0;  // element j0 of line k1 at src[j0 H RES + l]
-    load_transposed<RES, TC, LEAN>(rows, src, (int64_t)H * RES);
+    Transposed<RES, TC, LEAN> x, w;
+    x.fetch(src, (int64_t)H * RES);
+    // W = kappa_1 v~_1 + kappa_2 v~_2, summed on load; in a single solve, which
+    // leaves registers free, fetched under the first transform
+    if constexpr (!LEAN) {
+      w.fetch(src + CH, (int64_t)H * RES);
+      w.fetch_add(src + 2 * CH, (int64_t)H * RES);
+    }
+    x.put(rows);
     fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
     scale_odd<RES, LEAN>(acc, reg, lt);
-    // W = kappa_1 v~_1 + kappa_2 v~_2, summed on load
-    load_transposed<RES, TC, LEAN>(rows, src + CH, (int64_t)H * RES, src + 2 * CH);
+    if constexpr (LEAN) {
+      w.fetch(src + CH, (int64_t)H * RES);
+      w.fetch_add(src + 2 * CH, (int64_t)H * RES);
+    }
+    w.put(rows);
     fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
   } else {
     const cf* src = in + ((int64_t)k2 * RES + k1) * RES;
@@ -800,7 +817,9 @@ __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __res
   const int k1 = a0 + l;
   cf h[E], reg[E];
   if constexpr (IN_C) {
-    load_transposed<RES, TC, LEAN>(rows, in + (int64_t)k2 * RES + a0, (int64_t)H * RES);
+    Transposed<RES, TC, LEAN> x;
+    x.fetch(in + (int64_t)k2 * RES + a0, (int64_t)H * RES);
+    x.put(rows);
     fft<RES, -1, false, true, false, LEAN>(h, rows + l * LS, lt, stw);
   } else {
     const cf* src = in + ((int64_t)k2 * RES + k1) * RES;
@@ -1058,7 +1077,7 @@ __device__ __forceinline__ void b_c2r_gather(const cf* __restrict__ in,
 }
 
 // ---------------------------------------------------------------------------
-// Plane passes (res 64, 128, 256). One workgroup owns one j0 plane, or one
+// Plane passes (res 32 to 256). One workgroup owns one j0 plane, or one
 // part of it, and runs two transform axes on chip, so the data between the
 // j2 and j1 axes never goes through HBM:
 //   forward (P12, B12): rows of the plane -> r2c along j2 (LDS) -> FFT along
@@ -1069,14 +1088,25 @@ __device__ __forceinline__ void b_c2r_gather(const cf* __restrict__ in,
 // so they travel through the j1 axis as one packed column X_0 + i X_{r/2}:
 // r/2 complex columns per plane. At 256 a plane is split in two parts (k2
 // halves forward, j1 halves inverse); each part redoes the other axis.
+// At 32 and 64 the transforms of a plane need 32 and 128 threads; the workgroup
+// is wider (THREADS), so that its loops over the plane's points and samples
+// have more lanes: the first BLOCK threads transform (wavefront-synchronous,
+// the others wait at the next workgroup barrier). A single solve has fewer
+// workgroups than CUs and takes 512 threads, a batch 256, so that more
+// workgroups fit a CU (64^3, 20k points: P12 18.1 us with 128 threads, 15.2 with
+// 256, 12.4 with 512; in a batch 29.3, 26.6, 35.9).
 // ---------------------------------------------------------------------------
-template <int RES>
+__host__ __device__ constexpr int plane_threads(int maxj) { return maxj == 1 ? 512 : 256; }
+
+template <int RES, int TMIN = 256>
 struct Plane {
   static constexpr int M = RES / 2, H = M + 1;
   static constexpr int KP = RES >= PSR_PLANE_SPLIT_MIN ? 2 : 1;  // parts per plane
   static constexpr int NCOL = M / KP;            // packed columns per part (forward) / per round (inverse)
   static constexpr int TPL = plan_TPL(RES);      // threads per j1 line
-  static constexpr int BLOCK = NCOL * TPL;
+  static constexpr int BLOCK = NCOL * TPL;       // threads of the transforms
+  static constexpr int THREADS = BLOCK < TMIN ? TMIN : BLOCK;
+  static constexpr bool WIDE = THREADS > BLOCK;
   static constexpr int TPR = plan_TPL(M);        // threads per half-length row
   static constexpr int RC = BLOCK / TPR;         // rows per chunk (forward) = rows per part (inverse)
   static constexpr int NCHUNK = RES / RC;
@@ -1090,11 +1120,16 @@ struct Plane {
   static_assert(NCHUNK * RC == RES && RES / KP == RC, "chunks and parts tile the plane");
 };
 
+template <int RES, int MAXJ>
+constexpr int plane_wg() {
+  return Plane<RES, plane_threads(MAXJ)>::THREADS;
+}
+
 // Where the plane passes pay: at 256 a plane needs all of LDS, one workgroup
 // per CU, and each part redoes the other axis; only the inverse forward pass
 // (one channel, no point-free skip lost) still gains there.
-__host__ __device__ constexpr bool use_plane(int res) { return res >= 64 && res <= 128; }
-__host__ __device__ constexpr bool use_plane_p45(int res) { return res >= 64 && res <= 256; }
+__host__ __device__ constexpr bool use_plane(int res) { return res >= 32 && res <= 128; }
+__host__ __device__ constexpr bool use_plane_p45(int res) { return res >= 32 && res <= 256; }
 
 // Workgroup -> (plane j0, sub-index u < U). The U workgroups of one plane
 // get ids equal mod 8, so they are dispatched to the same XCD, close in
@@ -1114,22 +1149,23 @@ enum { PF_SPLAT = 0, PF_BWDH = 1, PF_LOADV = 2 };
 // cotangent H = s G + alpha W; PF_LOADV: v_ch rows from memory.
 // Returns false, uniformly and before any barrier, when a splat span holds
 // no point (its rows and spectra are zero and LDS is left untouched).
-template <int RES, int MODE>
+template <int RES, int MODE, int TMIN>
 __device__ __forceinline__ bool pf_rows(cf* rows, const cf* stw, const PointRec* __restrict__ sorted,
                                         const int* __restrict__ off, const float* __restrict__ gin,
                                         float3 sqa, int j0, int a0, int ch) {
-  using PL = Plane<RES>;
-  constexpr int M = PL::M, RC = PL::RC, LSR = PL::LSR, BLOCK = PL::BLOCK;
+  using PL = Plane<RES, TMIN>;
+  constexpr int M = PL::M, RC = PL::RC, LSR = PL::LSR;
   const int t = threadIdx.x;
   Ranges R{};
   if constexpr (MODE != PF_LOADV) R = span_ranges<RES, RC>(off, j0, a0);
   if (MODE == PF_SPLAT && R.total == 0) return false;
-  fill_rows<RES, RC, BLOCK, MODE>(rows, sorted, R, gin, sqa, j0, a0, ch);
-  {
+  fill_rows<RES, RC, PL::THREADS, MODE>(rows, sorted, R, gin, sqa, j0, a0, ch);
+  if (!PL::WIDE || t < PL::BLOCK) {
     cf reg[16];
-    fft<M, -1, false, false, false, PL::LEAN>(reg, rows + (t / PL::TPR) * LSR, t % PL::TPR, stw,
-                                              row_swz(M, t / PL::TPR));
+    fft<M, -1, false, false, PL::WIDE, PL::LEAN>(reg, rows + (t / PL::TPR) * LSR, t % PL::TPR, stw,
+                                                 row_swz(M, t / PL::TPR));
   }
+  if constexpr (PL::WIDE) __syncthreads();
   return true;
 }
 
@@ -1155,14 +1191,14 @@ __device__ __forceinline__ cf pf_pick(const cf* rows, const cf* wr, int l, int k
 // W (the whole grid runs in one wave at 64^3 and 128^3, so equal workgroups
 // beat one doing both W channels). B12 (PF_BWDH): H^ along (j2, j1). Output
 // C[set][j0][k2][k1].
-template <int RES, int MODE>
+template <int RES, int MODE, int TMIN>
 __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted, const int* __restrict__ off,
                                             const float* __restrict__ gin, BwdScalars* __restrict__ bs,
                                             const double2* __restrict__ bpart, const SavedHeader* __restrict__ hdr,
                                             const cf* __restrict__ tw, cf* __restrict__ out, int bid) {
-  using PL = Plane<RES>;
+  using PL = Plane<RES, TMIN>;
   constexpr int M = PL::M, H = PL::H, KP = PL::KP, NCOL = PL::NCOL, TPL = PL::TPL, RC = PL::RC;
-  constexpr int NCHUNK = PL::NCHUNK, LSC = PL::LSC, BLOCK = PL::BLOCK;
+  constexpr int NCHUNK = PL::NCHUNK, LSC = PL::LSC, BLOCK = PL::THREADS;
   constexpr int NSET = MODE == PF_BWDH ? 1 : 3;
   constexpr int VPC = 16 / NCHUNK;  // register elements filled per chunk
   constexpr int64_t CH = (int64_t)H * RES * RES;
@@ -1175,6 +1211,7 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
   plane_of<KP * NSET>(bid, j0, u);
   const int part = u % KP, set = u / KP;
   const int t = threadIdx.x, col = t / TPL, lt = t % TPL;
+  const bool fft_thread = !PL::WIDE || t < PL::BLOCK;
   const int kk = part * NCOL + col;  // packed column index; 0 = (k2 = 0, k2 = M)
   cf* const o = out + set * CH + (int64_t)j0 * H * RES;
   if constexpr (MODE == PF_SPLAT) {
@@ -1197,10 +1234,10 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
 #pragma unroll 1
     for (int q = 0; q < NCHUNK; ++q) {
       const int a0 = q * RC;
-      const bool any = pf_rows<RES, MODE>(buf, stw, sorted, off, gin, sqa, j0, a0, ch);
+      const bool any = pf_rows<RES, MODE, TMIN>(buf, stw, sorted, off, gin, sqa, j0, a0, ch);
 #pragma unroll
       for (int w2 = 0; w2 < VPC; ++w2) {
-        const cf x = any ? pf_pick<RES>(buf, ctw, lt + TPL * w2, kk) : cf{0.0f, 0.0f};
+        const cf x = any && fft_thread ? pf_pick<RES>(buf, ctw, lt + TPL * w2, kk) : cf{0.0f, 0.0f};
         // static register indices: chunk q fills reg[q VPC + w2]
 #pragma unroll
         for (int qq = 0; qq < NCHUNK; ++qq)
@@ -1208,7 +1245,7 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
       }
       __syncthreads();  // the rows are overwritten next
     }
-    fft<RES, -1, true, true, false, PL::LEAN>(reg, buf + col * LSC, lt, ctw);
+    if (fft_thread) fft<RES, -1, true, true, PL::WIDE, PL::LEAN>(reg, buf + col * LSC, lt, ctw);
   }
   if (set == 1 && kk != 0) {
     scale_odd<RES>(reg, reg, lt);
@@ -1227,6 +1264,7 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
     for (int v = 0; v < 16; ++v) line[pidx(lt + TPL * v)] = reg[v];
   }
   __syncthreads();
+  if (!fft_thread) return;
   if (kk == 0) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -1251,11 +1289,11 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
 // Splat test hook of the plane passes: the rows that P12 splats for plane
 // j0 and channel c (the same fill_rows instantiation and spans), written to
 // v_c[j0] instead of being transformed.
-template <int RES>
+template <int RES, int TMIN>
 __device__ __forceinline__ void b_plane_splat_dbg(const PointRec* __restrict__ sorted, const int* __restrict__ off,
                                                   float* __restrict__ vout, int bid) {
-  using PL = Plane<RES>;
-  constexpr int M = PL::M, RC = PL::RC, BLOCK = PL::BLOCK;
+  using PL = Plane<RES, TMIN>;
+  constexpr int M = PL::M, RC = PL::RC, BLOCK = PL::THREADS;
   constexpr int64_t N3 = (int64_t)RES * RES * RES;
   __shared__ __align__(16) cf buf[PL::SLOTS];
   const int j0 = bid / 3, c = bid % 3, t = threadIdx.x;
@@ -1282,19 +1320,19 @@ enum { PI_FWD = 0, PI_BWD = 1, PI_DBG = 2 };
 // chi' rows only. B45 (PI_BWD, grid x3): g_v channel c = IFFT of V0, of
 // kappa_1 U and of kappa_2 U, gather partials only; a part no point touches
 // is skipped. Input C[c][j0][k2][k1]; part p owns rows j1 in [p RC, p RC + RC).
-template <int RES, int MODE>
+template <int RES, int MODE, int TMIN>
 __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __restrict__ chi_out,
                                             SavedHeader* __restrict__ hdr,
                                             const PointRec* __restrict__ sorted, const int* __restrict__ off,
                                             float4* __restrict__ part, int64_t np, const cf* __restrict__ tw,
                                             int bid) {
-  using PL = Plane<RES>;
+  using PL = Plane<RES, TMIN>;
   constexpr int M = PL::M, H = PL::H, KP = PL::KP, NCOL = PL::NCOL, TPL = PL::TPL, RC = PL::RC;
-  constexpr int LSR = PL::LSR, LSC = PL::LSC, BLOCK = PL::BLOCK, TPR = PL::TPR;
+  constexpr int LSR = PL::LSR, LSC = PL::LSC, BLOCK = PL::THREADS, TPR = PL::TPR;
   constexpr int NCH = MODE == PI_BWD ? 3 : 1;
   constexpr int VK = 16 / KP;  // elements kept per round: the part's rows of the column
   constexpr int64_t CH = (int64_t)H * RES * RES;
-  constexpr bool WS = RES >= 256;  // wavefront-synchronous transforms
+  constexpr bool WS = RES >= 256 || PL::WIDE;  // wavefront-synchronous transforms
   __shared__ __align__(16) cf buf[PL::SLOTS];
   __shared__ cf stw[M];
   __shared__ cf ctw[RES];
@@ -1306,6 +1344,7 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
   const int p = u % KP, c = u / KP;
   const int a0 = p * RC;
   const int t = threadIdx.x, col = t / TPL, lt = t % TPL;
+  const bool fft_thread = !PL::WIDE || t < PL::BLOCK;
   Ranges R{};
   if constexpr (MODE != PI_DBG) R = span_ranges<RES, RC>(off, j0, a0);
   const int total = R.total;
@@ -1316,7 +1355,10 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
   for (int rd = 0; rd < KP; ++rd) {
     const int kk = rd * NCOL + col;
     cf reg[16];
-    if (kk == 0) {
+    if (!fft_thread) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) reg[v] = cf{0.0f, 0.0f};
+    } else if (kk == 0) {
       // pack the real-signal columns k2 = 0 and M: Z = A_0 + i A_M
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -1339,7 +1381,7 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
     // flight (P45 48.4 -> 47.4 us; at 64 and 128 the workgroup barriers cost
     // less than the extra ones here)
     if (WS && rd == 0) __syncthreads();
-    fft<RES, +1, true, true, WS, PL::LEAN>(reg, buf + col * LSC, lt, ctw);
+    if (fft_thread) fft<RES, +1, true, true, WS, PL::LEAN>(reg, buf + col * LSC, lt, ctw);
 #pragma unroll
     for (int w2 = 0; w2 < VK; ++w2) {
       cf x = reg[w2];
@@ -1360,6 +1402,7 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
 #pragma unroll
     for (int w2 = 0; w2 < VK; ++w2) {
       const int l = lt + TPL * w2;
+      if (!fft_thread) break;
       if (kk == 0) {
         buf[rpos<M>(l, 0)] = cf{keep[rd][w2].x, 0.0f};
         buf[rpos<M>(l, M)] = cf{keep[rd][w2].y, 0.0f};
@@ -1405,7 +1448,7 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
     }
   }
   __syncthreads();
-  {
+  if (fft_thread) {
     cf reg[16];
     fft<M, +1, false, false, WS, PL::LEAN>(reg, buf + (t / TPR) * LSR, t % TPR, stw, row_swz(M, t / TPR));
   }
@@ -1849,28 +1892,31 @@ __global__ __launch_bounds__(rows_wg(RES)) void k_c2r_gather(const Batch<MAXJ> B
 }
 
 template <int RES, int MODE, int MAXJ>
-__global__ __launch_bounds__(Plane<RES>::BLOCK) __attribute__((amdgpu_waves_per_eu(Plane<RES>::WPE)))
+__global__ __launch_bounds__((plane_wg<RES, MAXJ>()))
+__attribute__((amdgpu_waves_per_eu(Plane<RES>::WPE)))
 void k_plane_fwd(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   if constexpr (MODE == PF_BWDH) { PSR_BWD_GUARD(RES); }
   const float* gin = MODE == PF_BWDH ? J.dchi : J.aux_in;
-  b_plane_fwd<RES, MODE>(sv.sorted, sv.off, gin, w.bs, (const double2*)w.blockpart, sv.hdr, B.tw, w.Y, bid);
+  b_plane_fwd<RES, MODE, plane_threads(MAXJ)>(sv.sorted, sv.off, gin, w.bs, (const double2*)w.blockpart, sv.hdr, B.tw, w.Y, bid);
 }
 
 template <int RES, int MODE, int MAXJ>
-__global__ __launch_bounds__(Plane<RES>::BLOCK) __attribute__((amdgpu_waves_per_eu(Plane<RES>::WPE)))
+__global__ __launch_bounds__((plane_wg<RES, MAXJ>()))
+__attribute__((amdgpu_waves_per_eu(Plane<RES>::WPE)))
 void k_plane_inv(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   if constexpr (MODE == PI_BWD) { PSR_BWD_GUARD(RES); }
   float* outp = MODE == PI_DBG ? J.aux_out : J.chi;
-  b_plane_inv<RES, MODE>(w.X, outp, sv.hdr, sv.sorted, sv.off, w.part, J.P, B.tw, bid);
+  b_plane_inv<RES, MODE, plane_threads(MAXJ)>(w.X, outp, sv.hdr, sv.sorted, sv.off, w.part, J.P, B.tw, bid);
 }
 
 template <int RES, int MAXJ>
-__global__ __launch_bounds__(Plane<RES>::BLOCK) __attribute__((amdgpu_waves_per_eu(Plane<RES>::WPE)))
+__global__ __launch_bounds__((plane_wg<RES, MAXJ>()))
+__attribute__((amdgpu_waves_per_eu(Plane<RES>::WPE)))
 void k_plane_splat_dbg(const Batch<MAXJ> B) {
   PSR_JOB(RES);
-  b_plane_splat_dbg<RES>(sv.sorted, sv.off, J.aux_out, bid);
+  b_plane_splat_dbg<RES, plane_threads(MAXJ)>(sv.sorted, sv.off, J.aux_out, bid);
 }
 
 template <int RES, int MAXJ>
@@ -1983,7 +2029,7 @@ static int seq_forward(Exec& x, const JobArg* J, int n) {
   x.end(STAGE_BIN);
   if constexpr (use_plane(RES)) {
     x.begin(STAGE_P12);
-    rc |= launch<MAXJ>(x, k_plane_fwd<RES, PF_SPLAT, MAXJ>, Plane<RES>::BLOCK, J, n, c(RES * Plane<RES>::KP * 3));
+    rc |= launch<MAXJ>(x, k_plane_fwd<RES, PF_SPLAT, MAXJ>, (plane_wg<RES, MAXJ>()), J, n, c(RES * Plane<RES>::KP * 3));
     x.end(STAGE_P12);
   } else {
     x.begin(STAGE_P1);
@@ -1998,7 +2044,7 @@ static int seq_forward(Exec& x, const JobArg* J, int n) {
   x.end(STAGE_P3);
   if constexpr (use_plane_p45(RES)) {
     x.begin(STAGE_P45);
-    rc |= launch<MAXJ>(x, k_plane_inv<RES, PI_FWD, MAXJ>, Plane<RES>::BLOCK, J, n, c(RES * Plane<RES>::KP));
+    rc |= launch<MAXJ>(x, k_plane_inv<RES, PI_FWD, MAXJ>, (plane_wg<RES, MAXJ>()), J, n, c(RES * Plane<RES>::KP));
     x.end(STAGE_P45);
   } else {
     x.begin(STAGE_P4);
@@ -2028,7 +2074,7 @@ static int seq_backward(Exec& x, const JobArg* J, int n) {
     rc |= launch<MAXJ>(x, k_bwd_reduce<RES, MAXJ>, 256, J, n, c(bwd_reduce_blocks<RES>()));
     x.end(STAGE_BWD_REDUCE);
     x.begin(STAGE_B12);
-    rc |= launch<MAXJ>(x, k_plane_fwd<RES, PF_BWDH, MAXJ>, Plane<RES>::BLOCK, J, n, c(RES * Plane<RES>::KP));
+    rc |= launch<MAXJ>(x, k_plane_fwd<RES, PF_BWDH, MAXJ>, (plane_wg<RES, MAXJ>()), J, n, c(RES * Plane<RES>::KP));
     x.end(STAGE_B12);
   } else {
     // the reductions ride on the first row pass, which also transforms the
@@ -2048,7 +2094,7 @@ static int seq_backward(Exec& x, const JobArg* J, int n) {
   x.end(STAGE_B3);
   if constexpr (use_plane(RES)) {
     x.begin(STAGE_B45);
-    rc |= launch<MAXJ>(x, k_plane_inv<RES, PI_BWD, MAXJ>, Plane<RES>::BLOCK, J, n, c(RES * Plane<RES>::KP * 3));
+    rc |= launch<MAXJ>(x, k_plane_inv<RES, PI_BWD, MAXJ>, (plane_wg<RES, MAXJ>()), J, n, c(RES * Plane<RES>::KP * 3));
     x.end(STAGE_B45);
   } else {
     x.begin(STAGE_B4);
@@ -2083,14 +2129,14 @@ static int debug_spectral_res(Exec& x, const JobArg& job) {
   auto c = [](int v) { return [v](const JobArg&) { return v; }; };
   int rc = 0;
   if constexpr (use_plane(RES)) {
-    rc |= launch<1>(x, k_plane_fwd<RES, PF_LOADV, 1>, Plane<RES>::BLOCK, &job, 1, c(RES * Plane<RES>::KP * 3));
+    rc |= launch<1>(x, k_plane_fwd<RES, PF_LOADV, 1>, (plane_wg<RES, 1>()), &job, 1, c(RES * Plane<RES>::KP * 3));
   } else {
     rc |= launch<1>(x, k_splat_r2c<RES, MODE_LOADV, 1>, G::BR, &job, 1, c(3 * G::rows));
     rc |= launch<1>(x, k_axis1_fwd<RES, true, false, 1>, G::BC, &job, 1, c(2 * G::cols));
   }
   rc |= launch<1>(x, k_fwd_axis0<RES, false, 1>, G::BJ, &job, 1, c(G::j0s));
   if constexpr (use_plane_p45(RES)) {
-    rc |= launch<1>(x, k_plane_inv<RES, PI_DBG, 1>, Plane<RES>::BLOCK, &job, 1, c(RES * Plane<RES>::KP));
+    rc |= launch<1>(x, k_plane_inv<RES, PI_DBG, 1>, (plane_wg<RES, 1>()), &job, 1, c(RES * Plane<RES>::KP));
   } else {
     rc |= launch<1>(x, k_axis1_inv<RES, false, 1>, G::BC, &job, 1, c(G::cols));
     rc |= launch<1>(x, k_c2r_gather<RES, MODE_DBG, 1>, G::BR, &job, 1, c(G::rows));
@@ -2113,7 +2159,7 @@ static int debug_splat_res(Exec& x, const JobArg& job) {
   }
   // the splat of the production path: plane passes at 64 and 128, row passes elsewhere
   if constexpr (use_plane(RES))
-    rc |= launch<1>(x, k_plane_splat_dbg<RES, 1>, Plane<RES>::BLOCK, &job, 1, c(3 * RES));
+    rc |= launch<1>(x, k_plane_splat_dbg<RES, 1>, (plane_wg<RES, 1>()), &job, 1, c(3 * RES));
   else
     rc |= launch<1>(x, k_splat_r2c<RES, MODE_VOUT, 1>, G::BR, &job, 1, c(3 * G::rows));
   return rc ? -4 : 0;
