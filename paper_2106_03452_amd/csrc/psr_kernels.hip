@@ -108,18 +108,6 @@ __device__ __forceinline__ Ranges tile_ranges(const int* __restrict__ off, int j
 }
 
 
-// Whether any point's corners reach plane j0 (floor planes j0 - 1 and j0).
-// A plane no point reaches has zero splat rows, and nothing is gathered from
-// it: passes skip reading or writing what only such planes would use.
-template <int RES>
-__device__ __forceinline__ bool plane_live(const int* __restrict__ off, int j0) {
-  constexpr int NB = 2 * row_tiles(RES);  // bins per floor plane
-  const int r0 = ((j0 - 1) & (RES - 1)) * NB, r1 = j0 * NB;
-  return (off[r0 + NB] - off[r0]) + (off[r1 + NB] - off[r1]) > 0;
-}
-
-
-
 // ---------------------------------------------------------------------------
 // binning: counting sort of the points by row tile (b0, b1 / tile_rows)
 // ---------------------------------------------------------------------------
@@ -551,28 +539,46 @@ __device__ __forceinline__ void b_splat_r2c(const PointRec* __restrict__ sorted,
       const int l = t / TPL;
       fft<M, -1, false, false>(reg, rows + l * LS, t % TPL, stw, row_swz(M, l));
     }
-    // X[k] = E_k + W_r^k O_k with E = (Z_k + Z*_{M-k})/2, O = (Z_k - Z*_{M-k})/(2i)
-    for (int e = t; e < H * (TR / 2); e += BR) {
-      const int l = 2 * (e % (TR / 2)), k = e / (TR / 2);
+    // X[k] = E_k + W_r^k O_k with E = (Z_k + Z*_{M-k})/2, O = (Z_k - Z*_{M-k})/(2i),
+    // and X[M - k] = conj(E_k - W_r^k O_k): a thread forms both for two rows
+    // from four LDS reads. k in [0, M/2) divides evenly among the threads, so the
+    // loop unrolls; k = M/2, its own partner, follows for every row pair. (One k
+    // per turn in nine turns of H (TR / 2) / BR, the last nearly empty: a third
+    // of P1's time at 256^3, 47.7 us.)
+    constexpr int NP = (M / 2) * (TR / 2);
+    auto pair = [&](int l, int k, bool both) {
       const cf w = rtw[k];
-      float4 o;
+      float4 lo, hi;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const cf zk = rows[rpos<M>(l + h, k == M ? 0 : k)];
+        const cf zk = rows[rpos<M>(l + h, k)];
         const cf zm = rows[rpos<M>(l + h, k == 0 ? 0 : M - k)];
         const cf Ee{0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y)};
         const cf Oo{0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x)};
-        const cf X = cadd(Ee, cmul(w, Oo));
+        const cf wo = cmul(w, Oo);
+        const cf X = cadd(Ee, wo), Y = csub(Ee, wo);
         if (h == 0) {
-          o.x = X.x;
-          o.y = X.y;
+          lo.x = X.x;
+          lo.y = X.y;
+          hi.x = Y.x;
+          hi.y = -Y.y;
         } else {
-          o.z = X.x;
-          o.w = X.y;
+          lo.z = X.x;
+          lo.w = X.y;
+          hi.z = Y.x;
+          hi.w = -Y.y;
         }
       }
-      *reinterpret_cast<float4*>(out + (((int64_t)c * H + k) * RES + j0) * RES + a0 + l) = o;
+      cf* const o = out + ((int64_t)c * H * RES + j0) * RES + a0 + l;
+      *reinterpret_cast<float4*>(o + (int64_t)k * RES * RES) = lo;
+      if (both) *reinterpret_cast<float4*>(o + (int64_t)(M - k) * RES * RES) = hi;
+    };
+#pragma unroll
+    for (int it = 0; it < (NP + BR - 1) / BR; ++it) {
+      const int e = t + it * BR;
+      if (NP % BR == 0 || e < NP) pair(2 * (e % (TR / 2)), e / (TR / 2), true);
     }
+    if (t < TR / 2) pair(2 * t, M / 2, false);
   }
 }
 
@@ -625,11 +631,11 @@ struct Transposed {
 
 // Store the canonical registers of TC lines transposed: out[n][a0 + l] for
 // every element n of every line l, two lines per 16-byte store; with masks,
-// only the elements n with keep[n] != 0 and the line pairs with a line whose
+// only the elements n whose bit of keep is set and the line pairs with a line whose
 // keep_line is set.
 template <int RES, int TC, bool LEAN>
 __device__ __forceinline__ void store_transposed(cf* rows, const cf* reg, cf* __restrict__ dst, int64_t stride_n,
-                                                 int l, int lt, const uint8_t* keep = nullptr,
+                                                 int l, int lt, const uint32_t* keep = nullptr,
                                                  const int* keep_line = nullptr) {
   constexpr int BC = TC * plan_TPL(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
   if constexpr (LEAN) lt = opaque_v(lt);
@@ -638,7 +644,7 @@ __device__ __forceinline__ void store_transposed(cf* rows, const cf* reg, cf* __
   __syncthreads();
   for (int e = LEAN ? opaque_v(threadIdx.x) : threadIdx.x; e < RES * (TC / 2); e += BC) {
     const int l2 = 2 * (e % (TC / 2)), n = e / (TC / 2);
-    if (keep && !keep[n]) continue;
+    if (keep && !live_bit(keep, n)) continue;
     if (keep_line && !keep_line[l2] && !keep_line[l2 + 1]) continue;
     const cf x0 = rows[l2 * LS + pidx(n)], x1 = rows[(l2 + 1) * LS + pidx(n)];
     *reinterpret_cast<float4*>(dst + n * stride_n + l2) = make_float4(x0.x, x0.y, x1.x, x1.y);
@@ -800,16 +806,16 @@ __device__ __forceinline__ void b_fwd_axis0(const cf* __restrict__ in, cf* __res
 // IN_C) -> C[2][j0][k2][k1].
 template <int RES, bool IN_C, bool LEAN>
 __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __restrict__ out,
-                                            const cf* __restrict__ tw, float sigma, const int* __restrict__ off,
-                                            int bid) {
+                                            const cf* __restrict__ tw, float sigma,
+                                            const uint32_t* __restrict__ livebits, int bid) {
   constexpr int H = RES / 2 + 1, TC = tile_j0(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
   __shared__ float g1[RES / 2 + 1];
-  __shared__ uint8_t live[RES];  // planes some point reaches: the only ones the next passes read
+  __shared__ uint32_t live[(RES + 31) / 32];  // planes some point reaches: the only ones the next passes read
   stage_table<j0_block(RES)>(stw, tw + RES, RES);
   gauss_table<RES, j0_block(RES)>(g1, sigma);
-  for (int e = threadIdx.x; e < RES; e += j0_block(RES)) live[e] = plane_live<RES>(off, e);
+  if (threadIdx.x < (RES + 31) / 32) live[threadIdx.x] = livebits[threadIdx.x];
   const int tb = bid % (RES / TC);
   const int k2 = bid / (RES / TC);
   const int a0 = tb * TC;
@@ -855,13 +861,12 @@ __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __res
 // ---------------------------------------------------------------------------
 template <int RES, bool SPLIT>
 __device__ __forceinline__ void b_axis1_inv(const cf* __restrict__ in, cf* __restrict__ out,
-                                            const cf* __restrict__ tw, const int* __restrict__ off, int bid) {
+                                            const cf* __restrict__ tw, const uint32_t* __restrict__ tlive, int bid) {
   constexpr int H = RES / 2 + 1, TC = tile_cols(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
-  constexpr int NT = row_tiles(RES), TR = tile_rows(RES);
+  constexpr int TR = tile_rows(RES);
   constexpr int64_t CH = (int64_t)H * RES * RES;
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
-  __shared__ int tile_live[SPLIT ? TC * NT : 1];
   stage_table<cols_block(RES)>(stw, tw + RES, RES);
   int b = bid;
   const int tb = b % (RES / TC);
@@ -885,13 +890,10 @@ __device__ __forceinline__ void b_axis1_inv(const cf* __restrict__ in, cf* __res
   } else {
     // backward: B5 reads only row tiles some point touches. Lines of planes
     // no point reaches are neither read nor written; elsewhere only the
-    // segments of touched tiles are written (the FFT's barriers publish the
-    // flags before the stores read them).
-    if (threadIdx.x < TC * NT) {
-      const int li = threadIdx.x / NT, ti = threadIdx.x % NT;
-      tile_live[threadIdx.x] = tile_ranges<RES>(off, tb * TC + li, ti).total > 0;
-    }
-    const bool live = plane_live<RES>(off, j0);
+    // segments of touched tiles are written.
+    const uint32_t tiles = plane_tiles<RES>(tlive, j0);
+    const bool live = tiles != 0;
+    auto seg = [&](int j1) { return (tiles >> (j1 / TR)) & 1u; };
     if (c == 0) {
 #pragma unroll
       for (int v = 0; v < E; ++v) reg[v] = live ? src[lt + TPL * v] : cf{0.0f, 0.0f};
@@ -899,7 +901,7 @@ __device__ __forceinline__ void b_axis1_inv(const cf* __restrict__ in, cf* __res
 #pragma unroll
       for (int v = 0; v < E; ++v) {
         const int j1 = lt + TPL * v;
-        if (live && tile_live[l * NT + j1 / TR]) dst[j1] = reg[v];
+        if (seg(j1)) dst[j1] = reg[v];
       }
     } else {
       cf u[E];
@@ -910,13 +912,13 @@ __device__ __forceinline__ void b_axis1_inv(const cf* __restrict__ in, cf* __res
 #pragma unroll
       for (int v = 0; v < E; ++v) {
         const int j1 = lt + TPL * v;
-        if (live && tile_live[l * NT + j1 / TR]) dst[j1] = reg[v];
+        if (seg(j1)) dst[j1] = reg[v];
       }
       fft<RES, +1, true, true, false, LEAN>(u, rows + l * LS, lt, stw);
 #pragma unroll
       for (int v = 0; v < E; ++v) {
         const int j1 = lt + TPL * v;
-        if (live && tile_live[l * NT + j1 / TR]) dst[CH + j1] = u[v];
+        if (seg(j1)) dst[CH + j1] = u[v];
       }
     }
   }
@@ -1842,8 +1844,11 @@ __global__ __launch_bounds__(256) void k_scan_scatter(const Batch<MAXJ> B) {
   b_scatter(w.tmp, w.colrank, soff, sv.sorted, J.P, bid);
 }
 
+// the row passes at 256 and 512: two 512-thread workgroups per CU (LDS allows
+// them) need at most 128 VGPRs (B1 alone took 138, and ran one per CU)
 template <int RES, int MODE, int MAXJ>
-__global__ __launch_bounds__(rows_wg(RES)) void k_splat_r2c(const Batch<MAXJ> B) {
+__global__ __launch_bounds__(rows_wg(RES)) __attribute__((amdgpu_waves_per_eu(RES >= 256 ? 4 : 1)))
+void k_splat_r2c(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   if constexpr (MODE == MODE_BWDH || MODE == MODE_BWDA) { PSR_BWD_GUARD(RES); }
   const float* gin = MODE == MODE_BWDH || MODE == MODE_BWDA ? J.dchi : J.aux_in;
@@ -1873,14 +1878,14 @@ template <int RES, int MAXJ>
 __global__ __launch_bounds__(j0_block(RES)) void k_bwd_axis0(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   PSR_BWD_GUARD(RES);
-  b_bwd_axis0<RES, use_plane(RES), j0_lean(RES, MAXJ)>(w.Y, w.X, B.tw, J.sigma, sv.off, bid);
+  b_bwd_axis0<RES, use_plane(RES), j0_lean(RES, MAXJ)>(w.Y, w.X, B.tw, J.sigma, sv.hdr->live, bid);
 }
 
 template <int RES, bool SPLIT, int MAXJ>
 __global__ __launch_bounds__(cols_block(RES)) void k_axis1_inv(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   if constexpr (SPLIT) { PSR_BWD_GUARD(RES); }
-  b_axis1_inv<RES, SPLIT>(w.X, w.Y, B.tw, sv.off, bid);
+  b_axis1_inv<RES, SPLIT>(w.X, w.Y, B.tw, sv.hdr->tlive, bid);
 }
 
 template <int RES, int MODE, int MAXJ>
