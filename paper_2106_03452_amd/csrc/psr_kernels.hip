@@ -2,7 +2,8 @@
 //
 // Pipeline of one forward solve (main Sec. 3.1, Eqs. 2-4; supplement Sec. A):
 //   bin      points -> row-tile buckets (count, scan, scatter; below 512^3
-//            every scatter workgroup scans the bin counts in LDS)
+//            every scatter workgroup scans the bin counts in LDS, and up to
+//            128^3 small clouds take two launches)
 //   P1       splat normals into LDS rows + real-to-complex FFT along j2
 //            (supplement A.1 rasterisation fused with the first FFT axis)
 //   P2       FFT along j1 (3 channels in; out v~_0 and the merged channel
@@ -131,6 +132,50 @@ __device__ __forceinline__ void b_init(int* __restrict__ counts, int n, SavedHea
 // even when a surface crowds the points into a few bins.
 constexpr int kBinChunk = 1024;
 
+// The record of point i (the coordinates wrapped into the periodic domain) and
+// its bin; bad: a coordinate or normal component is not finite (the fixed-point
+// splat needs finite values), and the record is that of a zero normal at 0.
+template <int RES>
+__device__ __forceinline__ PointRec point_rec(const float* __restrict__ pts, const float* __restrict__ nrm, int64_t i,
+                                              int& bin, bool& bad) {
+  float f[3], n[3];
+  int b[3];
+  bad = false;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    float x = pts[3 * i + a];
+    n[a] = nrm[3 * i + a];
+    if (!isfinite(x)) {
+      bad = true;
+      x = 0.0f;
+    }
+    if (!isfinite(n[a])) bad = true;
+    float uu = x - floorf(x);  // wrap into [0,1): periodic domain
+    if (uu >= 1.0f) uu = 0.0f;
+    const float tt = uu * (float)RES;  // exact: RES is a power of two
+    int bi = (int)floorf(tt);
+    bi = bi < 0 ? 0 : (bi > RES - 1 ? RES - 1 : bi);
+    b[a] = bi;
+    f[a] = tt - (float)bi;
+  }
+  if (bad) {
+    f[0] = f[1] = f[2] = 0.0f;
+    n[0] = n[1] = n[2] = 0.0f;
+  }
+  bin = b[0] * 2 * row_tiles(RES) + 2 * (b[1] / tile_rows(RES)) +
+        (b[1] % tile_rows(RES) == tile_rows(RES) - 1 ? 1 : 0);
+  PointRec r;
+  r.f0 = f[0];
+  r.f1 = f[1];
+  r.f2 = f[2];
+  r.b = (uint32_t)b[0] | ((uint32_t)b[1] << 10) | ((uint32_t)b[2] << 20);
+  r.n0 = n[0];
+  r.n1 = n[1];
+  r.n2 = n[2];
+  r.idx = (uint32_t)i;
+  return r;
+}
+
 template <int RES>
 __device__ __forceinline__ void b_bin(const float* __restrict__ pts, const float* __restrict__ nrm,
                                       int64_t npoints, int* __restrict__ counts, PointRec* __restrict__ tmp, int2* __restrict__ colrank,
@@ -148,45 +193,10 @@ __device__ __forceinline__ void b_bin(const float* __restrict__ pts, const float
     const int64_t i = (int64_t)bid * kBinChunk + u * 256 + t;
     mybin[u] = -1;
     if (i >= npoints) continue;
-    float f[3], n[3];
-    int b[3];
-    bool bad = false;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      float x = pts[3 * i + a];
-      n[a] = nrm[3 * i + a];
-      if (!isfinite(x)) {
-        bad = true;
-        x = 0.0f;
-      }
-      if (!isfinite(n[a])) bad = true;  // the fixed-point splat needs finite values
-      float uu = x - floorf(x);  // wrap into [0,1): periodic domain
-      if (uu >= 1.0f) uu = 0.0f;
-      const float tt = uu * (float)RES;  // exact: RES is a power of two
-      int bi = (int)floorf(tt);
-      bi = bi < 0 ? 0 : (bi > RES - 1 ? RES - 1 : bi);
-      b[a] = bi;
-      f[a] = tt - (float)bi;
-    }
-    if (bad) {
-      f[0] = f[1] = f[2] = 0.0f;
-      n[0] = n[1] = n[2] = 0.0f;
-      anybad = true;
-    }
-    const int bin = b[0] * 2 * row_tiles(RES) + 2 * (b[1] / tile_rows(RES)) +
-                    (b[1] % tile_rows(RES) == tile_rows(RES) - 1 ? 1 : 0);
-    mybin[u] = bin;
-    myrank[u] = atomicAdd(&hist[bin], 1);
-    PointRec r;
-    r.f0 = f[0];
-    r.f1 = f[1];
-    r.f2 = f[2];
-    r.b = (uint32_t)b[0] | ((uint32_t)b[1] << 10) | ((uint32_t)b[2] << 20);
-    r.n0 = n[0];
-    r.n1 = n[1];
-    r.n2 = n[2];
-    r.idx = (uint32_t)i;
-    tmp[i] = r;
+    bool bad;
+    tmp[i] = point_rec<RES>(pts, nrm, i, mybin[u], bad);
+    myrank[u] = atomicAdd(&hist[mybin[u]], 1);
+    anybad |= bad;
   }
   if (anybad) atomicOr(&hdr->flags, 1);
   __syncthreads();
@@ -338,6 +348,130 @@ __device__ __forceinline__ void scan_to_lds(const int* __restrict__ counts, int*
   }
   if (t == BLOCK - 1) soff[NB] = run;  // the last thread's run ends at NB: the total
   __syncthreads();
+}
+
+// Clouds of up to kSortMax points on grids of up to 128^3 (at most one bin per
+// thread) are sorted in two launches instead of three, without global atomics:
+// at most kSortBlocks workgroups each count a chunk of points per bin in LDS and
+// write their row of counts; then every workgroup sums the rows (all of them for
+// the bins' offsets, those before its own for its slots) and scatters its
+// chunk's records, formed again from the points (24 bytes read instead of a
+// 32-byte record written and read). The row sums grow with bins times chunks and
+// few workgroups run, so the three kernels above remain for larger clouds and
+// for 256^3 (us, two against three launches: 32^3 / 3k points 7.5 against 9.4,
+// 128^3 / 20k 9.1 against 10.5, and one launch's gap; 256^3 / 100k 19.5 against
+// 19.7).
+constexpr int kSortBlocks = 32;  // at most one row per lane of a wavefront
+constexpr int kSortThreads = 1024;
+constexpr int kSortPer = 4;  // points per thread at most
+constexpr int64_t kSortMax = (int64_t)kSortBlocks * kSortThreads * kSortPer;
+
+// points per thread of a cloud's sort, and its workgroups
+__host__ __device__ inline int sort_per(int64_t npoints) {
+  return (int)((npoints + (int64_t)kSortBlocks * kSortThreads - 1) / ((int64_t)kSortBlocks * kSortThreads));
+}
+__host__ __device__ inline int sort_blocks(int64_t npoints) {
+  const int64_t chunk = (int64_t)sort_per(npoints) * kSortThreads;
+  return (int)((npoints + chunk - 1) / chunk);
+}
+
+// rows: [workgroup][sort_row(RES)]: the counts, then 1 where a point was not finite
+__host__ __device__ constexpr int sort_row(int res) { return num_bins(res) + 4; }
+
+template <int RES>
+__device__ __forceinline__ void b_sort_count(const float* __restrict__ pts, const float* __restrict__ nrm,
+                                             int64_t npoints, int* __restrict__ rows, int* __restrict__ rank, int bid) {
+  constexpr int NB = num_bins(RES);
+  __shared__ int hist[NB + 1];
+  const int t = threadIdx.x, per = sort_per(npoints);
+  for (int e = t; e <= NB; e += kSortThreads) hist[e] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kSortPer; ++u) {
+    const int64_t i = ((int64_t)bid * per + u) * kSortThreads + t;
+    if (u >= per || i >= npoints) continue;
+    int bin;
+    bool bad;
+    (void)point_rec<RES>(pts, nrm, i, bin, bad);
+    rank[i] = atomicAdd(&hist[bin], 1);
+    if (bad) hist[NB] = 1;
+  }
+  __syncthreads();
+  for (int e = t; e <= NB; e += kSortThreads) rows[bid * sort_row(RES) + e] = hist[e];
+}
+
+// Workgroups [0, nbl - 1) scatter the chunks; the last one publishes the
+// offsets, the bitmaps and the header meanwhile.
+template <int RES>
+__device__ __forceinline__ void b_sort_scatter(const float* __restrict__ pts, const float* __restrict__ nrm,
+                                               int64_t npoints, const int* __restrict__ rows,
+                                               const int* __restrict__ rank, int* __restrict__ off,
+                                               PointRec* __restrict__ sorted, SavedHeader* __restrict__ hdr,
+                                               float sigma, float m, int reading, int bid, int nbl) {
+  constexpr int NB = num_bins(RES), NW = kSortThreads / 64;
+  static_assert(NB <= kSortThreads && kSortBlocks <= 64, "a bin per thread, a row per lane");
+  __shared__ int slot[NB + 1];
+  __shared__ int wtot[NW];
+  __shared__ int bad_any;
+  const int t = threadIdx.x, lane = t & 63, wid = t >> 6, per = sort_per(npoints), nrow = nbl - 1;
+  const bool publish = bid == nrow;
+  // the records, their loads in flight under the row sums
+  PointRec rec[kSortPer];
+  int bin[kSortPer], rk[kSortPer];
+#pragma unroll
+  for (int u = 0; u < kSortPer; ++u) {
+    const int64_t i = ((int64_t)bid * per + u) * kSortThreads + t;
+    bin[u] = -1;
+    if (publish || u >= per || i >= npoints) continue;
+    bool bad;
+    rec[u] = point_rec<RES>(pts, nrm, i, bin[u], bad);
+    rk[u] = rank[i];
+  }
+  int pre = 0, sum = 0;
+  if (t < NB) {
+#pragma unroll 16
+    for (int g = 0; g < nrow; ++g) {
+      const int c = rows[g * sort_row(RES) + t];
+      sum += c;
+      if (g < bid) pre += c;
+    }
+  }
+  if (wid == NW - 1) {
+    const bool bad = lane < nrow && rows[lane * sort_row(RES) + NB] != 0;
+    const bool any = __any(bad);
+    if (lane == 0) bad_any = any;
+  }
+  int x = sum;  // inclusive scan of the bins' totals within the wavefront
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
+  }
+  if (lane == 63) wtot[wid] = x;
+  __syncthreads();
+  int run = x - sum;
+#pragma unroll
+  for (int q = 0; q < NW; ++q)
+    if (q < wid) run += wtot[q];
+  if (t < NB) slot[t] = publish ? run : run + pre;
+  if (t == kSortThreads - 1) slot[NB] = run + sum;  // the total (threads beyond the bins add nothing)
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kSortPer; ++u)
+    if (bin[u] >= 0) sorted[slot[bin[u]] + rk[u]] = rec[u];
+  if (publish) {
+    for (int e = t; e <= NB; e += kSortThreads) off[e] = slot[e];
+    b_live_planes<RES>(slot, hdr);
+    if (t == 0) {
+      hdr->status = 0;
+      hdr->flags = bad_any;
+      hdr->res = RES;
+      hdr->reading = reading;
+      hdr->npoints = npoints;
+      hdr->sigma = sigma;
+      hdr->m = m;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1817,6 +1951,23 @@ __global__ __launch_bounds__(256) void k_bin(const Batch<MAXJ> B) {
   b_bin<RES>(J.pts, J.nrm, J.P, w.counts, w.tmp, w.colrank, sv.hdr, bid);
 }
 
+// The rows of counts lie in the spectrum buffer X, which the first transform
+// overwrites later, the ranks in the room of the (bin, rank) pairs.
+template <int RES, int MAXJ>
+__global__ __launch_bounds__(kSortThreads) void k_sort_count(const Batch<MAXJ> B) {
+  PSR_JOB(RES);
+  static_assert((size_t)kSortBlocks * sort_row(RES) * 4 <= (size_t)3 * (RES / 2 + 1) * RES * RES * 8,
+                "the rows of counts fit the spectrum buffer");
+  b_sort_count<RES>(J.pts, J.nrm, J.P, reinterpret_cast<int*>(w.X), reinterpret_cast<int*>(w.colrank), bid);
+}
+
+template <int RES, int MAXJ>
+__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const Batch<MAXJ> B) {
+  PSR_JOB(RES);
+  b_sort_scatter<RES>(J.pts, J.nrm, J.P, reinterpret_cast<const int*>(w.X), reinterpret_cast<const int*>(w.colrank),
+                      sv.off, sv.sorted, sv.hdr, J.sigma, B.m, B.reading, bid, nbl);
+}
+
 template <int RES, int MAXJ>
 __global__ __launch_bounds__(1024) void k_scan(const Batch<MAXJ> B) {
   PSR_JOB(RES);
@@ -2017,20 +2168,40 @@ static int launch(Exec& x, void (*K)(const Batch<MAXJ>), int block, const JobArg
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
+// points into bin order, the bins' offsets and the bitmaps
+template <int RES, int MAXJ>
+static int seq_bin(Exec& x, const JobArg* J, int n) {
+  using G = Grid<RES>;
+  int rc = 0;
+  if constexpr (num_bins(RES) <= kSortThreads) {
+    bool small = true;
+    for (int j = 0; j < n; ++j) small = small && J[j].P <= kSortMax;
+    if (small) {
+      auto nb = [](const JobArg& a) { return sort_blocks(a.P); };
+      rc |= launch<MAXJ>(x, k_sort_count<RES, MAXJ>, kSortThreads, J, n, nb);
+      rc |= launch<MAXJ>(x, k_sort_scatter<RES, MAXJ>, kSortThreads, J, n,
+                         [](const JobArg& a) { return sort_blocks(a.P) + 1; });
+      return rc;
+    }
+  }
+  rc |= launch<MAXJ>(x, k_init<RES, MAXJ>, 256, J, n, [](const JobArg&) { return G::init_blocks; });
+  rc |= launch<MAXJ>(x, k_bin<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, kBinChunk); });
+  if constexpr (num_bins(RES) <= kLdsBins) {
+    rc |= launch<MAXJ>(x, k_scan_scatter<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, 256); });
+  } else {
+    rc |= launch<MAXJ>(x, k_scan<RES, MAXJ>, 1024, J, n, [](const JobArg&) { return 1; });
+    rc |= launch<MAXJ>(x, k_scatter<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, 256); });
+  }
+  return rc;
+}
+
 template <int RES, int MAXJ>
 static int seq_forward(Exec& x, const JobArg* J, int n) {
   using G = Grid<RES>;
   int rc = 0;
   auto c = [](int v) { return [v](const JobArg&) { return v; }; };
   x.begin(STAGE_BIN);
-  rc |= launch<MAXJ>(x, k_init<RES, MAXJ>, 256, J, n, c(G::init_blocks));
-  rc |= launch<MAXJ>(x, k_bin<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, kBinChunk); });
-  if constexpr (num_bins(RES) <= kLdsBins) {
-    rc |= launch<MAXJ>(x, k_scan_scatter<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, 256); });
-  } else {
-    rc |= launch<MAXJ>(x, k_scan<RES, MAXJ>, 1024, J, n, c(1));
-    rc |= launch<MAXJ>(x, k_scatter<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, 256); });
-  }
+  rc |= seq_bin<RES, MAXJ>(x, J, n);
   x.end(STAGE_BIN);
   if constexpr (use_plane(RES)) {
     x.begin(STAGE_P12);
@@ -2154,14 +2325,7 @@ static int debug_splat_res(Exec& x, const JobArg& job) {
   using G = Grid<RES>;
   auto c = [](int v) { return [v](const JobArg&) { return v; }; };
   int rc = 0;
-  rc |= launch<1>(x, k_init<RES, 1>, 256, &job, 1, c(G::init_blocks));
-  rc |= launch<1>(x, k_bin<RES, 1>, 256, &job, 1, [](const JobArg& a) { return nblk(a.P, kBinChunk); });
-  if constexpr (num_bins(RES) <= kLdsBins) {
-    rc |= launch<1>(x, k_scan_scatter<RES, 1>, 256, &job, 1, [](const JobArg& a) { return nblk(a.P, 256); });
-  } else {
-    rc |= launch<1>(x, k_scan<RES, 1>, 1024, &job, 1, c(1));
-    rc |= launch<1>(x, k_scatter<RES, 1>, 256, &job, 1, [](const JobArg& a) { return nblk(a.P, 256); });
-  }
+  rc |= seq_bin<RES, 1>(x, &job, 1);
   // the splat of the production path: plane passes at 64 and 128, row passes elsewhere
   if constexpr (use_plane(RES))
     rc |= launch<1>(x, k_plane_splat_dbg<RES, 1>, (plane_wg<RES, 1>()), &job, 1, c(3 * RES));
