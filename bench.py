@@ -79,40 +79,41 @@ def stage_bytes(r: int, P: int, fp: float = 1.0, ft: float = 1.0) -> dict:
     method leaves them zero or unused."""
     S = half_spec_bytes(r)
     N4 = 4 * r ** 3
+    slots = 2 if r <= 128 else 4  # gather partials per point and channel (16 bytes each)
     return {
         "bin": 24 * P + 32 * P * 2 + 8 * P,
         "P1_splat_r2c": 32 * P + 3 * S * ft,           # sorted points in, 3 half-spectra of touched row tiles out
         "P2_fft_j1": 3 * S * ft + 2 * S * fp,          # touched tile segments of 3 channels in, v~_0 and merged W of live planes out
-        # live planes of the 2 in, chi~ (after the k0 inverse) out; at 64-128 the plane pass hands over 3 channels
+        # live planes of the 2 in, chi~ (after the k0 inverse) out; at 32-128 the plane pass hands over 3 channels
         # (v~_0, kappa_1 v~_1, kappa_2 v~_2), read whole
-        "P3_fft_j0_spectral_ifft_j0": (3 * S if 64 <= r <= 128 else 2 * S * fp) + S,
+        "P3_fft_j0_spectral_ifft_j0": (3 * S if 32 <= r <= 128 else 2 * S * fp) + S,
         "P4_ifft_j1": 2 * S,
-        "P5_c2r_gather": S + N4 + 32 * P + 64 * P,     # chi' written, gather partials
+        "P5_c2r_gather": S + N4 + 32 * P + 16 * slots * P,  # chi' written, gather partials
         "fwd_reduce": 64 * P + 16 * P,
-        "normalize": 2 * N4,
+        "normalize": 2 * N4 + (16 * slots * P + 16 * P if r <= 256 else 0),  # the points' gradients ride along up to 256
         "bwd_reduce": 2 * N4,
         "B1a_reduce_r2c": 2 * N4 + S * (1 - ft),      # G and chi in (FP64 partials), H = sG spectra of point-free tiles out
         "B1_cotangent_r2c": N4 * ft + 32 * P + S * ft, # the tiles with points: G in, splat of W, spectra out
         "B2_fft_j1": 2 * S,
         "B3_fft_j0_conjop_ifft_j0": S + 2 * S * fp,    # 1 in; kappa_0 channel and U out on live planes
         "B4_ifft_j1": 2 * S * fp + 3 * S * ft,         # live planes in, touched tiles out
-        "B5_c2r_gather": 3 * S * ft + 32 * P + 192 * P,
-        "bwd_finalize": 192 * P + 16 * P + 32 * P + 24 * P,
-        # plane passes (two axes per kernel; 64^3 to 256^3)
+        "B5_c2r_gather": 3 * S * ft + 32 * P + 48 * slots * P,
+        "bwd_finalize": 48 * slots * P + 16 * P + 32 * P + 24 * P,
+        # plane passes (two axes per kernel; 32^3 to 256^3)
         "P12_splat_r2c_fft_j1": 32 * P + 3 * S,        # sorted points in, v~_0, kappa_1 v~_1, kappa_2 v~_2 out
-        "P45_ifft_j1_c2r_gather": S + N4 + 32 * P + 64 * P,
+        "P45_ifft_j1_c2r_gather": S + N4 + 32 * P + 16 * slots * P,
         "B12_cotangent_r2c_fft_j1": N4 + 32 * P + S,
-        "B45_ifft_j1_c2r_gather": 2 * S * fp + 32 * P + 192 * P,  # upper bound: plane parts without points are skipped
+        "B45_ifft_j1_c2r_gather": 2 * S * fp + 32 * P + 48 * slots * P,  # upper bound: plane parts without points are skipped
     }
 
 
 def path_stages(r: int, backward: bool = True) -> list:
-    """The stages one solve runs at grid size r (plane passes at 64-128, the
+    """The stages one solve runs at grid size r (plane passes at 32-128, the
     plane inverse pass also at 256, two-pass row/column kernels elsewhere)."""
-    plane, p45 = 64 <= r <= 128, 64 <= r <= 256
+    plane, p45 = 32 <= r <= 128, 32 <= r <= 256
     f = ["bin"] + (["P12_splat_r2c_fft_j1"] if plane else ["P1_splat_r2c", "P2_fft_j1"])
     f += ["P3_fft_j0_spectral_ifft_j0"] + (["P45_ifft_j1_c2r_gather"] if p45 else ["P4_ifft_j1", "P5_c2r_gather"])
-    f += ["fwd_reduce", "normalize"]
+    f += (["fwd_reduce"] if r >= 512 else []) + ["normalize"]
     b = ["bwd_reduce", "B12_cotangent_r2c_fft_j1"] if plane else ["B1a_reduce_r2c", "B1_cotangent_r2c", "B2_fft_j1"]
     b += ["B3_fft_j0_conjop_ifft_j0"] + (["B45_ifft_j1_c2r_gather"] if plane else ["B4_ifft_j1", "B5_c2r_gather"])
     b += ["bwd_finalize"]

@@ -1063,14 +1063,83 @@ __device__ __forceinline__ void b_axis1_inv(const cf* __restrict__ in, cf* __res
 // then the trilinear gather at the points whose corner lines fall in the tile.
 // Per (point, corner line, channel) the partial is (value, d/dc0, d/dc1,
 // d/dc2) of the interpolant restricted to that line. Partials are slot-major,
-// one array of np float4 per (channel, corner line): part[(c 4 + slot) np + s]
-// with slot = 2 o0 + o1, so the lanes of a wavefront, which hold consecutive
-// sorted points, store whole lines.
+// one array of np float4 per (channel, slot): part[(c NS + slot) np + s] with
+// slot = 2 o0 + o1, or o0 where both lines are in the workgroup (NS =
+// gather_slots), so the lanes of a wavefront, which hold consecutive sorted
+// points, store whole lines.
 // MODE_FWD: chi' (1 channel): writes chi' rows and the partials.
 // MODE_BWD: g_v channel c (grid x3): partials only.
 // MODE_DBG: chi' rows only.
 // ---------------------------------------------------------------------------
 enum { MODE_FWD = 0, MODE_BWD = 1, MODE_DBG = 2 };
+
+// Corner-line slots per point of the gather partials. Where a workgroup holds a
+// whole plane (up to 128) it adds the two lines j1 = b1, b1 + 1 of a point, so
+// only the two planes remain.
+__host__ __device__ constexpr int gather_slots(int res) { return row_tiles(res) == 1 ? 2 : 4; }
+
+// Up to 256 the gather also sums its partials of chi' (FP64, one sum per
+// workgroup), and k_normalize forms the per-point gradients, so no launch of its
+// own stands between them (3 to 5 us). At 512 the 8192 sums would be read by
+// every workgroup of k_normalize; k_fwd_point_reduce sums them there.
+__host__ __device__ constexpr bool fold_reduce(int res) { return res <= 256; }
+
+// This workgroup's sum of v into *out, in a fixed order (lanes, then wavefronts).
+template <int BLOCK>
+__device__ __forceinline__ void workgroup_sum(double v, double* __restrict__ out) {
+  constexpr int NW = BLOCK / 64;
+  static_assert(BLOCK % 64 == 0, "whole wavefronts");
+  __shared__ double ws[NW];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double tot = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) tot += ws[w];
+    *out = tot;
+  }
+}
+
+// The partials of one point at rows [a0, a0 + ROWS) of plane j0, whose samples
+// are in LDS (float slot 2 rpos(l, n/2) + (n & 1)): per corner line the value and
+// the three derivatives of the interpolant restricted to it, lines of the same
+// plane added where gather_slots is 2 (the workgroup then holds both). acc: FP64
+// sum of the values.
+template <int RES, int ROWS>
+__device__ __forceinline__ void gather_point(const float* rf, const float4& p0, int64_t s, int j0, int a0,
+                                             float4* __restrict__ part, int64_t np, double& acc) {
+  constexpr int M = RES / 2, NS = gather_slots(RES);
+  static_assert(NS == 4 || ROWS == RES, "two slots: the workgroup holds the whole plane");
+  const uint32_t bb = __float_as_uint(p0.w);
+  const int b0 = bb & 1023, b1 = (bb >> 10) & 1023, b2 = bb >> 20;
+  const int n0 = b2, n1 = (b2 + 1) & (RES - 1);
+  const float fz = p0.z;
+#pragma unroll
+  for (int o0 = 0; o0 < 2; ++o0) {
+    if (((b0 + o0) & (RES - 1)) != j0) continue;
+    const float wa = o0 ? p0.x : 1.0f - p0.x;
+    const float sa = o0 ? 1.0f : -1.0f;
+    float4 first = make_float4(0, 0, 0, 0);
+#pragma unroll
+    for (int o1 = 0; o1 < 2; ++o1) {
+      const int l = (b1 + o1 - a0) & (RES - 1);
+      if (l >= ROWS) continue;
+      const float wb = o1 ? p0.y : 1.0f - p0.y;
+      const float sb = o1 ? 1.0f : -1.0f;
+      const float v0 = rf[2 * rpos<M>(l, n0 >> 1) + (n0 & 1)], v1 = rf[2 * rpos<M>(l, n1 >> 1) + (n1 & 1)];
+      const float L = (1.0f - fz) * v0 + fz * v1;
+      const float dL = v1 - v0;
+      const float4 q = make_float4(wa * wb * L, (float)RES * sa * wb * L, (float)RES * wa * sb * L,
+                                   (float)RES * wa * wb * dL);
+      acc += (double)q.x;
+      if constexpr (NS == 4) part[(o0 * 2 + o1) * np + s] = q;
+      else if (o1 == 0) first = q;
+      else part[o0 * np + s] = make_float4(first.x + q.x, first.y + q.y, first.z + q.z, first.w + q.w);
+    }
+  }
+}
 
 template <int RES, int MODE>
 __device__ __forceinline__ void b_c2r_gather(const cf* __restrict__ in,
@@ -1079,7 +1148,8 @@ __device__ __forceinline__ void b_c2r_gather(const cf* __restrict__ in,
                                                                const PointRec* __restrict__ sorted,
                                                                const int* __restrict__ off,
                                                                float4* __restrict__ part, int64_t np,
-                                                               const cf* __restrict__ tw, int bid) {
+                                                               const cf* __restrict__ tw,
+                                                               double* __restrict__ sums, int bid) {
   constexpr int M = RES / 2, H = M + 1, TR = tile_rows(RES), NT = row_tiles(RES), BR = rows_wg(RES);
   constexpr int TPL = plan_TPL(M), E = plan_E(M), LS = row_ls(M);
   __shared__ __align__(16) cf rows[rows_lds(RES) * LS];
@@ -1182,33 +1252,11 @@ __device__ __forceinline__ void b_c2r_gather(const cf* __restrict__ in,
     }
   }
   if constexpr (MODE != MODE_DBG) {
-    for_recs<KR, BR, rec_tail(RES)>(recs, sorted, R, t, [&](const float4& p0, const float4& p1, int64_t s) {
-      const uint32_t bb = __float_as_uint(p0.w);
-      const int b0 = bb & 1023, b1 = (bb >> 10) & 1023, b2 = bb >> 20;
-      const int n0 = b2, n1 = (b2 + 1) & (RES - 1);
-
-      const float fz = p0.z;
-#pragma unroll
-      for (int o0 = 0; o0 < 2; ++o0) {
-        if (((b0 + o0) & (RES - 1)) != j0) continue;
-        const float wa = o0 ? p0.x : 1.0f - p0.x;
-        const float sa = o0 ? 1.0f : -1.0f;
-#pragma unroll
-        for (int o1 = 0; o1 < 2; ++o1) {
-          const int l = (b1 + o1 - a0) & (RES - 1);
-          if (l >= TR) continue;
-          const float wb = o1 ? p0.y : 1.0f - p0.y;
-          const float sb = o1 ? 1.0f : -1.0f;
-          const float v0 = rf[2 * rpos<M>(l, n0 >> 1) + (n0 & 1)], v1 = rf[2 * rpos<M>(l, n1 >> 1) + (n1 & 1)];
-          const float L = (1.0f - fz) * v0 + fz * v1;
-          const float dL = v1 - v0;
-          const float4 q = make_float4(wa * wb * L, (float)RES * sa * wb * L, (float)RES * wa * sb * L,
-                                       (float)RES * wa * wb * dL);
-          const int slot = o0 * 2 + o1;
-          part[((MODE == MODE_FWD ? 0 : c * 4) + slot) * np + s] = q;
-        }
-      }
+    double acc = 0.0;
+    for_recs<KR, BR, rec_tail(RES)>(recs, sorted, R, t, [&](const float4& p0, const float4&, int64_t s) {
+      gather_point<RES, TR>(rf, p0, s, j0, a0, part + (MODE == MODE_FWD ? 0 : c * gather_slots(RES)) * np, np, acc);
     });
+    if constexpr (MODE == MODE_FWD && fold_reduce(RES)) workgroup_sum<BR>(acc, sums + bid);
   }
 }
 
@@ -1461,7 +1509,7 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
                                             SavedHeader* __restrict__ hdr,
                                             const PointRec* __restrict__ sorted, const int* __restrict__ off,
                                             float4* __restrict__ part, int64_t np, const cf* __restrict__ tw,
-                                            int bid) {
+                                            double* __restrict__ sums, int bid) {
   using PL = Plane<RES, TMIN>;
   constexpr int M = PL::M, H = PL::H, KP = PL::KP, NCOL = PL::NCOL, TPL = PL::TPL, RC = PL::RC;
   constexpr int LSR = PL::LSR, LSC = PL::LSC, BLOCK = PL::THREADS, TPR = PL::TPR;
@@ -1605,32 +1653,11 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
     first.a[0] = pre0;
     first.b[0] = pre1;
     first.s[0] = pre_s;
+    double acc = 0.0;
     for_recs<1, BLOCK, rec_tail(RES)>(first, sorted, R, t, [&](const float4& p0, const float4&, int64_t s) {
-      const uint32_t bb = __float_as_uint(p0.w);
-      const int b0 = bb & 1023, b1 = (bb >> 10) & 1023, b2 = bb >> 20;
-      const int n0 = b2, n1 = (b2 + 1) & (RES - 1);
-      const float fz = p0.z;
-#pragma unroll
-      for (int o0 = 0; o0 < 2; ++o0) {
-        if (((b0 + o0) & (RES - 1)) != j0) continue;
-        const float wa = o0 ? p0.x : 1.0f - p0.x;
-        const float sa = o0 ? 1.0f : -1.0f;
-#pragma unroll
-        for (int o1 = 0; o1 < 2; ++o1) {
-          const int l = (b1 + o1 - a0) & (RES - 1);
-          if (l >= RC) continue;
-          const float wb = o1 ? p0.y : 1.0f - p0.y;
-          const float sb = o1 ? 1.0f : -1.0f;
-          const float v0 = rf[2 * rpos<M>(l, n0 >> 1) + (n0 & 1)], v1 = rf[2 * rpos<M>(l, n1 >> 1) + (n1 & 1)];
-          const float L = (1.0f - fz) * v0 + fz * v1;
-          const float dL = v1 - v0;
-          const float4 qv = make_float4(wa * wb * L, (float)RES * sa * wb * L, (float)RES * wa * sb * L,
-                                        (float)RES * wa * wb * dL);
-          const int slot = o0 * 2 + o1;
-          part[((MODE == PI_FWD ? 0 : c * 4) + slot) * np + s] = qv;
-        }
-      }
+      gather_point<RES, RC>(rf, p0, s, j0, a0, part + (MODE == PI_FWD ? 0 : c * gather_slots(RES)) * np, np, acc);
     });
+    if constexpr (MODE == PI_FWD) workgroup_sum<BLOCK>(acc, sums + bid);
   }
 }
 
@@ -1638,17 +1665,30 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
 // FP64 reductions and normalisation (main Eq. 4)
 // ---------------------------------------------------------------------------
 
-// Per point: f_i = sum of its 4 corner-line partials (FP64), grad f_i (FP32).
+// grad f_i (FP32) of one point from its partials; .w = f_i
+template <int RES>
+__device__ __forceinline__ float4 point_grad(const float4* __restrict__ part, int64_t npoints, int64_t s) {
+  const float4 q0 = part[s], q1 = part[npoints + s];
+  if constexpr (gather_slots(RES) == 2) {
+    return make_float4(q0.y + q1.y, q0.z + q1.z, q0.w + q1.w, q0.x + q1.x);
+  } else {
+    const float4 q2 = part[2 * npoints + s], q3 = part[3 * npoints + s];
+    const double f = ((double)q0.x + (double)q1.x) + ((double)q2.x + (double)q3.x);
+    return make_float4((q0.y + q1.y) + (q2.y + q3.y), (q0.z + q1.z) + (q2.z + q3.z), (q0.w + q1.w) + (q2.w + q3.w),
+                       (float)f);
+  }
+}
+
+// Per point (512): f_i = sum of its 4 corner-line partials (FP64), grad f_i.
+template <int RES>
 __device__ __forceinline__ void b_fwd_point_reduce(const float4* __restrict__ part, int64_t npoints,
                                                           float4* __restrict__ gradf, double* __restrict__ blockpart, int bid, int nblocks) {
   __shared__ double sh[256];
   double acc = 0.0;
   for (int64_t s = (int64_t)bid * blockDim.x + threadIdx.x; s < npoints; s += (int64_t)nblocks * blockDim.x) {
-    const float4 q0 = part[s], q1 = part[npoints + s], q2 = part[2 * npoints + s], q3 = part[3 * npoints + s];
-    const double f = ((double)q0.x + (double)q1.x) + ((double)q2.x + (double)q3.x);
-    gradf[s] = make_float4((q0.y + q1.y) + (q2.y + q3.y), (q0.z + q1.z) + (q2.z + q3.z),
-                           (q0.w + q1.w) + (q2.w + q3.w), (float)f);
-    acc += f;
+    gradf[s] = point_grad<RES>(part, npoints, s);
+    acc += ((double)part[s].x + (double)part[npoints + s].x) +
+           ((double)part[2 * npoints + s].x + (double)part[3 * npoints + s].x);
   }
   const double tot = block_sum(acc, sh);
   if (threadIdx.x == 0) blockpart[bid] = tot;
@@ -1756,12 +1796,14 @@ __device__ __forceinline__ void b_bwd_point_finalize(const float4* __restrict__ 
   load_rec(sorted, sr, p0, p1);
   const float nv[3] = {p1.x, p1.y, p1.z};
   float dn[3] = {0.0f, 0.0f, 0.0f}, dc[3] = {0.0f, 0.0f, 0.0f};
-  // partials (c, slot) = (o / 2, 2 (o % 2) + h) for lanes 0-5: channel c, two slots each
+  // partials (c, slot) = (o / 2, (NS / 2) (o % 2) + h) for lanes 0-5: channel c,
+  // one slot each (two where the corner lines are apart)
+  constexpr int NS = gather_slots(RES);
   if (o < 6 && live) {
     const int c = o >> 1;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const float4 q = part[(c * 4 + 2 * (o & 1) + h) * npoints + s];
+    for (int h = 0; h < NS / 2; ++h) {
+      const float4 q = part[(c * NS + (NS / 2) * (o & 1) + h) * npoints + s];
       dn[c] += q.x;
       dc[0] += nv[c] * q.y;
       dc[1] += nv[c] * q.z;
@@ -1917,6 +1959,16 @@ __device__ __forceinline__ int job_of(const Batch<MAXJ>& B, int blk) {
   }
 }
 
+__host__ __device__ constexpr int nblk(int64_t n, int b) { return (int)((n + b - 1) / b); }
+// workgroups of the normalisation proper
+__host__ __device__ constexpr int norm_blocks(int res) {
+  return imin(1024, nblk((int64_t)res * res * res / 4, 256));
+}
+// workgroups of the forward gather (P45 or P5), one FP64 sum each
+__host__ __device__ constexpr int gather_wgs(int res) {
+  return use_plane_p45(res) ? res * (res >= PSR_PLANE_SPLIT_MIN ? 2 : 1) : res * row_tiles(res);
+}
+
 #define PSR_JOB(RES)                                                  \
   const int j_ = job_of(B, blockIdx.x);                               \
   const int bid = blockIdx.x - B.start[j_];                           \
@@ -2044,7 +2096,7 @@ __global__ __launch_bounds__(rows_wg(RES)) void k_c2r_gather(const Batch<MAXJ> B
   PSR_JOB(RES);
   if constexpr (MODE == MODE_BWD) { PSR_BWD_GUARD(RES); }
   float* out = MODE == MODE_DBG ? J.aux_out : J.chi;
-  b_c2r_gather<RES, MODE>(w.Y, out, sv.hdr, sv.sorted, sv.off, w.part, J.P, B.tw, bid);
+  b_c2r_gather<RES, MODE>(w.Y, out, sv.hdr, sv.sorted, sv.off, w.part, J.P, B.tw, w.blockpart, bid);
 }
 
 template <int RES, int MODE, int MAXJ>
@@ -2064,7 +2116,8 @@ void k_plane_inv(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   if constexpr (MODE == PI_BWD) { PSR_BWD_GUARD(RES); }
   float* outp = MODE == PI_DBG ? J.aux_out : J.chi;
-  b_plane_inv<RES, MODE, plane_threads(MAXJ)>(w.X, outp, sv.hdr, sv.sorted, sv.off, w.part, J.P, B.tw, bid);
+  b_plane_inv<RES, MODE, plane_threads(MAXJ)>(w.X, outp, sv.hdr, sv.sorted, sv.off, w.part, J.P, B.tw,
+                                                      w.blockpart, bid);
 }
 
 template <int RES, int MAXJ>
@@ -2078,14 +2131,25 @@ void k_plane_splat_dbg(const Batch<MAXJ> B) {
 template <int RES, int MAXJ>
 __global__ __launch_bounds__(256) void k_fwd_point_reduce(const Batch<MAXJ> B) {
   PSR_JOB(RES);
-  b_fwd_point_reduce(w.part, J.P, sv.gradf, w.blockpart, bid, nbl);
+  b_fwd_point_reduce<RES>(w.part, J.P, sv.gradf, w.blockpart, bid, nbl);
 }
 
+// Up to 256 (fold_reduce) the workgroups after the first norm_blocks form the
+// points' gradients from the gather's partials meanwhile.
 template <int RES, int MAXJ>
 __global__ __launch_bounds__(256) void k_normalize(const Batch<MAXJ> B) {
   PSR_JOB(RES);
-  const int nb = (int)((J.P + 255) / 256) > kRedBlocks ? kRedBlocks : (int)((J.P + 255) / 256);
-  b_normalize(J.chi, (int64_t)RES * RES * RES, w.blockpart, nb, sv.hdr, bid, nbl);
+  constexpr int NBL = norm_blocks(RES);
+  if constexpr (fold_reduce(RES)) {
+    if (bid >= NBL) {
+      for (int64_t s = (int64_t)(bid - NBL) * 256 + threadIdx.x; s < J.P; s += (int64_t)(nbl - NBL) * 256)
+        sv.gradf[s] = point_grad<RES>(w.part, J.P, s);
+      return;
+    }
+  }
+  const int np = nblk(J.P, 256);
+  const int nb = fold_reduce(RES) ? gather_wgs(RES) : (np > kRedBlocks ? kRedBlocks : np);
+  b_normalize(J.chi, (int64_t)RES * RES * RES, w.blockpart, nb, sv.hdr, bid, NBL);
 }
 
 template <int RES, int MAXJ>
@@ -2129,8 +2193,6 @@ int static_scratch_address(void** out) {
 // ---------------------------------------------------------------------------
 // host-side launch sequences
 // ---------------------------------------------------------------------------
-static inline int nblk(int64_t n, int b) { return (int)((n + b - 1) / b); }
-constexpr int nblk_c(int64_t n, int b) { return (int)((n + b - 1) / b); }
 
 template <int RES>
 struct Grid {
@@ -2141,8 +2203,7 @@ struct Grid {
   static constexpr int BJ = j0_block(RES);
   static constexpr int BR = rows_wg(RES), BC = cols_block(RES);
   static constexpr int64_t N3 = (int64_t)RES * RES * RES;
-  static constexpr int init_blocks = nblk_c(num_bins(RES), 256) > 64 ? 64 : nblk_c(num_bins(RES), 256);
-  static constexpr int norm_blocks = nblk_c(N3 / 4, 256) > 1024 ? 1024 : nblk_c(N3 / 4, 256);
+  static constexpr int init_blocks = nblk(num_bins(RES), 256) > 64 ? 64 : nblk(num_bins(RES), 256);
 };
 
 // Launch kernel K once per chunk of up to MAXJ jobs; workgroups per job from nb(job).
@@ -2230,12 +2291,16 @@ static int seq_forward(Exec& x, const JobArg* J, int n) {
     rc |= launch<MAXJ>(x, k_c2r_gather<RES, MODE_FWD, MAXJ>, G::BR, J, n, c(G::rows));
     x.end(STAGE_P5);
   }
-  x.begin(STAGE_FWD_REDUCE);
-  rc |= launch<MAXJ>(x, k_fwd_point_reduce<RES, MAXJ>, 256, J, n,
-                     [](const JobArg& a) { return nblk(a.P, 256) > kRedBlocks ? kRedBlocks : nblk(a.P, 256); });
-  x.end(STAGE_FWD_REDUCE);
+  auto point_blocks = [](const JobArg& a) { return imin(nblk(a.P, 256), kRedBlocks); };
+  if constexpr (!fold_reduce(RES)) {
+    x.begin(STAGE_FWD_REDUCE);
+    rc |= launch<MAXJ>(x, k_fwd_point_reduce<RES, MAXJ>, 256, J, n, point_blocks);
+    x.end(STAGE_FWD_REDUCE);
+  }
   x.begin(STAGE_NORMALIZE);
-  rc |= launch<MAXJ>(x, k_normalize<RES, MAXJ>, 256, J, n, c(G::norm_blocks));
+  rc |= launch<MAXJ>(x, k_normalize<RES, MAXJ>, 256, J, n, [&](const JobArg& a) {
+    return norm_blocks(RES) + (fold_reduce(RES) ? point_blocks(a) : 0);
+  });
   x.end(STAGE_NORMALIZE);
   return rc ? -4 : 0;
 }
