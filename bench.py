@@ -95,14 +95,15 @@ def stage_bytes(r: int, P: int, fp: float = 1.0, ft: float = 1.0) -> dict:
         "B1a_reduce_r2c": 2 * N4 + S * (1 - ft),      # G and chi in (FP64 partials), H = sG spectra of point-free tiles out
         "B1_cotangent_r2c": N4 * ft + 32 * P + S * ft, # the tiles with points: G in, splat of W, spectra out
         "B2_fft_j1": 2 * S,
-        "B3_fft_j0_conjop_ifft_j0": S + 2 * S * fp,    # 1 in; kappa_0 channel and U out on live planes
+        # 1 in (2 after a plane pass); kappa_0 channel and U out on live planes
+        "B3_fft_j0_conjop_ifft_j0": (2 * S if 32 <= r <= 128 else S) + 2 * S * fp,
         "B4_ifft_j1": 2 * S * fp + 3 * S * ft,         # live planes in, touched tiles out
         "B5_c2r_gather": 3 * S * ft + 32 * P + 48 * slots * P,
         "bwd_finalize": 48 * slots * P + 16 * P + 32 * P + 24 * P,
         # plane passes (two axes per kernel; 32^3 to 256^3)
         "P12_splat_r2c_fft_j1": 32 * P + 3 * S,        # sorted points in, v~_0, kappa_1 v~_1, kappa_2 v~_2 out
         "P45_ifft_j1_c2r_gather": S + N4 + 32 * P + 16 * slots * P,
-        "B12_cotangent_r2c_fft_j1": N4 + 32 * P + S,
+        "B12_cotangent_r2c_fft_j1": 2 * N4 + 32 * P + 2 * S,  # G and chi in (FP64 sums), (sG)^ and W^ out
         "B45_ifft_j1_c2r_gather": 2 * S * fp + 32 * P + 48 * slots * P,  # upper bound: plane parts without points are skipped
     }
 
@@ -114,7 +115,7 @@ def path_stages(r: int, backward: bool = True) -> list:
     f = ["bin"] + (["P12_splat_r2c_fft_j1"] if plane else ["P1_splat_r2c", "P2_fft_j1"])
     f += ["P3_fft_j0_spectral_ifft_j0"] + (["P45_ifft_j1_c2r_gather"] if p45 else ["P4_ifft_j1", "P5_c2r_gather"])
     f += (["fwd_reduce"] if r >= 512 else []) + ["normalize"]
-    b = ["bwd_reduce", "B12_cotangent_r2c_fft_j1"] if plane else ["B1a_reduce_r2c", "B1_cotangent_r2c", "B2_fft_j1"]
+    b = ["B12_cotangent_r2c_fft_j1"] if plane else ["B1a_reduce_r2c", "B1_cotangent_r2c", "B2_fft_j1"]
     b += ["B3_fft_j0_conjop_ifft_j0"] + (["B45_ifft_j1_c2r_gather"] if plane else ["B4_ifft_j1", "B5_c2r_gather"])
     b += ["bwd_finalize"]
     return f + (b if backward else [])
@@ -150,7 +151,7 @@ KERNEL_STAGES = [
     (r"k_c2r_gather<{r}, 1,", "B5_c2r_gather"),
     (r"k_plane_fwd<{r}, 0,", "P12_splat_r2c_fft_j1"),
     (r"k_plane_inv<{r}, 0,", "P45_ifft_j1_c2r_gather"),
-    (r"k_plane_fwd<{r}, 1,", "B12_cotangent_r2c_fft_j1"),
+    (r"k_plane_fwd<{r}, 3,", "B12_cotangent_r2c_fft_j1"),
     (r"k_plane_inv<{r}, 1,", "B45_ifft_j1_c2r_gather"),
 ]
 

@@ -178,8 +178,8 @@ __device__ __forceinline__ void stage_table(cf* dst, const cf* __restrict__ src,
 // normal component ch over the points of R; KIND 1: the cotangent without
 // its point source at vertex 0, H = s G + alpha W (W = splat of ones, G from
 // gin; the -Q delta_0 term is applied at the points from the point-source
-// table, see b_bwd_point_finalize); KIND 2: rows of v_ch from gin. Ends with a
-// barrier.
+// table, see b_bwd_point_finalize); KIND 2: rows of v_ch from gin; KIND 3: W
+// alone. Ends with a barrier.
 template <int RES, int NROWS, int BLOCK, int KIND, bool LEAN = false>
 __device__ __forceinline__ void fill_rows(cf* rows, const PointRec* __restrict__ sorted, const Ranges& R,
                                           const float* __restrict__ gin, float3 sqa, int j0, int a0, int ch) {
@@ -261,7 +261,7 @@ __device__ __forceinline__ void fill_rows(cf* rows, const PointRec* __restrict__
         const uint32_t bb = __float_as_uint(p0.w);
         const int b0 = bb & 1023, b1 = (bb >> 10) & 1023, b2 = bb >> 20;
         float val;
-        if constexpr (KIND == 1) val = 1.0f;
+        if constexpr (KIND == 1 || KIND == 3) val = 1.0f;
         else val = ch == 0 ? p1.x : (ch == 1 ? p1.y : p1.z);
         // the corner along j2 whose sample index has this round's parity
         // (r is even, so the wrap keeps the parity)

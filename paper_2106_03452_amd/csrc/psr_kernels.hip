@@ -748,6 +748,12 @@ struct Transposed {
       }
     }
   }
+  __device__ __forceinline__ void axpy(float a, const Transposed& y) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+      buf[it] = make_float4(buf[it].x + a * y.buf[it].x, buf[it].y + a * y.buf[it].y, buf[it].z + a * y.buf[it].z,
+                            buf[it].w + a * y.buf[it].w);
+  }
   __device__ __forceinline__ void put(cf* rows) const {
     const int t = LEAN ? opaque_v(threadIdx.x) : threadIdx.x;
 #pragma unroll
@@ -938,10 +944,14 @@ __device__ __forceinline__ void b_fwd_axis0(const cf* __restrict__ in, cf* __res
 // unscaled channel U = IFFT_k0(-i F H^) serves both (kappa_1 is applied in
 // the k1 pass, kappa_2 in the k2 pass). B[1][k2][k1][j0] (or C[1][j0][k2][k1],
 // IN_C) -> C[2][j0][k2][k1].
-template <int RES, bool IN_C, bool LEAN>
+// SEP (after PF_BWDS): the input is (s G)^ and W^, summed on load with alpha
+// from the per-plane FP64 sums; workgroup 0 records the backward scalars.
+template <int RES, bool IN_C, bool SEP, bool LEAN>
 __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __restrict__ out,
                                             const cf* __restrict__ tw, float sigma,
-                                            const uint32_t* __restrict__ livebits, int bid) {
+                                            const uint32_t* __restrict__ livebits, const double2* __restrict__ bpart,
+                                            const SavedHeader* __restrict__ hdr, BwdScalars* __restrict__ bs,
+                                            int bid) {
   constexpr int H = RES / 2 + 1, TC = tile_j0(RES), TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES);
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
@@ -959,6 +969,11 @@ __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __res
   if constexpr (IN_C) {
     Transposed<RES, TC, LEAN> x;
     x.fetch(in + (int64_t)k2 * RES + a0, (int64_t)H * RES);
+    if constexpr (SEP) {
+      Transposed<RES, TC, LEAN> y;
+      y.fetch(in + (int64_t)RES * H * RES + (int64_t)k2 * RES + a0, (int64_t)H * RES);
+      x.axpy(bwd_scalars<j0_block(RES)>(bpart, RES, hdr, bs, bid == 0).z, y);
+    }
     x.put(rows);
     fft<RES, -1, false, true, false, LEAN>(h, rows + l * LS, lt, stw);
   } else {
@@ -1325,25 +1340,33 @@ __device__ __forceinline__ void plane_of(int bid, int& j0, int& u) {
   j0 = (q / U) * 8 + x;
 }
 
-enum { PF_SPLAT = 0, PF_BWDH = 1, PF_LOADV = 2 };
+enum { PF_SPLAT = 0, PF_BWDH = 1, PF_LOADV = 2, PF_BWDS = 3 };
 
 // Rows [a0, a0 + RC) of plane j0 of one channel into LDS (real samples at
 // float slot 2 rpos(l, n/2) + (n & 1)), then the half-length FFT of each row in
 // place. PF_SPLAT: trilinear splat of normal component ch; PF_BWDH: the
-// cotangent H = s G + alpha W; PF_LOADV: v_ch rows from memory.
+// cotangent H = s G + alpha W; PF_LOADV: v_ch rows from memory; PF_BWDS: s G
+// (ch 0), with the FP64 sums of G and G chi into *part, or W (ch 1).
 // Returns false, uniformly and before any barrier, when a splat span holds
 // no point (its rows and spectra are zero and LDS is left untouched).
 template <int RES, int MODE, int TMIN>
 __device__ __forceinline__ bool pf_rows(cf* rows, const cf* stw, const PointRec* __restrict__ sorted,
                                         const int* __restrict__ off, const float* __restrict__ gin,
-                                        float3 sqa, int j0, int a0, int ch) {
+                                        const float* __restrict__ chi, double2* __restrict__ part, float3 sqa, int j0,
+                                        int a0, int ch) {
   using PL = Plane<RES, TMIN>;
   constexpr int M = PL::M, RC = PL::RC, LSR = PL::LSR;
   const int t = threadIdx.x;
   Ranges R{};
   if constexpr (MODE != PF_LOADV) R = span_ranges<RES, RC>(off, j0, a0);
-  if (MODE == PF_SPLAT && R.total == 0) return false;
-  fill_rows<RES, RC, PL::THREADS, MODE>(rows, sorted, R, gin, sqa, j0, a0, ch);
+  if constexpr (MODE == PF_BWDS) {
+    if (ch == 0) bwda_rows<RES, RC, PL::THREADS>(rows, gin, chi, sqa.x, j0, a0, part, true);
+    else if (R.total == 0) return false;
+    else fill_rows<RES, RC, PL::THREADS, 3>(rows, sorted, R, gin, sqa, j0, a0, 0);
+  } else {
+    if (MODE == PF_SPLAT && R.total == 0) return false;
+    fill_rows<RES, RC, PL::THREADS, MODE>(rows, sorted, R, gin, sqa, j0, a0, ch);
+  }
   if (!PL::WIDE || t < PL::BLOCK) {
     cf reg[16];
     fft<M, -1, false, false, PL::WIDE, PL::LEAN>(reg, rows + (t / PL::TPR) * LSR, t % PL::TPR, stw,
@@ -1373,17 +1396,23 @@ __device__ __forceinline__ cf pf_pick(const cf* rows, const cf* wr, int l, int k
 // P12 (MODE PF_SPLAT / PF_LOADV): one channel per workgroup, out v~_0,
 // kappa_1(k1) v~_1 and kappa_2(k2) v~_2; the j0 pass sums the last two into
 // W (the whole grid runs in one wave at 64^3 and 128^3, so equal workgroups
-// beat one doing both W channels). B12 (PF_BWDH): H^ along (j2, j1). Output
-// C[set][j0][k2][k1].
+// beat one doing both W channels). B12 (PF_BWDH, batches): H^ along (j2, j1).
+// B12 (PF_BWDS, single solves): (s G)^ and W^ on separate workgroups, twice as
+// many (one per plane leaves half of the chip idle at 128^3), with the FP64 sums
+// of G and G chi per plane; B3 forms H^ = (s G)^ + alpha W^ on load, so alpha's
+// reduction needs no launch before this one and the splat and the rows of G do
+// not follow each other. A batch fills the chip, where the second channel's
+// traffic would cost more than the launch. Output C[set][j0][k2][k1].
 template <int RES, int MODE, int TMIN>
 __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted, const int* __restrict__ off,
-                                            const float* __restrict__ gin, BwdScalars* __restrict__ bs,
-                                            const double2* __restrict__ bpart, const SavedHeader* __restrict__ hdr,
-                                            const cf* __restrict__ tw, cf* __restrict__ out, int bid) {
+                                            const float* __restrict__ gin, const float* __restrict__ chi,
+                                            BwdScalars* __restrict__ bs, double2* __restrict__ bpart,
+                                            const SavedHeader* __restrict__ hdr, const cf* __restrict__ tw,
+                                            cf* __restrict__ out, int bid) {
   using PL = Plane<RES, TMIN>;
   constexpr int M = PL::M, H = PL::H, KP = PL::KP, NCOL = PL::NCOL, TPL = PL::TPL, RC = PL::RC;
   constexpr int NCHUNK = PL::NCHUNK, LSC = PL::LSC, BLOCK = PL::THREADS;
-  constexpr int NSET = MODE == PF_BWDH ? 1 : 3;
+  constexpr int NSET = MODE == PF_BWDH ? 1 : (MODE == PF_BWDS ? 2 : 3);
   constexpr int VPC = 16 / NCHUNK;  // register elements filled per chunk
   constexpr int64_t CH = (int64_t)H * RES * RES;
   __shared__ __align__(16) cf buf[PL::SLOTS];
@@ -1398,7 +1427,7 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
   const bool fft_thread = !PL::WIDE || t < PL::BLOCK;
   const int kk = part * NCOL + col;  // packed column index; 0 = (k2 = 0, k2 = M)
   cf* const o = out + set * CH + (int64_t)j0 * H * RES;
-  if constexpr (MODE == PF_SPLAT) {
+  if (MODE == PF_SPLAT || (MODE == PF_BWDS && set == 1)) {
     // no point touches the plane: its spectrum is zero
     if (span_ranges<RES, RES>(off, j0, 0).total == 0) {
       const int nout = NCOL + (part == 0 ? 1 : 0);  // output k2 columns of this part (part 0 adds k2 = M)
@@ -1412,13 +1441,15 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
   }
   float3 sqa = make_float3(1.0f, 0.0f, 1.0f);
   if constexpr (MODE == PF_BWDH) sqa = bwd_scalars<BLOCK>(bpart, bwd_reduce_blocks<RES>(), hdr, bs, bid == 0);
+  if constexpr (MODE == PF_BWDS) sqa.x = (float)hdr->scale;
   cf reg[16];
   {
     const int ch = set;
 #pragma unroll 1
     for (int q = 0; q < NCHUNK; ++q) {
       const int a0 = q * RC;
-      const bool any = pf_rows<RES, MODE, TMIN>(buf, stw, sorted, off, gin, sqa, j0, a0, ch);
+      const bool any = pf_rows<RES, MODE, TMIN>(buf, stw, sorted, off, gin, chi, bpart + j0 * NCHUNK + q, sqa, j0,
+                                                a0, ch);
 #pragma unroll
       for (int w2 = 0; w2 < VPC; ++w2) {
         const cf x = any && fft_thread ? pf_pick<RES>(buf, ctw, lt + TPL * w2, kk) : cf{0.0f, 0.0f};
@@ -1431,7 +1462,7 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
     }
     if (fft_thread) fft<RES, -1, true, true, PL::WIDE, PL::LEAN>(reg, buf + col * LSC, lt, ctw);
   }
-  if (set == 1 && kk != 0) {
+  if (MODE != PF_BWDS && set == 1 && kk != 0) {
     scale_odd<RES>(reg, reg, lt);
   }
   if (set == 2) {
@@ -1456,7 +1487,7 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
       const cf pm = line[pidx((RES - k) & (RES - 1))];
       cf f0{0.5f * (reg[v].x + pm.x), 0.5f * (reg[v].y - pm.y)};
       cf fm{0.5f * (reg[v].y + pm.y), -0.5f * (reg[v].x - pm.x)};
-      if (set == 1) {
+      if (MODE != PF_BWDS && set == 1) {
         const float k1f = kappa_odd(k, RES);
         f0 = cscale(f0, k1f);
         fm = cscale(fm, k1f);
@@ -2066,6 +2097,9 @@ __global__ __launch_bounds__(cols_block(RES)) void k_axis1_fwd(const Batch<MAXJ>
   b_axis1_fwd<RES, MERGE, SKIP>(w.X, w.Y, B.tw, sv.hdr->tlive, bid);
 }
 
+// Whether B12 transforms s G and W separately (PF_BWDS).
+__host__ __device__ constexpr bool separate_cotangent(int res, int maxj) { return use_plane(res) && maxj == 1; }
+
 // Whether the j0 passes (three transforms) hold down their registers: where
 // the grid has more workgroups than run at once (256 and 512, batches).
 __host__ __device__ constexpr bool j0_lean(int res, int maxj) { return res >= 256 || maxj > 1; }
@@ -2081,7 +2115,8 @@ template <int RES, int MAXJ>
 __global__ __launch_bounds__(j0_block(RES)) void k_bwd_axis0(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   PSR_BWD_GUARD(RES);
-  b_bwd_axis0<RES, use_plane(RES), j0_lean(RES, MAXJ)>(w.Y, w.X, B.tw, J.sigma, sv.hdr->live, bid);
+  b_bwd_axis0<RES, use_plane(RES), separate_cotangent(RES, MAXJ), j0_lean(RES, MAXJ)>(
+      w.Y, w.X, B.tw, J.sigma, sv.hdr->live, (const double2*)w.blockpart, sv.hdr, w.bs, bid);
 }
 
 template <int RES, bool SPLIT, int MAXJ>
@@ -2104,9 +2139,10 @@ __global__ __launch_bounds__((plane_wg<RES, MAXJ>()))
 __attribute__((amdgpu_waves_per_eu(Plane<RES>::WPE)))
 void k_plane_fwd(const Batch<MAXJ> B) {
   PSR_JOB(RES);
-  if constexpr (MODE == PF_BWDH) { PSR_BWD_GUARD(RES); }
-  const float* gin = MODE == PF_BWDH ? J.dchi : J.aux_in;
-  b_plane_fwd<RES, MODE, plane_threads(MAXJ)>(sv.sorted, sv.off, gin, w.bs, (const double2*)w.blockpart, sv.hdr, B.tw, w.Y, bid);
+  constexpr bool BWD = MODE == PF_BWDH || MODE == PF_BWDS;
+  if constexpr (BWD) { PSR_BWD_GUARD(RES); }
+  b_plane_fwd<RES, MODE, plane_threads(MAXJ)>(sv.sorted, sv.off, BWD ? J.dchi : J.aux_in, J.chi, w.bs,
+                                              (double2*)w.blockpart, sv.hdr, B.tw, w.Y, bid);
 }
 
 template <int RES, int MODE, int MAXJ>
@@ -2310,7 +2346,11 @@ static int seq_backward(Exec& x, const JobArg* J, int n) {
   using G = Grid<RES>;
   int rc = 0;
   auto c = [](int v) { return [v](const JobArg&) { return v; }; };
-  if constexpr (use_plane(RES)) {
+  if constexpr (separate_cotangent(RES, MAXJ)) {
+    x.begin(STAGE_B12);
+    rc |= launch<MAXJ>(x, k_plane_fwd<RES, PF_BWDS, MAXJ>, (plane_wg<RES, MAXJ>()), J, n, c(RES * Plane<RES>::KP * 2));
+    x.end(STAGE_B12);
+  } else if constexpr (use_plane(RES)) {
     x.begin(STAGE_BWD_REDUCE);
     rc |= launch<MAXJ>(x, k_bwd_reduce<RES, MAXJ>, 256, J, n, c(bwd_reduce_blocks<RES>()));
     x.end(STAGE_BWD_REDUCE);
