@@ -306,6 +306,14 @@ int psr_marching_cubes(psr_ctx* ctx, const float* chi, int res, float iso, float
                        int32_t* edges, int64_t vcap, int32_t* tris, int64_t tcap, void* state,
                        hipStream_t stream);
 
+/* psr_marching_cubes and its totals in one call: *nverts, *ntris and *status
+ * (each may be NULL) as psr_mc_counts gives them. The host waits only for the
+ * counting half of the work; the vertices and triangles are written on `stream`
+ * after the call returns. Not for stream capture (it waits). */
+int psr_marching_cubes_sized(psr_ctx* ctx, const float* chi, int res, float iso, float* verts, float* normals,
+                             int32_t* edges, int64_t vcap, int32_t* tris, int64_t tcap, void* state, int64_t* nverts,
+                             int64_t* ntris, int* status, hipStream_t stream);
+
 /* Synchronises `stream` and reads the totals of the last psr_marching_cubes
  * into *nverts and *ntris (either may be NULL); *status (may be NULL) is
  * PSR_OK, or PSR_ETOOBIG when the mesh has 2^29 vertices or more (the vertex
@@ -413,8 +421,8 @@ int psr_opt_step_workspace_bytes(int res, int64_t npoints, int64_t ntarget, int6
  * then wrapped into [0, 1) (the periodic domain), and on the normals.
  * *loss (device double) receives the Chamfer loss; mesh_counts (host,
  * int64_t[2], may be NULL) the mesh's vertices and triangles. The same
- * kernels as the separate calls, in the same order. Synchronises the stream
- * once, to read the mesh size. Returns PSR_ETOOBIG with points, normals and
+ * kernels as the separate calls, in the same order. Waits once, for the
+ * mesh size. Returns PSR_ETOOBIG with points, normals and
  * moments untouched when the mesh exceeds vcap or tcap (mesh_counts then
  * holds the sizes needed), PSR_EDEGENERATE when the mesh is empty. Calls
  * that overlap on one workspace race. */

@@ -86,6 +86,7 @@ def _declare(L):
         "psr_slab_debug_spectral": ([vp, vp, i32, f32, i32, vp, vp, sz, vp], i32),
         "psr_mc_state_bytes": ([i32, P(sz)], i32),
         "psr_marching_cubes": ([vp, vp, i32, f32, vp, vp, vp, i64, vp, i64, vp, vp], i32),
+        "psr_marching_cubes_sized": ([vp, vp, i32, f32, vp, vp, vp, i64, vp, i64, vp, P(i64), P(i64), P(i32), vp], i32),
         "psr_mc_counts": ([vp, vp, P(i64), P(i64), P(i32)], i32),
         "psr_marching_cubes_backward": ([vp, vp, i32, f32, vp, vp, vp, i64, vp, vp], i32),
         "psr_mc_case_table": ([vp, vp], i32),

@@ -100,6 +100,14 @@ struct psr_ctx {
   };
   std::mutex kmu;
   std::vector<KTab> ktabs;
+  // Mesh totals on their way to the host: device-visible host memory and an
+  // event, one pair per call in flight (psr_marching_cubes_sized), reused.
+  struct Totals {
+    psr::mc::McHeader* host;
+    hipEvent_t counted;
+  };
+  std::mutex tmu;
+  std::vector<Totals> totals;
 };
 
 namespace {
@@ -222,6 +230,32 @@ int point_source_table(psr_ctx* ctx, int res, float sigma, hipStream_t stream, c
   return PSR_OK;
 }
 
+// A pair of the context's pool, or a new one; false if it cannot be made.
+bool take_totals(psr_ctx* ctx, psr_ctx::Totals& t) {
+  {
+    std::lock_guard<std::mutex> lk(ctx->tmu);
+    if (!ctx->totals.empty()) {
+      t = ctx->totals.back();
+      ctx->totals.pop_back();
+      return true;
+    }
+  }
+  void* p = nullptr;
+  if (hipHostMalloc(&p, sizeof(psr::mc::McHeader), hipHostMallocCoherent) != hipSuccess) return false;
+  t.host = static_cast<psr::mc::McHeader*>(p);
+  if (hipEventCreateWithFlags(&t.counted, hipEventDisableTiming) != hipSuccess) {
+    (void)hipHostFree(p);
+    return false;
+  }
+  return true;
+}
+
+// The pool holds at most as many pairs as calls have run at once.
+void give_totals(psr_ctx* ctx, const psr_ctx::Totals& t) {
+  std::lock_guard<std::mutex> lk(ctx->tmu);
+  ctx->totals.push_back(t);
+}
+
 const char* const kStageNames[psr::NUM_STAGES] = {
     "bin", "P1_splat_r2c", "P2_fft_j1", "P3_fft_j0_spectral_ifft_j0", "P4_ifft_j1", "P5_c2r_gather",
     "fwd_reduce", "normalize", "bwd_reduce", "B1_cotangent_r2c", "B2_fft_j1", "B3_fft_j0_conjop_ifft_j0",
@@ -291,6 +325,10 @@ int psr_ctx_destroy(psr_ctx* ctx) {
   delete ctx->timers;
   if (ctx->tw) (void)hipFree(ctx->tw);
   for (auto& k : ctx->ktabs) (void)hipFree(k.table);
+  for (auto& t : ctx->totals) {
+    (void)hipEventDestroy(t.counted);
+    (void)hipHostFree(t.host);
+  }
   delete ctx;
   return PSR_OK;
 }
@@ -556,6 +594,32 @@ int psr_marching_cubes(psr_ctx* ctx, const float* chi, int res, float iso, float
   return psr::mc::run_forward(res, chi, iso, psr::mc::state_view(state, res), out, stream) ? PSR_EDEVICE : PSR_OK;
 }
 
+int psr_marching_cubes_sized(psr_ctx* ctx, const float* chi, int res, float iso, float* verts, float* normals,
+                             int32_t* edges, int64_t vcap, int32_t* tris, int64_t tcap, void* state, int64_t* nverts,
+                             int64_t* ntris, int* status, hipStream_t stream) {
+  if (!ctx || !chi || !state || !valid_res(res) || !std::isfinite(iso) || vcap < 0 || tcap < 0) return PSR_EINVAL;
+  if ((vcap > 0 && (!verts || !normals)) || (tcap > 0 && !tris)) return PSR_EINVAL;
+  if (!aligned(state, 256) || !aligned(chi, 4)) return PSR_EINVAL;
+  DeviceGuard g(ctx->device);
+  psr_ctx::Totals t;
+  if (!take_totals(ctx, t)) return PSR_ENOMEM;
+  psr::mc::McOut out{verts, normals, edges, tris, vcap, tcap};
+  int rc = psr::mc::run_forward(res, chi, iso, psr::mc::state_view(state, res), out, stream, t.host, t.counted)
+               ? PSR_EDEVICE
+               : PSR_OK;
+  if (rc == PSR_OK && hipEventSynchronize(t.counted) != hipSuccess) rc = PSR_EDEVICE;
+  if (rc != PSR_OK) {
+    // a kernel of this call may still write the pair: it does not go back to the pool
+    return rc;
+  }
+  const psr::mc::McHeader h = *t.host;
+  give_totals(ctx, t);
+  if (nverts) *nverts = h.nv;
+  if (ntris) *ntris = h.nt;
+  if (status) *status = h.status ? PSR_ETOOBIG : PSR_OK;
+  return PSR_OK;
+}
+
 int psr_mc_counts(const void* state, hipStream_t stream, int64_t* nverts, int64_t* ntris, int* status) {
   if (!state) return PSR_EINVAL;
   if (hipStreamSynchronize(stream) != hipSuccess) return PSR_EDEVICE;
@@ -736,12 +800,10 @@ int psr_opt_step(psr_ctx* ctx, float* points, float* normals, int64_t npoints, f
   float* chi = f32(L.chi);
   int rc = psr_forward(ctx, points, normals, npoints, res, sigma, chi, b + L.saved, b + L.fws, L.fws_bytes, stream);
   if (rc != PSR_OK) return rc;
-  rc = psr_marching_cubes(ctx, chi, res, 0.0f, f32(L.verts), f32(L.vnorm), i32(L.edges), vcap, i32(L.tris), tcap,
-                          b + L.mcs, stream);
-  if (rc != PSR_OK) return rc;
   int64_t nv = 0, nt = 0;
   int st = PSR_OK;
-  rc = psr_mc_counts(b + L.mcs, stream, &nv, &nt, &st);
+  rc = psr_marching_cubes_sized(ctx, chi, res, 0.0f, f32(L.verts), f32(L.vnorm), i32(L.edges), vcap, i32(L.tris), tcap,
+                                b + L.mcs, &nv, &nt, &st, stream);
   if (rc != PSR_OK) return rc;
   if (mesh_counts) {
     mesh_counts[0] = nv;

@@ -22,6 +22,7 @@ constexpr int kMcThreads = 256;                 // threads per workgroup of the 
 constexpr int kMcVpt = 4;                       // consecutive grid vertices (along j2) per thread
 constexpr int kMcBlock = kMcThreads * kMcVpt;   // grid vertices per workgroup
 constexpr int kMcGroup = 1024;                  // workgroup counts per first-level scan group
+constexpr int kMcOne = 2 * kMcGroup;            // workgroup counts that one workgroup scans (grids up to 128^3)
 
 struct McState {
   McHeader* hdr;
@@ -72,7 +73,11 @@ inline McState state_view(void* base, int res) {
   return s;
 }
 
-int run_forward(int res, const float* chi, float iso, const McState& st, const McOut& out, hipStream_t s);
+// The totals are known after the counting half: host (may be null, device-visible
+// host memory) receives the header there, and counted (may be null) is recorded
+// between the halves, so that a caller may read them while the mesh is written.
+int run_forward(int res, const float* chi, float iso, const McState& st, const McOut& out, hipStream_t s,
+                McHeader* host = nullptr, hipEvent_t counted = nullptr);
 int run_backward(int res, const float* chi, float iso, const McState& st, const float* normals,
                  const float* dverts, int64_t nverts, float* dchi, hipStream_t s);
 void case_table(int8_t* ntri, int8_t* edge);

@@ -7,7 +7,7 @@
 //   count  per vertex: crossing edges it owns and triangles of its cell,
 //          summed per workgroup (1024 vertices: 4 consecutive ones along j2
 //          per thread, read as float4 rows)
-//   scan   exclusive offsets of the workgroup sums, in two levels
+//   scan   exclusive offsets of the workgroup sums (in two levels from 256^3)
 //   emit   per vertex again, in the workgroups that hold surface only: its
 //          mesh vertices (position by linear zero along the edge, normal from
 //          the central-difference gradient), the base index of its vertices,
@@ -206,8 +206,21 @@ __global__ __launch_bounds__(kMcGroup) void k_mc_scan1(McState st, int nblocks) 
   if (threadIdx.x == 0) st.tops[blockIdx.x] = tot;
 }
 
+// the totals, to the state and, where the caller waits for them, to host memory
+__device__ __forceinline__ void put_header(const McState& st, McHeader* host, int2 total, int res, float iso) {
+  McHeader h;
+  h.nv = total.x;
+  h.nt = total.y;
+  h.res = res;
+  h.status = total.x >= (1 << 29) ? -1 : 0;
+  h.iso = iso;
+  h.pad = 0;
+  *st.hdr = h;
+  if (host) *host = h;
+}
+
 // second level: exclusive offsets of the groups (one workgroup); totals to the header
-__global__ __launch_bounds__(kMcGroup) void k_mc_scan2(McState st, int ngroups, int res, float iso) {
+__global__ __launch_bounds__(kMcGroup) void k_mc_scan2(McState st, McHeader* host, int ngroups, int res, float iso) {
   __shared__ int2 wtot[kMcGroup / 64];
   int2 carry = make_int2(0, 0);
   for (int g0 = 0; g0 < ngroups; g0 += kMcGroup) {
@@ -220,13 +233,25 @@ __global__ __launch_bounds__(kMcGroup) void k_mc_scan2(McState st, int ngroups, 
     carry.x += tot.x;
     carry.y += tot.y;
   }
-  if (threadIdx.x == 0) {
-    st.hdr->nv = carry.x;
-    st.hdr->nt = carry.y;
-    st.hdr->res = res;
-    st.hdr->iso = iso;
-    st.hdr->status = carry.x >= (1 << 29) ? -1 : 0;
-  }
+  if (threadIdx.x == 0) put_header(st, host, carry, res, iso);
+}
+
+// Both levels in one workgroup, for up to kMcOne counts: one launch less. At
+// 256^3 (16384 counts) one workgroup takes 17 us where the two kernels take 8.
+__global__ __launch_bounds__(kMcGroup) void k_mc_scan_one(McState st, McHeader* host, int nblocks, int res,
+                                                          float iso) {
+  __shared__ int2 wtot[kMcGroup / 64];
+  const int t = threadIdx.x, i = 2 * t;
+  static_assert(kMcOne == 2 * kMcGroup, "two counts per thread");
+  const int2 a = i < nblocks ? st.blk[i] : make_int2(0, 0), b = i + 1 < nblocks ? st.blk[i + 1] : make_int2(0, 0);
+  const int2 sum = make_int2(a.x + b.x, a.y + b.y);
+  int2 tot;
+  const int2 incl = block_scan2<kMcGroup>(sum, wtot, tot);
+  const int2 run = make_int2(incl.x - sum.x, incl.y - sum.y);
+  if (i < nblocks) st.blk[i] = run;
+  if (i + 1 < nblocks) st.blk[i + 1] = make_int2(run.x + a.x, run.y + a.y);
+  if (t < (nblocks + kMcGroup - 1) / kMcGroup) st.tops[t] = make_int2(0, 0);
+  if (t == 0) put_header(st, host, tot, res, iso);
 }
 
 template <int R>
@@ -472,11 +497,17 @@ __global__ __launch_bounds__(kMcThreads) void k_mc_backward(const float* __restr
 }
 
 template <int R>
-static int forward_res(const float* chi, float iso, const McState& st, const McOut& out, hipStream_t s) {
+static int forward_res(const float* chi, float iso, const McState& st, const McOut& out, hipStream_t s,
+                       McHeader* host, hipEvent_t counted) {
   const int nb = (int)mc_blocks(R), ng = (int)mc_groups(R);
   hipLaunchKernelGGL(k_mc_count<R>, dim3(nb), dim3(kMcThreads), 0, s, chi, iso, st);
-  hipLaunchKernelGGL(k_mc_scan1, dim3(ng), dim3(kMcGroup), 0, s, st, nb);
-  hipLaunchKernelGGL(k_mc_scan2, dim3(1), dim3(kMcGroup), 0, s, st, ng, R, iso);
+  if (nb <= kMcOne) {
+    hipLaunchKernelGGL(k_mc_scan_one, dim3(1), dim3(kMcGroup), 0, s, st, host, nb, R, iso);
+  } else {
+    hipLaunchKernelGGL(k_mc_scan1, dim3(ng), dim3(kMcGroup), 0, s, st, nb);
+    hipLaunchKernelGGL(k_mc_scan2, dim3(1), dim3(kMcGroup), 0, s, st, host, ng, R, iso);
+  }
+  if (counted && hipEventRecord(counted, s) != hipSuccess) return -4;
   hipLaunchKernelGGL(k_mc_emit<R>, dim3(nb), dim3(kMcThreads), 0, s, chi, iso, st, out);
   hipLaunchKernelGGL(k_mc_link, dim3(1024), dim3(256), 0, s, st, out);
   return hipGetLastError() == hipSuccess ? 0 : -4;
@@ -503,8 +534,9 @@ static int backward_res(const float* chi, float iso, const McState& st, const fl
     default: return -1;            \
   }
 
-int run_forward(int res, const float* chi, float iso, const McState& st, const McOut& out, hipStream_t s) {
-#define CALL(R) forward_res<R>(chi, iso, st, out, s)
+int run_forward(int res, const float* chi, float iso, const McState& st, const McOut& out, hipStream_t s,
+                McHeader* host, hipEvent_t counted) {
+#define CALL(R) forward_res<R>(chi, iso, st, out, s, host, counted)
   PSR_MC_DISPATCH(res, CALL)
 #undef CALL
 }

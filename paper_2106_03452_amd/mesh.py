@@ -1,7 +1,7 @@
 """Marching Cubes on the indicator grid, differentiable with respect to the
 grid through the inverse surface normal (main Sec. 3.2, Eq. 6).
 
-Every step runs in ``libpsr.so`` (``psr_marching_cubes`` and
+Every step runs in ``libpsr.so`` (``psr_marching_cubes_sized`` and
 ``psr_marching_cubes_backward``); this module allocates buffers through
 PyTorch, reads the mesh size, and wraps the two calls in an autograd Function.
 """
@@ -45,8 +45,8 @@ def marching_cubes(chi: torch.Tensor, iso: float = 0.0, ctx: _lib.Context | None
     """Mesh of the level chi = iso of a (res, res, res) float32 CUDA grid.
 
     Runs the library call with a capacity guess and, if the mesh is larger,
-    once more with the exact sizes (the call synchronises the stream to read
-    the mesh size)."""
+    once more with the exact sizes (the call waits for the mesh size, not for
+    the mesh)."""
     if not chi.is_cuda or chi.dtype != torch.float32 or chi.dim() != 3 or len(set(chi.shape)) != 1:
         raise ValueError("chi must be a cubic CUDA float32 grid")
     chi = chi.detach().contiguous()
@@ -61,12 +61,11 @@ def marching_cubes(chi: torch.Tensor, iso: float = 0.0, ctx: _lib.Context | None
         normals = torch.empty((vcap, 3), dtype=torch.float32, device=dev)
         edges = torch.empty((vcap,), dtype=torch.int32, device=dev)
         tris = torch.empty((tcap, 3), dtype=torch.int32, device=dev)
-        _lib.check(L.psr_marching_cubes(ctx.handle, _ptr(chi), res, float(iso), _ptr(verts), _ptr(normals),
-                                        _ptr(edges), vcap, _ptr(tris), tcap, _ptr(state), _stream(dev)),
-                   "psr_marching_cubes")
         nv, nt, st = ctypes.c_int64(0), ctypes.c_int64(0), ctypes.c_int(0)
-        _lib.check(L.psr_mc_counts(_ptr(state), _stream(dev), ctypes.byref(nv), ctypes.byref(nt), ctypes.byref(st)),
-                   "psr_mc_counts")
+        _lib.check(L.psr_marching_cubes_sized(ctx.handle, _ptr(chi), res, float(iso), _ptr(verts), _ptr(normals),
+                                              _ptr(edges), vcap, _ptr(tris), tcap, _ptr(state), ctypes.byref(nv),
+                                              ctypes.byref(nt), ctypes.byref(st), _stream(dev)),
+                   "psr_marching_cubes")
         _lib.check(st.value, "psr_marching_cubes")
         if nv.value <= vcap and nt.value <= tcap:
             n, m = int(nv.value), int(nt.value)
