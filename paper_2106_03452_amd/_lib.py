@@ -9,6 +9,7 @@ missing, loading fails loudly.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import re
 import threading
@@ -115,6 +116,8 @@ def _declare(L):
 def lib():
     """Load ``libpsr.so`` (once). Raises ImportError if it has not been built."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -123,7 +126,7 @@ def lib():
                     "(python -m paper_2106_03452_amd.build, or __graft_entry__.build())")
             L = ctypes.CDLL(LIB_PATH)
             _declare(L)
-            _lib = L
+            _lib = L  # published last: a thread that sees it sees the signatures
     return _lib
 
 
@@ -145,17 +148,28 @@ def check(code: int, what: str) -> None:
         raise PSRError(code, what)
 
 
-def workspace_bytes(res: int, npoints: int, with_backward: bool = True) -> int:
+# The sizes depend on these numbers alone, and a training loop asks for the
+# same few on every call: kept for the last 256 (errors are not kept).
+@functools.lru_cache(maxsize=256)
+def _workspace_bytes(res: int, npoints: int, with_backward: int) -> int:
     out = ctypes.c_size_t(0)
-    check(lib().psr_workspace_bytes(int(res), int(npoints), int(with_backward), ctypes.byref(out)),
-          "psr_workspace_bytes")
+    check(lib().psr_workspace_bytes(res, npoints, with_backward, ctypes.byref(out)), "psr_workspace_bytes")
     return int(out.value)
+
+
+@functools.lru_cache(maxsize=256)
+def _saved_bytes(res: int, npoints: int) -> int:
+    out = ctypes.c_size_t(0)
+    check(lib().psr_saved_bytes(res, npoints, ctypes.byref(out)), "psr_saved_bytes")
+    return int(out.value)
+
+
+def workspace_bytes(res: int, npoints: int, with_backward: bool = True) -> int:
+    return _workspace_bytes(int(res), int(npoints), int(with_backward))
 
 
 def saved_bytes(res: int, npoints: int) -> int:
-    out = ctypes.c_size_t(0)
-    check(lib().psr_saved_bytes(int(res), int(npoints), ctypes.byref(out)), "psr_saved_bytes")
-    return int(out.value)
+    return _saved_bytes(int(res), int(npoints))
 
 
 class Context:
@@ -203,8 +217,7 @@ _contexts: dict[int, Context] = {}
 
 def context(device: int = 0) -> Context:
     """Process-wide context per device (created on first use)."""
-    with _lock:
-        c = _contexts.get(int(device))
+    c = _contexts.get(int(device))
     if c is None:
         c = Context(device)
         with _lock:

@@ -13,12 +13,18 @@ import torch
 from . import _lib
 
 
-def _ptr(t: torch.Tensor | None):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+def _ptr(t: torch.Tensor | None) -> int | None:
+    """Device address for an argument declared as a pointer (None: NULL)."""
+    return t.data_ptr() if t is not None else None
 
 
-def _stream(device: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _device_index(dev: torch.device) -> int:
+    return dev.index if dev.index is not None else torch.cuda.current_device()
+
+
+def _stream(dev: torch.device) -> int:
+    """The current HIP stream of the device, without a torch.cuda.Stream around it."""
+    return torch._C._cuda_getCurrentRawStream(_device_index(dev))
 
 
 def _check_points(points: torch.Tensor, normals: torch.Tensor):
@@ -37,7 +43,7 @@ def forward(points: torch.Tensor, normals: torch.Tensor, res: int, sigma: float 
     points = points.contiguous()
     normals = normals.contiguous()
     dev = points.device
-    ctx = ctx or _lib.context(dev.index if dev.index is not None else torch.cuda.current_device())
+    ctx = ctx or _lib.context(_device_index(dev))
     P = int(points.shape[0])
     ws_bytes = _lib.workspace_bytes(res, P)
     if workspace is None or workspace.numel() < ws_bytes:
@@ -45,7 +51,7 @@ def forward(points: torch.Tensor, normals: torch.Tensor, res: int, sigma: float 
     saved = torch.empty(_lib.saved_bytes(res, P), dtype=torch.uint8, device=dev)
     chi = torch.empty((res, res, res), dtype=torch.float32, device=dev)
     rc = _lib.lib().psr_forward(ctx.handle, _ptr(points), _ptr(normals), P, int(res), float(sigma),
-                                _ptr(chi), _ptr(saved), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+                                _ptr(chi), _ptr(saved), _ptr(workspace), workspace.numel(),
                                 _stream(dev))
     _lib.check(rc, "psr_forward")
     # the resolution and point count this state was made for; backward checks them
@@ -72,7 +78,7 @@ def backward(chi: torch.Tensor, saved: torch.Tensor, dchi: torch.Tensor, npoints
     """Run ``psr_backward``. Returns (dpoints or None, dnormals or None), each (P, 3)."""
     dev = chi.device
     _check_saved(chi, saved, npoints, res)
-    ctx = ctx or _lib.context(dev.index if dev.index is not None else torch.cuda.current_device())
+    ctx = ctx or _lib.context(_device_index(dev))
     dchi = dchi.contiguous().to(torch.float32)
     if dchi.shape != chi.shape:
         raise ValueError("dchi must have the shape of chi")
@@ -83,7 +89,7 @@ def backward(chi: torch.Tensor, saved: torch.Tensor, dchi: torch.Tensor, npoints
     dn = torch.empty((npoints, 3), dtype=torch.float32, device=dev) if need_normals else None
     rc = _lib.lib().psr_backward(ctx.handle, int(npoints), int(res), float(sigma), _ptr(chi), _ptr(saved),
                                  _ptr(dchi), _ptr(dp), _ptr(dn), _ptr(workspace),
-                                 ctypes.c_size_t(workspace.numel()), _stream(dev))
+                                 workspace.numel(), _stream(dev))
     _lib.check(rc, "psr_backward")
     return dp, dn
 
@@ -111,11 +117,11 @@ def debug_spectral(v: torch.Tensor, sigma: float = 2.0, ctx: _lib.Context | None
     v = v.contiguous()
     res = int(v.shape[-1])
     dev = v.device
-    ctx = ctx or _lib.context(dev.index if dev.index is not None else torch.cuda.current_device())
+    ctx = ctx or _lib.context(_device_index(dev))
     ws = torch.empty(_lib.workspace_bytes(res, 1), dtype=torch.uint8, device=dev)
     out = torch.empty((res, res, res), dtype=torch.float32, device=dev)
     _lib.check(_lib.lib().psr_debug_spectral(ctx.handle, _ptr(v), res, float(sigma), _ptr(out), _ptr(ws),
-                                             ctypes.c_size_t(ws.numel()), _stream(dev)), "psr_debug_spectral")
+                                             ws.numel(), _stream(dev)), "psr_debug_spectral")
     return out
 
 
@@ -125,13 +131,13 @@ def debug_splat(points: torch.Tensor, normals: torch.Tensor, res: int,
     _check_points(points, normals)
     points, normals = points.contiguous(), normals.contiguous()
     dev = points.device
-    ctx = ctx or _lib.context(dev.index if dev.index is not None else torch.cuda.current_device())
+    ctx = ctx or _lib.context(_device_index(dev))
     P = int(points.shape[0])
     ws = torch.empty(_lib.workspace_bytes(res, P), dtype=torch.uint8, device=dev)
     saved = torch.empty(_lib.saved_bytes(res, P), dtype=torch.uint8, device=dev)
     v = torch.empty((3, res, res, res), dtype=torch.float32, device=dev)
     _lib.check(_lib.lib().psr_debug_splat(ctx.handle, _ptr(points), _ptr(normals), P, int(res), _ptr(v),
-                                          _ptr(saved), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream(dev)),
+                                          _ptr(saved), _ptr(ws), ws.numel(), _stream(dev)),
                "psr_debug_splat")
     return v
 

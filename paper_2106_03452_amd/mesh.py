@@ -8,25 +8,24 @@ PyTorch, reads the mesh size, and wraps the two calls in an autograd Function.
 from __future__ import annotations
 
 import ctypes
+import functools
 from dataclasses import dataclass
 
 import torch
 
 from . import _lib
+from .function import _device_index, _ptr, _stream
 
 
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
-
-
-def _stream(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+@functools.lru_cache(maxsize=64)  # of the resolution alone
+def _state_bytes(res: int) -> int:
+    out = ctypes.c_size_t(0)
+    _lib.check(_lib.lib().psr_mc_state_bytes(res, ctypes.byref(out)), "psr_mc_state_bytes")
+    return int(out.value)
 
 
 def state_bytes(res: int) -> int:
-    out = ctypes.c_size_t(0)
-    _lib.check(_lib.lib().psr_mc_state_bytes(int(res), ctypes.byref(out)), "psr_mc_state_bytes")
-    return int(out.value)
+    return _state_bytes(int(res))
 
 
 @dataclass
@@ -52,7 +51,7 @@ def marching_cubes(chi: torch.Tensor, iso: float = 0.0, ctx: _lib.Context | None
     chi = chi.detach().contiguous()
     res = int(chi.shape[0])
     dev = chi.device
-    ctx = ctx or _lib.context(dev.index if dev.index is not None else torch.cuda.current_device())
+    ctx = ctx or _lib.context(_device_index(dev))
     L = _lib.lib()
     state = torch.empty(state_bytes(res), dtype=torch.uint8, device=dev)
     vcap, tcap = capacity or (max(4096, 8 * res * res), max(8192, 16 * res * res))
@@ -84,7 +83,7 @@ def marching_cubes_backward(chi: torch.Tensor, mesh: Mesh, dverts: torch.Tensor,
     dverts = dverts.contiguous().to(torch.float32)
     if dverts.shape != mesh.verts.shape:
         raise ValueError("dverts must have the shape of the mesh vertices")
-    ctx = ctx or _lib.context(dev.index if dev.index is not None else torch.cuda.current_device())
+    ctx = ctx or _lib.context(_device_index(dev))
     dchi = torch.empty_like(chi)
     nv = int(mesh.verts.shape[0])
     _lib.check(_lib.lib().psr_marching_cubes_backward(ctx.handle, _ptr(chi), mesh.res, float(mesh.iso),
@@ -103,11 +102,14 @@ class MarchingCubesFunction(torch.autograd.Function):
         ctx.mesh = mesh
         ctx.save_for_backward(chi)
         ctx.mark_non_differentiable(mesh.faces, mesh.normals)
+        ctx.set_materialize_grads(False)  # no zeros for the faces and normals
         return mesh.verts, mesh.faces, mesh.normals
 
     @staticmethod
     def backward(ctx, dverts, dfaces, dnormals):
         (chi,) = ctx.saved_tensors
+        if dverts is None:
+            dverts = torch.zeros_like(ctx.mesh.verts)
         return marching_cubes_backward(chi, ctx.mesh, dverts), None
 
 

@@ -29,18 +29,11 @@ import torch
 from . import _lib
 from . import function as F
 from . import mesh as M
-
-
-def _p(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
-
-
-def _st(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+from .function import _ptr as _p, _stream as _st
 
 
 def _ctx(dev):
-    return _lib.context(dev.index if dev.index is not None else torch.cuda.current_device())
+    return _lib.context(F._device_index(dev))
 
 
 def _size(fn, *args):
@@ -64,7 +57,7 @@ def sample_raw(verts, faces, u, vnormals=None, face_weight=None):
                                  _p(faces.contiguous()), nf,
                                  _p(face_weight.contiguous()) if face_weight is not None else None,
                                  _p(u.contiguous()), m, _p(pts), _p(nrm), _p(face), _p(bary), _p(ws),
-                                 ctypes.c_size_t(ws.numel()), _st(dev)), "psr_mesh_sample")
+                                 ws.numel(), _st(dev)), "psr_mesh_sample")
     return pts, nrm, face, bary
 
 
@@ -101,7 +94,7 @@ def chamfer_raw(x, y):
     dy = torch.empty((ny,), dtype=torch.float32, device=dev)
     loss = torch.empty((), dtype=torch.float64, device=dev)
     _lib.check(L.psr_chamfer(_ctx(dev).handle, _p(x.detach().contiguous()), nx, _p(y.contiguous()), ny, _p(nnx),
-                             _p(dx), _p(nny), _p(dy), _p(loss), _p(ws), ctypes.c_size_t(ws.numel()), _st(dev)),
+                             _p(dx), _p(nny), _p(dy), _p(loss), _p(ws), ws.numel(), _st(dev)),
                "psr_chamfer")
     return loss, nnx, dx, nny, dy
 
@@ -136,7 +129,7 @@ def components(verts, faces, largest: bool = True):
     lab = torch.empty((nv,), dtype=torch.int32, device=dev)
     w = torch.empty((nf,), dtype=torch.float32, device=dev) if largest else None
     _lib.check(L.psr_mesh_components(_ctx(dev).handle, _p(verts.detach().contiguous()), nv, _p(faces.contiguous()),
-                                     nf, _p(lab), _p(w), _p(ws), ctypes.c_size_t(ws.numel()), _st(dev)),
+                                     nf, _p(lab), _p(w), _p(ws), ws.numel(), _st(dev)),
                "psr_mesh_components")
     return lab, w
 
@@ -215,7 +208,7 @@ class NativeStep:
             rc = L.psr_opt_step(_ctx(self.dev).handle, _p(p), _p(n), self.P, _p(mp), _p(vp), _p(mn), _p(vn), int(t),
                                 float(lr), float(betas[0]), float(betas[1]), float(eps), _p(target), self.T, _p(u),
                                 self.S, self.res, float(sigma), self.vcap, self.tcap, _p(self.loss), self.counts,
-                                _p(self.ws), ctypes.c_size_t(self.ws.numel()), _st(self.dev))
+                                _p(self.ws), self.ws.numel(), _st(self.dev))
             if rc == _lib.PSR_ETOOBIG:  # nothing was updated: grow the mesh cap and run the step again
                 self.vcap = max(self.vcap, int(self.counts[0]))
                 self.tcap = max(self.tcap, int(self.counts[1]))

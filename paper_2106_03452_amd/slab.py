@@ -43,7 +43,7 @@ def forward_raw(points: torch.Tensor, normals: torch.Tensor, res: int, sigma: fl
     dev = points.device
     _lib.check(_lib.lib().psr_slab_forward(_ctx(dev, ctx).handle, _ptr(points), _ptr(normals),
                                            int(points.shape[0]), int(res), float(sigma), int(slabs), _ptr(chi),
-                                           _ptr(result), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+                                           _ptr(result), _ptr(workspace), workspace.numel(),
                                            _stream(dev)), "psr_slab_forward")
 
 
@@ -81,6 +81,6 @@ def debug_spectral(v: torch.Tensor, sigma: float = 2.0, slabs: int = 8,
     ws = torch.empty(workspace_bytes(res, 0, slabs), dtype=torch.uint8, device=dev)
     out = torch.empty((res, res, res), dtype=torch.float32, device=dev)
     _lib.check(_lib.lib().psr_slab_debug_spectral(_ctx(dev, ctx).handle, _ptr(v), res, float(sigma), int(slabs),
-                                                  _ptr(out), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream(dev)),
+                                                  _ptr(out), _ptr(ws), ws.numel(), _stream(dev)),
                "psr_slab_debug_spectral")
     return out
