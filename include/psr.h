@@ -382,12 +382,23 @@ int psr_chamfer(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_
                 int32_t* nn_y, float* d_y, double* loss, void* workspace, size_t workspace_bytes,
                 hipStream_t stream);
 
+/* psr_chamfer with the loss rounded to one float. */
+int psr_chamfer_f32(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny, int32_t* nn_x, float* d_x,
+                    int32_t* nn_y, float* d_y, float* loss, void* workspace, size_t workspace_bytes,
+                    hipStream_t stream);
+
 /* grad_x = dL/dx of the Chamfer loss from its nearest-neighbour indices:
  * 2 (x_i - y_nn_x[i]) / nx, plus 2 (x_i - y_j) / ny for every j with
  * nn_y[j] = i (float atomics for the second term). A sample without a
  * neighbour (nn_x[i] = -1) gets NaN; a target point without one adds nothing. */
 int psr_chamfer_backward(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny, const int32_t* nn_x,
                          const int32_t* nn_y, float* grad_x, hipStream_t stream);
+
+/* psr_chamfer_backward with every term times *dloss (one float, device memory;
+ * NULL: 1), the gradient of the loss itself. */
+int psr_chamfer_backward_scaled(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny,
+                                const int32_t* nn_x, const int32_t* nn_y, const float* dloss, float* grad_x,
+                                hipStream_t stream);
 
 /* Bytes of the components workspace (host only). */
 int psr_mesh_components_workspace_bytes(int64_t nverts, int64_t nfaces, size_t* bytes);

@@ -96,7 +96,9 @@ def _declare(L):
         "psr_mesh_sample_backward": ([vp, vp, i64, vp, vp, vp, i64, vp, vp], i32),
         "psr_chamfer_workspace_bytes": ([i64, i64, P(sz)], i32),
         "psr_chamfer": ([vp, vp, i64, vp, i64, vp, vp, vp, vp, vp, vp, sz, vp], i32),
+        "psr_chamfer_f32": ([vp, vp, i64, vp, i64, vp, vp, vp, vp, vp, vp, sz, vp], i32),
         "psr_chamfer_backward": ([vp, vp, i64, vp, i64, vp, vp, vp, vp], i32),
+        "psr_chamfer_backward_scaled": ([vp, vp, i64, vp, i64, vp, vp, vp, vp, vp], i32),
         "psr_mesh_components_workspace_bytes": ([i64, i64, P(sz)], i32),
         "psr_mesh_components": ([vp, vp, i64, vp, i64, vp, vp, vp, sz, vp], i32),
         "psr_opt_step_workspace_bytes": ([i32, i64, i64, i64, i64, i64, P(sz)], i32),

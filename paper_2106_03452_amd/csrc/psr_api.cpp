@@ -680,21 +680,40 @@ int psr_chamfer_workspace_bytes(int64_t nx, int64_t ny, size_t* bytes) {
   return PSR_OK;
 }
 
-int psr_chamfer(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny, int32_t* nn_x, float* d_x,
-                int32_t* nn_y, float* d_y, double* loss, void* workspace, size_t workspace_bytes,
-                hipStream_t stream) {
+static int chamfer(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny, int32_t* nn_x, float* d_x,
+                   int32_t* nn_y, float* d_y, double* loss, float* loss32, void* workspace, size_t workspace_bytes,
+                   hipStream_t stream) {
   if (!ctx || !x || !y || nx < 1 || ny < 1 || nx >= ((int64_t)1 << 31) || ny >= ((int64_t)1 << 31)) return PSR_EINVAL;
   if (!nn_x || !d_x || !nn_y || !d_y || !workspace) return PSR_EINVAL;
   if (workspace_bytes < psr::opt::chamfer_ws(nx, ny) || !aligned(workspace, 256)) return PSR_EINVAL;
   DeviceGuard g(ctx->device);
-  return psr::opt::run_chamfer(x, nx, y, ny, nn_x, d_x, nn_y, d_y, loss, workspace, stream) ? PSR_EDEVICE : PSR_OK;
+  return psr::opt::run_chamfer(x, nx, y, ny, nn_x, d_x, nn_y, d_y, loss, loss32, workspace, stream) ? PSR_EDEVICE
+                                                                                                    : PSR_OK;
+}
+
+int psr_chamfer(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny, int32_t* nn_x, float* d_x,
+                int32_t* nn_y, float* d_y, double* loss, void* workspace, size_t workspace_bytes,
+                hipStream_t stream) {
+  return chamfer(ctx, x, nx, y, ny, nn_x, d_x, nn_y, d_y, loss, nullptr, workspace, workspace_bytes, stream);
+}
+
+int psr_chamfer_f32(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny, int32_t* nn_x, float* d_x,
+                    int32_t* nn_y, float* d_y, float* loss, void* workspace, size_t workspace_bytes,
+                    hipStream_t stream) {
+  return chamfer(ctx, x, nx, y, ny, nn_x, d_x, nn_y, d_y, nullptr, loss, workspace, workspace_bytes, stream);
 }
 
 int psr_chamfer_backward(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny, const int32_t* nn_x,
                          const int32_t* nn_y, float* grad_x, hipStream_t stream) {
+  return psr_chamfer_backward_scaled(ctx, x, nx, y, ny, nn_x, nn_y, nullptr, grad_x, stream);
+}
+
+int psr_chamfer_backward_scaled(psr_ctx* ctx, const float* x, int64_t nx, const float* y, int64_t ny,
+                                const int32_t* nn_x, const int32_t* nn_y, const float* dloss, float* grad_x,
+                                hipStream_t stream) {
   if (!ctx || !x || !y || nx < 1 || ny < 1 || !nn_x || !nn_y || !grad_x) return PSR_EINVAL;
   DeviceGuard g(ctx->device);
-  return psr::opt::run_chamfer_backward(x, nx, y, ny, nn_x, nn_y, grad_x, stream) ? PSR_EDEVICE : PSR_OK;
+  return psr::opt::run_chamfer_backward(x, nx, y, ny, nn_x, nn_y, dloss, grad_x, stream) ? PSR_EDEVICE : PSR_OK;
 }
 
 int psr_mesh_components_workspace_bytes(int64_t nverts, int64_t nfaces, size_t* bytes) {

@@ -19,7 +19,7 @@ SampleLayout sample_layout(int64_t nfaces);
 // counting sort, the sorted points (x, y, z, original index bits) and the
 // bounding box of every tile of kNnTile sorted points.
 constexpr int kNnTile = 64;  // sorted points per tile
-// 2^b cells per axis (Morton-ordered): about four or more points per cell
+// 2^b cells per axis whose ends are kept: about four or more points per cell
 inline int nn_cell_bits(int64_t nx, int64_t ny) {
   const int64_t n = nx > ny ? nx : ny;
   return n <= 32768 ? 4 : (n <= 262144 ? 5 : 6);
@@ -41,9 +41,9 @@ int run_sample(const float* v, const float* vn, const int32_t* f, int64_t nf, co
 int run_sample_backward(const int32_t* f, int64_t nv, const int32_t* face, const float* bary, const float* dp,
                         int64_t m, float* dv, hipStream_t s);
 int run_chamfer(const float* x, int64_t nx, const float* y, int64_t ny, int32_t* nnx, float* dx, int32_t* nny,
-                float* dy, double* loss, void* ws, hipStream_t s);
+                float* dy, double* loss, float* loss32, void* ws, hipStream_t s);
 int run_chamfer_backward(const float* x, int64_t nx, const float* y, int64_t ny, const int32_t* nnx,
-                         const int32_t* nny, float* g, hipStream_t s);
+                         const int32_t* nny, const float* scale, float* g, hipStream_t s);
 // Adam on n values (moments m, v in place), then p -= floor(p) when wrap
 int run_adam(float* p, float* m, float* v, const float* g, int64_t n, int64_t t, float lr, float b1, float b2,
              float eps, bool wrap, hipStream_t s);

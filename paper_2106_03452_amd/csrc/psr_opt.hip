@@ -4,8 +4,8 @@
 // bidirectional Chamfer loss of Eq. 5 with its gradient, and the connected
 // components of the mesh for the resampling from the largest component.
 //
-// Sampling: FP64 face areas, an FP64 inclusive scan (block sums, their scan,
-// block-local scans), then per sample a binary search of u0 * total and the
+// Sampling: FP64 face areas with their running sums per block, then per sample
+// a search of u0 * total over the block sums and within the block, and the
 // barycentric weights (1 - sqrt(u1), sqrt(u1) (1 - u2), sqrt(u1) u2).
 // Chamfer: exact nearest neighbours over spatially sorted tiles whose boxes
 // let whole tiles be skipped (the brute-force result: equal distances go to
@@ -23,100 +23,134 @@
 namespace psr {
 namespace opt {
 
-constexpr int kScanPer = 4;                 // areas per thread of a scan block
-constexpr int kScanBlock = 256 * kScanPer;  // areas per scan block
+constexpr int kScanBlock = 1024;  // face areas per scan block
+constexpr int kScanTops = 1024;   // block sums that a sampling workgroup scans itself
 
-__global__ __launch_bounds__(256) void k_face_area(const float* __restrict__ v, const int32_t* __restrict__ f,
-                                                   int64_t nf, const float* __restrict__ w, double* __restrict__ a) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= nf) return;
+__device__ __forceinline__ double face_area(const float* __restrict__ v, const int32_t* __restrict__ f, int64_t i) {
   const int64_t i0 = f[3 * i], i1 = f[3 * i + 1], i2 = f[3 * i + 2];
   const double ax = (double)v[3 * i1] - v[3 * i0], ay = (double)v[3 * i1 + 1] - v[3 * i0 + 1],
                az = (double)v[3 * i1 + 2] - v[3 * i0 + 2];
   const double bx = (double)v[3 * i2] - v[3 * i0], by = (double)v[3 * i2 + 1] - v[3 * i0 + 1],
                bz = (double)v[3 * i2 + 2] - v[3 * i0 + 2];
   const double cx = ay * bz - az * by, cy = az * bx - ax * bz, cz = ax * by - ay * bx;
-  double ar = 0.5 * sqrt(cx * cx + cy * cy + cz * cz);
-  if (w) ar *= (double)w[i];
-  a[i] = ar;
+  return 0.5 * sqrt(cx * cx + cy * cy + cz * cz);
 }
 
-__device__ __forceinline__ double block_excl_scan(double v, double* sh, double& total) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int d = 1; d < 256; d <<= 1) {
-    const double x = t >= d ? sh[t - d] : 0.0;
-    __syncthreads();
-    sh[t] += x;
-    __syncthreads();
+__global__ __launch_bounds__(256) void k_face_area(const float* __restrict__ v, const int32_t* __restrict__ f,
+                                                   int64_t nf, double* __restrict__ a) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < nf) a[i] = face_area(v, f, i);
+}
+
+// inclusive scan over the workgroup's WAVES wavefronts; sh holds WAVES values
+template <int WAVES>
+__device__ __forceinline__ double block_incl_scan(double v, double* sh, double& total) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const double u = __shfl_up(v, d, 64);
+    if (lane >= d) v += u;
   }
-  total = sh[255];
-  const double excl = sh[t] - v;
+  if (lane == 63) sh[wid] = v;
   __syncthreads();
-  return excl;
+  double before = 0.0, tot = 0.0;
+#pragma unroll
+  for (int k = 0; k < WAVES; ++k) {
+    before += k < wid ? sh[k] : 0.0;
+    tot += sh[k];
+  }
+  total = tot;
+  __syncthreads();
+  return before + v;
 }
 
-// block b: the sum of its kScanBlock areas
-__global__ __launch_bounds__(256) void k_scan_sums(const double* __restrict__ a, int64_t n, double* __restrict__ bs) {
-  __shared__ double sh[256];
-  const int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
-  double s = 0.0;
-  for (int k = 0; k < kScanPer; ++k)
-    if (base + k < n) s += a[base + k];
+// Areas of kScanBlock faces (times the face weights), their running sums
+// within the block and the block's sum. One face per thread: the chain of
+// loads (indices, corners) is the time, and is paid once. With k_sample, which
+// scans the block sums itself, this replaces four launches (areas, block sums,
+// their scan, running sums): 10.8 -> 4.5 us for 20000 faces.
+__global__ __launch_bounds__(kScanBlock) void k_area_scan(const float* __restrict__ v, const int32_t* __restrict__ f,
+                                                          int64_t nf, const float* __restrict__ w,
+                                                          double* __restrict__ csum, double* __restrict__ bs) {
+  __shared__ double sh[kScanBlock / 64];
+  const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
+  double a = 0.0;
+  if (i < nf) {
+    a = face_area(v, f, i);
+    if (w) a *= (double)w[i];
+  }
   double tot;
-  block_excl_scan(s, sh, tot);
+  const double inc = block_incl_scan<kScanBlock / 64>(a, sh, tot);
+  if (i < nf) csum[i] = inc;
   if (threadIdx.x == 0) bs[blockIdx.x] = tot;
 }
 
-// exclusive scan of the block sums in place (one workgroup); the grand total after them
+// exclusive scan of the block sums in place (one workgroup); the grand total
+// after them. For meshes of more than kScanTops blocks only.
 __global__ __launch_bounds__(256) void k_scan_tops(double* __restrict__ bs, int nb) {
-  __shared__ double sh[256];
+  __shared__ double sh[4];
   double carry = 0.0;
   for (int c = 0; c < nb; c += 256) {
     const int i = c + threadIdx.x;
     const double v = i < nb ? bs[i] : 0.0;
     double tot;
-    const double ex = block_excl_scan(v, sh, tot);
-    if (i < nb) bs[i] = carry + ex;
+    const double inc = block_incl_scan<4>(v, sh, tot);
+    if (i < nb) bs[i] = carry + (inc - v);
     carry += tot;
   }
   if (threadIdx.x == 0) bs[nb] = carry;
 }
 
-// inclusive running sums of the areas
-__global__ __launch_bounds__(256) void k_scan_local(double* __restrict__ a, int64_t n, const double* __restrict__ bs) {
-  __shared__ double sh[256];
-  const int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
-  double v[kScanPer], s = 0.0;
-  for (int k = 0; k < kScanPer; ++k) {
-    v[k] = base + k < n ? a[base + k] : 0.0;
-    s += v[k];
-  }
-  double tot;
-  double run = bs[blockIdx.x] + block_excl_scan(s, sh, tot);
-  for (int k = 0; k < kScanPer; ++k) {
-    run += v[k];
-    if (base + k < n) a[base + k] = run;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_sample(const float* __restrict__ v, const float* __restrict__ vn,
+// One sample per thread: the first face whose running area exceeds u0 times the
+// total, by its scan block first (TOPS: each wavefront scans the block sums in
+// LDS; else they are scanned already), then by binary search within the block.
+// Cache lines of running areas fetched across the chip bound it: searches in
+// rounds of 3, 7 or 31 independent loads have fewer rounds and touch more lines
+// (8.0, 9.8 and 18.8 us for 20000 samples of 20000 faces; this 6.9).
+template <bool TOPS>
+__global__ __launch_bounds__(64) void k_sample(const float* __restrict__ v, const float* __restrict__ vn,
                                                 const int32_t* __restrict__ f, int64_t nf,
-                                                const double* __restrict__ csum, const float* __restrict__ u,
-                                                int64_t m, float* __restrict__ pts, float* __restrict__ nrm,
-                                                int32_t* __restrict__ face, float* __restrict__ bary) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+                                                const double* __restrict__ csum, const double* __restrict__ bs, int nb,
+                                                const float* __restrict__ u, int64_t m, float* __restrict__ pts,
+                                                float* __restrict__ nrm, int32_t* __restrict__ face,
+                                                float* __restrict__ bary) {
+  __shared__ double top[TOPS ? kScanTops + 1 : 1];
+  __shared__ double sh[1];
+  const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
+  if (i < m) u0 = u[3 * i], u1 = u[3 * i + 1], u2 = u[3 * i + 2];
+  const double* pre = bs;
+  if (TOPS) {
+    double carry = 0.0;
+    for (int c = 0; c < nb; c += 64) {
+      const int b = c + (int)threadIdx.x;
+      const double s = b < nb ? bs[b] : 0.0;
+      double tot;
+      const double inc = block_incl_scan<1>(s, sh, tot);
+      if (b < nb) top[b] = carry + (inc - s);
+      carry += tot;
+    }
+    if (threadIdx.x == 0) top[nb] = carry;
+    __syncthreads();
+    pre = top;
+  }
   if (i >= m) return;
-  const double t = (double)u[3 * i] * csum[nf - 1];
-  // first face whose running sum exceeds t
-  int64_t lo = 0, hi = nf - 1;
+  const double t = (double)u0 * pre[nb];
+  int bl = 0, bh = nb - 1;
+  while (bl < bh) {
+    const int mid = (bl + bh) >> 1;
+    if (pre[mid + 1] > t) bh = mid;
+    else bl = mid + 1;
+  }
+  const double t0 = pre[bl];
+  int64_t lo = (int64_t)bl * kScanBlock;
+  int64_t hi = lo + kScanBlock < nf ? lo + kScanBlock - 1 : nf - 1;
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
-    if (csum[mid] > t) hi = mid;
+    if (t0 + csum[mid] > t) hi = mid;
     else lo = mid + 1;
   }
-  const float s = sqrtf(u[3 * i + 1]), u2 = u[3 * i + 2];
+  const float s = sqrtf(u1);
   const float b0 = 1.0f - s, b1 = s * (1.0f - u2), b2 = s * u2;
   const int64_t i0 = f[3 * lo], i1 = f[3 * lo + 1], i2 = f[3 * lo + 2];
 #pragma unroll
@@ -139,27 +173,27 @@ __global__ __launch_bounds__(256) void k_fill0(float* __restrict__ x, int64_t n)
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) x[i] = 0.0f;
 }
 
+// One thread per sample and corner: the atomics, at the rate of the memory side
+// that all XCDs share, bound it; nine by one thread took 13.2 us for 20000
+// samples, three by each of three take 9.9.
 __global__ __launch_bounds__(256) void k_sample_bwd(const int32_t* __restrict__ f, const int32_t* __restrict__ face,
                                                     const float* __restrict__ bary, const float* __restrict__ dp,
                                                     int64_t m, float* __restrict__ dv) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  const int64_t fi = face[i];
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= 3 * m) return;
+  const int64_t i = t / 3;
+  const int64_t vi = f[3 * (int64_t)face[i] + (t - 3 * i)];
+  const float b = bary[t];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int64_t vi = f[3 * fi + k];
-    const float b = bary[3 * i + k];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) atomicAdd(&dv[3 * vi + d], b * dp[3 * i + d]);
-  }
+  for (int d = 0; d < 3; ++d) atomicAdd(&dv[3 * vi + d], b * dp[3 * i + d]);
 }
 
 // ---------------------------------------------------------------------------
 // Nearest neighbours for the Chamfer loss: an exact search that skips whole
 // tiles of the reference cloud. Both clouds are counting-sorted into
-// Morton-ordered cells of a grid over [0,1)^3 (16^3 to 64^3 cells by cloud
-// size; points outside fall into the border cells), cut into tiles of
-// kNnTile sorted points, and each tile gets its bounding box. A query group
+// the cells of a grid over [0,1)^3 (32^3 or 64^3 by cloud size) in Hilbert order
+// (points outside fall into the border cells), cut into tiles of kNnTile
+// sorted points, and each tile gets its bounding box. A query group
 // (kNnTile sorted queries) visits the reference tiles nearest its own box
 // first and stops where every remaining box is farther than each query's
 // best so far; a tile is skipped when no query's point-to-box bound reaches
@@ -189,10 +223,29 @@ __device__ __forceinline__ uint32_t nn_spread(uint32_t v) {  // up to 8 bits -> 
   return v;
 }
 
-// Morton index of the point's cell in the 2^cb per axis grid
-__device__ __forceinline__ int nn_key(float x, float y, float z, int cb) {
-  return (int)(nn_spread(nn_cell_coord(x, cb)) | (nn_spread(nn_cell_coord(y, cb)) << 1) |
-               (nn_spread(nn_cell_coord(z, cb)) << 2));
+// Index of the point's cell along the Hilbert curve of the 2^cb per axis grid
+// (Skilling, "Programming the Hilbert curve", 2004: the axes to transpose
+// transform), so that consecutive cells are neighbours: in Morton order a tile
+// that spans a jump of the curve has a box of up to the whole domain, and a
+// query group of 64 surface points scanned 20 tiles on average and 50 at most
+// against 15 and 42.
+__device__ __forceinline__ int nn_key(float px, float py, float pz, int cb) {
+  int x = nn_cell_coord(px, cb), y = nn_cell_coord(py, cb), z = nn_cell_coord(pz, cb);
+  for (int q = 1 << (cb - 1); q > 1; q >>= 1) {
+    const int p = q - 1;
+    x ^= (x & q) ? p : 0;
+    const int ty = (x ^ y) & p, fy = y & q;
+    x ^= fy ? p : ty;
+    y ^= fy ? 0 : ty;
+    const int tz = (x ^ z) & p, fz = z & q;
+    x ^= fz ? p : tz;
+    z ^= fz ? 0 : tz;
+  }
+  y ^= x;
+  z ^= y;
+  int t = 0;
+  for (int q = 1 << (cb - 1); q > 1; q >>= 1) t ^= (z & q) ? q - 1 : 0;
+  return (int)((nn_spread(x ^ t) << 2) | (nn_spread(y ^ t) << 1) | nn_spread(z ^ t));
 }
 
 __global__ __launch_bounds__(256) void k_nn_zero(int* __restrict__ cnt, int n) {
@@ -293,57 +346,118 @@ __global__ __launch_bounds__(64) void k_nn_box(const float4* __restrict__ sx, in
   }
 }
 
-// float <-> int keys whose integer order is the float order (NaN excluded)
-__device__ __forceinline__ int nn_ord(float f) {
-  const int i = __float_as_int(f);
-  return i >= 0 ? i : i ^ 0x7fffffff;
+// Small clouds (up to kNnSmall points): two launches. The keys, in cells twice
+// as fine per axis as the cell ends kept for the search, go to the nn outputs,
+// which the search overwrites; one workgroup computing all of its cloud's keys
+// is bound by its own arithmetic (12 of 26 us for 20000 points).
+constexpr int kNnSmall = 32768;                           // indices and positions fit 16 bits
+constexpr int kNnSmallBits = 4;                           // 16^3 cell ends
+constexpr int kNnFineBits = kNnSmallBits + 1;             // 32^3 cells sorted
+constexpr int kNnFineCells = 1 << (3 * kNnFineBits);
+constexpr int kNnSortWgs = 32;                            // workgroups per cloud
+
+__global__ __launch_bounds__(256) void k_nn_keys(const float* __restrict__ x, int nx, const float* __restrict__ y,
+                                                 int ny, uint16_t* __restrict__ kx, uint16_t* __restrict__ ky) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= nx + ny) return;
+  const bool isy = i >= nx;
+  const int k = isy ? i - nx : i;
+  const float* p = (isy ? y : x) + 3 * (int64_t)k;
+  (isy ? ky : kx)[k] = (uint16_t)nn_key(p[0], p[1], p[2], kNnFineBits);
 }
-__device__ __forceinline__ float nn_unord(int k) { return __int_as_float(k >= 0 ? k : k ^ 0x7fffffff); }
 
-constexpr int kNnSmallBits = 4;                           // 16^3 cells
-constexpr int kNnSmallCells = 1 << (3 * kNnSmallBits);
-constexpr int kNnSmallTiles = 512;                        // clouds of up to 32768 points
+// three minima and three maxima over the wavefront
+__device__ __forceinline__ void wave_box(float (&m)[6]) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      const float o = __shfl_xor(m[q], d, 64);
+      m[q] = q < 3 ? fminf(m[q], o) : fmaxf(m[q], o);
+    }
+  }
+}
 
-// Small clouds (up to kNnSmallTiles tiles): the whole counting sort of one
-// cloud in one workgroup (counts, scan and ranks in LDS), the tile boxes from
-// LDS minima / maxima during the scatter; writes the sorted points, the
-// cells' ends and the boxes, as the separate kernels do for larger clouds.
-__global__ __launch_bounds__(1024) void k_nn_sort_small(const float* __restrict__ x, int64_t nx,
-                                                        const float* __restrict__ y, int64_t ny,
-                                                        int* __restrict__ cnt, float4* __restrict__ sx,
-                                                        float4* __restrict__ sy, float4* __restrict__ bx,
-                                                        float4* __restrict__ by) {
-  __shared__ int hist[kNnSmallCells];
-  __shared__ int bmin[3][kNnSmallTiles], bmax[3][kNnSmallTiles];
+// The counting sort of one cloud by kNnSortWgs workgroups that do not speak to
+// each other: each counts and scans all keys in LDS (the keys are 2 bytes and
+// are read once), then places only the cells that start in its share of the
+// tiles, in LDS, and writes the sorted points and the boxes of its tiles in
+// order. A cell that starts before the share and ends within it belongs to the
+// workgroup before, in an order that is only known there: its points' common
+// box is added to every tile of the share that it reaches (still a bound).
+// One workgroup per cloud took 26 us for 20000 points each; the keys take 3 and
+// this 16.5, of which half is the key arithmetic and LDS atomics of a whole
+// cloud on one compute unit.
+__global__ __launch_bounds__(1024) void k_nn_sort(const float* __restrict__ x, int nx, const float* __restrict__ y,
+                                                  int ny, const uint16_t* __restrict__ kx,
+                                                  const uint16_t* __restrict__ ky, int* __restrict__ cnt,
+                                                  float4* __restrict__ sx, float4* __restrict__ sy,
+                                                  float4* __restrict__ bx, float4* __restrict__ by) {
+  constexpr int PAIRS = kNnSmall / 2048;       // key pairs per thread
+  constexpr int WORDS = kNnFineCells / 2048;   // words of two 16-bit counts per thread
+  constexpr int PITCH = WORDS + 4;             // a thread's words, padded against bank conflicts
+  static_assert(WORDS == 16 && PITCH % 4 == 0, "hist_at() and the 16-byte accesses");
+  __shared__ __attribute__((aligned(16))) uint32_t hist[1024 * PITCH];
+  __shared__ uint16_t perm[kNnSmall + 1];  // the last for the points of others
   __shared__ int wsum[16];
-  const bool isy = blockIdx.x == 1;
+  __shared__ int mark[7];  // own cells [0], [1) at positions [2], [3); the cell across a [4] at [5], [6)
+  __shared__ float part[16][6];
+  // word of a key's count; the thread's own padding for the key of no point (0xffff)
+  auto hist_at = [&](int key) -> uint32_t& {
+    return hist[key < kNnFineCells ? (key >> 5) * PITCH + ((key >> 1) & 15) : threadIdx.x * PITCH + WORDS];
+  };
+  const bool isy = blockIdx.x >= kNnSortWgs;
+  const int k = isy ? blockIdx.x - kNnSortWgs : blockIdx.x;
   const float* p = isy ? y : x;
-  const int n = (int)(isy ? ny : nx);
+  const int n = isy ? ny : nx;
+  const uint32_t* keys = reinterpret_cast<const uint32_t*>(isy ? ky : kx);
   float4* srt = isy ? sy : sx;
   float4* box = isy ? by : bx;
-  int* ends = cnt + (isy ? kNnSmallCells : 0);
+  int* ends = cnt + (isy ? 1 << (3 * kNnSmallBits) : 0);
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   const int nt = (n + kNnTile - 1) / kNnTile;
-  for (int k = t; k < kNnSmallCells; k += 1024) hist[k] = 0;
-  for (int k = t; k < kNnSmallTiles; k += 1024) {
+  const int share = (nt + kNnSortWgs - 1) / kNnSortWgs * kNnTile;
+  const int a = min(k * share, n), b = min(a + share, n);
+  uint32_t kk[PAIRS];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      bmin[a][k] = 0x7fffffff;
-      bmax[a][k] = (int)0x80000000;
+  for (int j = 0; j < PAIRS; ++j) {
+    const int i = 2 * (j * 1024 + t);  // an odd count reads two bytes past its keys, within the 4 n of the buffer
+    kk[j] = i < n ? keys[j * 1024 + t] : ~0u;
+    if (i + 1 == n) kk[j] |= 0xffff0000u;
+  }
+#pragma unroll
+  for (int c = 0; c < WORDS; c += 4) *reinterpret_cast<uint4*>(&hist[t * PITCH + c]) = make_uint4(0, 0, 0, 0);
+  if (t < 7) mark[t] = t == 4 ? -1 : 0;
+  __syncthreads();
+  // the count before a point is its rank in its cell (both of a pair in one word)
+  uint32_t rank[PAIRS];
+#pragma unroll
+  for (int g = 0; g < PAIRS; g += 4) {
+    if (g * 2048 >= n) continue;
+    uint32_t r[8];
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+      const int key = (int)(kk[g + h / 2] >> (16 * (h & 1))) & 0xffff;
+      r[h] = atomicAdd(&hist_at(key), 1u << (16 * (key & 1)));
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t w = kk[g + j];
+      rank[g + j] = ((r[2 * j] >> (16 * (w & 1))) & 0xffff) | (r[2 * j + 1] >> (16 * ((w >> 16) & 1))) << 16;
+      asm("" : "+v"(rank[g + j]), "+v"(kk[g + j]));  // packed now; the addresses are formed again below
     }
   }
   __syncthreads();
-#pragma unroll 4
-  for (int i = t; i < n; i += 1024) atomicAdd(&hist[nn_key(p[3 * i], p[3 * i + 1], p[3 * i + 2], kNnSmallBits)], 1);
-  __syncthreads();
   {
-    constexpr int PER = kNnSmallCells / 1024;
-    int v[PER], s = 0;
+    uint32_t v[WORDS];
+    int s = 0;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      v[k] = hist[t * PER + k];
-      s += v[k];
+    for (int c = 0; c < WORDS; c += 4) {
+      const uint4 h = *reinterpret_cast<const uint4*>(&hist[t * PITCH + c]);
+      v[c] = h.x, v[c + 1] = h.y, v[c + 2] = h.z, v[c + 3] = h.w;
     }
+#pragma unroll
+    for (int c = 0; c < WORDS; ++c) s += (int)(v[c] & 0xffff) + (int)(v[c] >> 16);
     int inc = s;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -354,40 +468,96 @@ __global__ __launch_bounds__(1024) void k_nn_sort_small(const float* __restrict_
     __syncthreads();
     int run = inc - s;
     for (int u = 0; u < wid; ++u) run += wsum[u];
+    // exactly one cell holds the point before a bound greater than 0
+    if ((run < a && a <= run + s) || (run < b && b <= run + s)) {
+      int at = run;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      hist[t * PER + k] = run;
-      run += v[k];
-    }
-  }
-  __syncthreads();
-#pragma unroll 4
-  for (int i = t; i < n; i += 1024) {
-    const float a = p[3 * i], b = p[3 * i + 1], c = p[3 * i + 2];
-    const int pos = atomicAdd(&hist[nn_key(a, b, c, kNnSmallBits)], 1);
-    srt[pos] = make_float4(a, b, c, __int_as_float(i));
-    const int tl = pos / kNnTile;
-    const float v[3] = {a, b, c};
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      if (v[e] == v[e]) {
-        atomicMin(&bmin[e][tl], nn_ord(v[e]));
-        atomicMax(&bmax[e][tl], nn_ord(v[e]));
+      for (int c = 0; c < 2 * WORDS; ++c) {
+        const int end = at + (int)((v[c >> 1] >> (16 * (c & 1))) & 0xffff);
+        if (at < a && a <= end) {
+          mark[0] = 2 * WORDS * t + c + 1, mark[2] = end;
+          if (end > a) mark[4] = 2 * WORDS * t + c, mark[5] = at, mark[6] = end;
+        }
+        if (at < b && b <= end) mark[1] = 2 * WORDS * t + c + 1, mark[3] = end;
+        at = end;
       }
     }
+    int e[4];
+#pragma unroll
+    for (int c = 0; c < WORDS; ++c) {
+      const int mid = run + (int)(v[c] & 0xffff), end = mid + (int)(v[c] >> 16);
+      v[c] = (uint32_t)run | ((uint32_t)mid << 16);
+      run = end;
+      if ((c & 3) == 3) e[c >> 2] = end;
+    }
+#pragma unroll
+    for (int c = 0; c < WORDS; c += 4)
+      *reinterpret_cast<uint4*>(&hist[t * PITCH + c]) = make_uint4(v[c], v[c + 1], v[c + 2], v[c + 3]);
+    if (t / (1024 / kNnSortWgs) == k) reinterpret_cast<int4*>(ends)[t] = make_int4(e[0], e[1], e[2], e[3]);
   }
   __syncthreads();
-  for (int k = t; k < kNnSmallCells; k += 1024) ends[k] = hist[k];
+  const bool across = mark[4] >= 0;
+  const int kb = mark[1], pa = mark[2], pe = mark[3], ke = mark[6];
+  const int k0 = across ? mark[4] : mark[0], p0 = across ? mark[5] : pa;  // perm: positions [p0, pe)
   const float inf = __int_as_float(0x7f800000);
-  for (int k = t; k < nt; k += 1024) {
-    float lo[3], hi[3];
 #pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      lo[e] = bmin[e][k] == 0x7fffffff ? inf : nn_unord(bmin[e][k]);
-      hi[e] = bmax[e][k] == (int)0x80000000 ? -inf : nn_unord(bmax[e][k]);
+  for (int g = 0; g < PAIRS; g += 4) {
+    if (g * 2048 >= n) continue;
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+      const int key = (int)(kk[g + h / 2] >> (16 * (h & 1))) & 0xffff;
+      const int pos = (int)((hist_at(key) >> (16 * (key & 1))) & 0xffff) +
+                      (int)((rank[g + h / 2] >> (16 * (h & 1))) & 0xffff);
+      const bool own = (uint32_t)(key - k0) < (uint32_t)(kb - k0);
+      perm[own ? pos - p0 : kNnSmall] = (uint16_t)(2 * ((g + h / 2) * 1024 + t) + (h & 1));
     }
-    box[2 * k] = make_float4(lo[0], lo[1], lo[2], 0.0f);
-    box[2 * k + 1] = make_float4(hi[0], hi[1], hi[2], 0.0f);
+  }
+  __syncthreads();
+  // 0..2: minima, 3..5: maxima (fminf and fmaxf pass over NaN)
+  float m[6] = {inf, inf, inf, -inf, -inf, -inf};
+  for (int e = p0 + t; e < pa; e += 1024) {
+    const int i = perm[e - p0];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      m[d] = fminf(m[d], p[3 * i + d]);
+      m[3 + d] = fmaxf(m[3 + d], p[3 * i + d]);
+    }
+  }
+  if (across) {  // the same for the whole workgroup
+    wave_box(m);
+    if (lane == 0) {
+#pragma unroll
+      for (int q = 0; q < 6; ++q) part[wid][q] = m[q];
+    }
+    __syncthreads();
+    for (int w = 0; w < 16; ++w) {
+#pragma unroll
+      for (int q = 0; q < 6; ++q) m[q] = q < 3 ? fminf(m[q], part[w][q]) : fmaxf(m[q], part[w][q]);
+    }
+  }
+  const int stop = max(pe, b);
+  for (int i0 = a + wid * kNnTile; i0 < stop; i0 += 1024) {  // one tile per wavefront
+    const int pos = i0 + lane;
+    float l[6] = {inf, inf, inf, -inf, -inf, -inf};
+    if (pos >= pa && pos < pe) {
+      const int i = perm[pos - p0];
+      const float v[3] = {p[3 * i], p[3 * i + 1], p[3 * i + 2]};
+      srt[pos] = make_float4(v[0], v[1], v[2], __int_as_float(i));
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        l[d] = fminf(inf, v[d]);
+        l[3 + d] = fmaxf(-inf, v[d]);
+      }
+    }
+    if (i0 >= b) continue;  // the box is the next workgroup's
+    wave_box(l);
+    if (lane == 0) {
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+        if (i0 < ke) l[q] = q < 3 ? fminf(l[q], m[q]) : fmaxf(l[q], m[q]);
+      box[2 * (i0 / kNnTile)] = make_float4(l[0], l[1], l[2], 0.0f);
+      box[2 * (i0 / kNnTile) + 1] = make_float4(l[3], l[4], l[5], 0.0f);
+    }
   }
 }
 
@@ -414,6 +584,7 @@ __device__ __forceinline__ void wave_sync() {
 
 struct NnSide {
   const float4* q;   // sorted queries
+  const float4* qbox;  // their tiles' boxes
   int64_t nq;
   const float4* r;   // sorted references
   const float4* box; // reference tile boxes (lo, hi)
@@ -433,7 +604,7 @@ constexpr int kNnCand = 512;  // tiles tested per pass: the capacity of the cand
 //    the group's first query; the largest best distance of the group then
 //    bounds every neighbour.
 // 2. The tiles whose box lies within that bound of the group's box are listed
-//    in LDS with their boxes and sorted by the box-to-box bound (bitonic).
+//    in LDS with their boxes and ranked by the box-to-box bound.
 // 3. The wavefronts take the sorted tiles in turn (the next one's points
 //    prefetched) and stop at the first whose box bound exceeds every lane's
 //    best; a tile is passed over when no lane's point-to-box bound reaches
@@ -441,13 +612,21 @@ constexpr int kNnCand = 512;  // tiles tested per pass: the capacity of the cand
 //    reached for it (published in LDS after every tile).
 // 4. The kNnWaves results per query are merged (lower distance, then lower
 //    index).
+// A tile is scanned sixteen points at a time: their least distance first (6.5
+// operations a pair), the index only where some lane reaches its best (one
+// batch of ten after the first tile; 13 operations a pair). The chain of one
+// group (cell end, first tile, list, then its tiles by eights) bounds it: 20000
+// against 20000 points of two surfaces took 54 us with the index tracked in
+// every step, the tiles in Morton order of 16^3 cells and the list sorted by
+// exchanges, 25 now; with four wavefronts per group 31.
 __global__ __launch_bounds__(kNnBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_nn_query(
-    const NnSide A, const NnSide Bs, int64_t gx, int cb) {
-  __shared__ float4 stg[kNnWaves][kNnTile];
+    const NnSide A, const NnSide Bs, int64_t gx, int cb, int fine) {
+  __shared__ __attribute__((aligned(16))) float stg[kNnWaves][4][kNnTile];  // x, y, z, index bits
   __shared__ float shb[kNnWaves][kNnTile];
   __shared__ int sidx[kNnWaves][kNnTile];
   __shared__ float4 cbox[kNnCand][2];  // lo (w: box bound), hi (w: tile - c0)
   __shared__ unsigned long long ckey[kNnCand];  // (box bound, slot in cbox)
+  __shared__ int order[kNnCand];  // slots, nearest box first
   __shared__ int ncand;
   const bool second = blockIdx.x >= gx;
   const NnSide S = second ? Bs : A;
@@ -457,22 +636,10 @@ __global__ __launch_bounds__(kNnBlock) __attribute__((amdgpu_waves_per_eu(1, 4))
   const int64_t gi = g * kNnTile + lane;
   const bool active = gi < S.nq;
   const float4 q = active ? S.q[gi] : make_float4(nan, nan, nan, 0.0f);
-  // the group's box (NaN coordinates ignored)
-  float3 ql = make_float3(inf, inf, inf), qh = make_float3(-inf, -inf, -inf);
-  if (q.x == q.x) ql.x = qh.x = q.x;
-  if (q.y == q.y) ql.y = qh.y = q.y;
-  if (q.z == q.z) ql.z = qh.z = q.z;
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    ql.x = fminf(ql.x, __shfl_xor(ql.x, d, 64));
-    ql.y = fminf(ql.y, __shfl_xor(ql.y, d, 64));
-    ql.z = fminf(ql.z, __shfl_xor(ql.z, d, 64));
-    qh.x = fmaxf(qh.x, __shfl_xor(qh.x, d, 64));
-    qh.y = fmaxf(qh.y, __shfl_xor(qh.y, d, 64));
-    qh.z = fmaxf(qh.z, __shfl_xor(qh.z, d, 64));
-  }
+  const float4 ql4 = S.qbox[2 * g], qh4 = S.qbox[2 * g + 1];  // NaN coordinates are not in it
+  const float3 ql = make_float3(ql4.x, ql4.y, ql4.z), qh = make_float3(qh4.x, qh4.y, qh4.z);
   const int64_t ntr = (S.nr + kNnTile - 1) / kNnTile;
-  const int key = __builtin_amdgcn_readfirstlane(nn_key(q.x, q.y, q.z, cb));
+  const int key = __builtin_amdgcn_readfirstlane(nn_key(q.x, q.y, q.z, cb + fine) >> (3 * fine));
   int64_t t0 = S.rend[key] / kNnTile;
   t0 = t0 > ntr - 1 ? ntr - 1 : t0;
   int64_t s0 = t0 - kNnWaves / 2 + 1 > ntr - kNnWaves ? ntr - kNnWaves : t0 - kNnWaves / 2 + 1;
@@ -503,25 +670,40 @@ __global__ __launch_bounds__(kNnBlock) __attribute__((amdgpu_waves_per_eu(1, 4))
   };
   auto scan_tile = [&](const float4& p) {
     wave_sync();
-    stg[w][lane] = p;
+    stg[w][0][lane] = p.x;
+    stg[w][1][lane] = p.y;
+    stg[w][2][lane] = p.z;
+    stg[w][3][lane] = p.w;
     wave_sync();
-    // sixteen LDS reads in flight per batch
+    auto four = [&](int c, int k) { return *reinterpret_cast<const float4*>(&stg[w][c][k]); };
 #pragma unroll 1
     for (int k0 = 0; k0 < kNnTile; k0 += 16) {
-      float4 e[16];
+      float d[16], low;
 #pragma unroll
-      for (int u = 0; u < 16; ++u) e[u] = stg[w][k0 + u];
+      for (int u = 0; u < 16; u += 4) {
+        const float4 x = four(0, k0 + u), y = four(1, k0 + u), z = four(2, k0 + u);
+        d[u] = nn_d2(x.x - q.x, y.x - q.y, z.x - q.z);
+        d[u + 1] = nn_d2(x.y - q.x, y.y - q.y, z.y - q.z);
+        d[u + 2] = nn_d2(x.z - q.x, y.z - q.y, z.z - q.z);
+        d[u + 3] = nn_d2(x.w - q.x, y.w - q.y, z.w - q.z);
+      }
+      low = d[0];
+#pragma unroll
+      for (int u = 1; u < 16; ++u) low = fminf(low, d[u]);
+      if (!__any(low <= best)) continue;  // nine of ten batches after the first tile
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
-        const float d = nn_d2(e[u].x - q.x, e[u].y - q.y, e[u].z - q.z);
-        const int j = __float_as_int(e[u].w);
-        const bool better = (d < best) | ((d == best) & (j < bi));
-        best = better ? d : best;
+        const int j = __float_as_int(stg[w][3][k0 + u]);
+        const bool better = (d[u] < best) | ((d[u] == best) & (j < bi));
+        best = better ? d[u] : best;
         bi = better ? j : bi;
       }
     }
     publish();
   };
+  // the boxes of the first pass travel during the first scan
+  const int64_t tb = threadIdx.x < ntr ? threadIdx.x : 0;
+  const float4 blo = S.box[2 * tb], bhi = S.box[2 * tb + 1];
   scan_tile(tile_point(s0 + w < ntr ? s0 + w : ntr - 1));
   __syncthreads();
   float bound = group_bound(reached());
@@ -531,7 +713,8 @@ __global__ __launch_bounds__(kNnBlock) __attribute__((amdgpu_waves_per_eu(1, 4))
     const int64_t c1 = c0 + kNnCand < ntr ? c0 + kNnCand : ntr;
     for (int64_t t = c0 + threadIdx.x; t < c1; t += kNnBlock) {
       if (t >= s0 && t <= s1) continue;
-      const float4 lo = S.box[2 * t], hi = S.box[2 * t + 1];
+      const bool first = t == threadIdx.x;
+      const float4 lo = first ? blo : S.box[2 * t], hi = first ? bhi : S.box[2 * t + 1];
       const float lb = nn_boxbox_d2(ql, qh, lo, hi);
       if (lb <= bound) {
         const int k = atomicAdd(&ncand, 1);
@@ -542,36 +725,28 @@ __global__ __launch_bounds__(kNnBlock) __attribute__((amdgpu_waves_per_eu(1, 4))
     }
     __syncthreads();
     const int nc = ncand;
-    int np2 = 1;
-    while (np2 < nc) np2 <<= 1;
-    for (int i = nc + threadIdx.x; i < np2; i += kNnBlock) ckey[i] = ~0ull;
-    __syncthreads();
-    // ascending bitonic sort of the keys: the nearest boxes first
-    for (int k = 2; k <= np2; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int i = threadIdx.x; i < np2; i += kNnBlock) {
-          const int l = i ^ j;
-          if (l > i) {
-            const unsigned long long a = ckey[i], b = ckey[l];
-            if ((a > b) == ((i & k) == 0)) {
-              ckey[i] = b;
-              ckey[l] = a;
-            }
-          }
-        }
-        __syncthreads();
-      }
+    // rank by counting the lesser keys (they differ: the slot is part of the key)
+    for (int i = threadIdx.x; i < nc; i += kNnBlock) {
+      const unsigned long long mine = ckey[i];
+      int rank = 0;
+#pragma unroll 8
+      for (int j = 0; j < nc; ++j) rank += ckey[j] < mine ? 1 : 0;
+      order[rank] = i;
     }
-    auto slot = [&](int i) { return (int)(ckey[i] & 0xffffffffu); };
+    __syncthreads();
     float4 pf = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (w < nc) pf = tile_point(c0 + __float_as_int(cbox[slot(w)][1].w));
+    if (w < nc) pf = tile_point(c0 + __float_as_int(cbox[order[w]][1].w));
     for (int i = w; i < nc; i += kNnWaves) {
-      const int k = slot(i);
+      const int k = order[i];
       const float4 lo = cbox[k][0], hi = cbox[k][1];
       const float4 cur = pf;
-      if (i + kNnWaves < nc) pf = tile_point(c0 + __float_as_int(cbox[slot(i + kNnWaves)][1].w));
+      if (i + kNnWaves < nc) pf = tile_point(c0 + __float_as_int(cbox[order[i + kNnWaves]][1].w));
       const float ub = reached();
-      if (lo.w > group_bound(ub)) break;  // every later box is farther
+      if (!__any(active && ub >= lo.w)) break;  // every later box is farther
+      if (ub < best) {  // another wavefront's: it holds the index
+        best = ub;
+        bi = 0x7fffffff;
+      }
       const bool need = active && nn_box_d2(q.x, q.y, q.z, lo, hi) <= ub;
       if (__any(need)) scan_tile(cur);
     }
@@ -603,14 +778,25 @@ __global__ __launch_bounds__(kNnBlock) __attribute__((amdgpu_waves_per_eu(1, 4))
 // does not depend on the order the search sorted the points in
 __global__ __launch_bounds__(1024) void k_chamfer_loss(const float* __restrict__ dx, int64_t nx,
                                                        const float* __restrict__ dy, int64_t ny,
-                                                       double* __restrict__ loss) {
+                                                       double* __restrict__ loss, float* __restrict__ loss32) {
   __shared__ double sh[16];
   const int t = threadIdx.x;
   double a = 0.0, b = 0.0;
-#pragma unroll 8
-  for (int64_t i = t; i < nx; i += 1024) a += dx[i];
-#pragma unroll 8
-  for (int64_t i = t; i < ny; i += 1024) b += dy[i];
+  for (int64_t i0 = t; i0 < nx || i0 < ny; i0 += 16 * 1024) {  // 32 loads in flight
+    float vx[16], vy[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int64_t i = i0 + 1024 * k;
+      vx[k] = dx[i < nx ? i : 0];  // no branch between the loads
+      vy[k] = dy[i < ny ? i : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int64_t i = i0 + 1024 * k;
+      a += i < nx ? vx[k] : 0.0f;
+      b += i < ny ? vy[k] : 0.0f;
+    }
+  }
   double v = a / (double)nx + b / (double)ny;
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
@@ -619,36 +805,37 @@ __global__ __launch_bounds__(1024) void k_chamfer_loss(const float* __restrict__
   if (t == 0) {
     double tot = 0.0;
     for (int w = 0; w < 16; ++w) tot += sh[w];
-    *loss = tot;
+    if (loss) *loss = tot;
+    if (loss32) *loss32 = (float)tot;
   }
 }
 
 __global__ __launch_bounds__(256) void k_chamfer_bwd_x(const float* __restrict__ x, int64_t nx,
                                                        const float* __restrict__ y, const int32_t* __restrict__ nnx,
-                                                       float* __restrict__ g) {
+                                                       const float* __restrict__ scale, float* __restrict__ g) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= nx) return;
   const int64_t j = nnx[i];
-  const float s = 2.0f / (float)nx;
+  const float s = 2.0f / (float)nx, c = scale ? *scale : 1.0f;
   if (j < 0) {  // no neighbour: the query holds NaN
 #pragma unroll
     for (int d = 0; d < 3; ++d) g[3 * i + d] = __int_as_float(0x7fc00000);
     return;
   }
 #pragma unroll
-  for (int d = 0; d < 3; ++d) g[3 * i + d] = s * (x[3 * i + d] - y[3 * j + d]);
+  for (int d = 0; d < 3; ++d) g[3 * i + d] = s * (x[3 * i + d] - y[3 * j + d]) * c;
 }
 
 __global__ __launch_bounds__(256) void k_chamfer_bwd_y(const float* __restrict__ x, const float* __restrict__ y,
                                                        int64_t ny, const int32_t* __restrict__ nny,
-                                                       float* __restrict__ g) {
+                                                       const float* __restrict__ scale, float* __restrict__ g) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= ny) return;
   const int64_t i = nny[j];
   if (i < 0) return;  // no neighbour: the target point holds NaN
-  const float s = 2.0f / (float)ny;
+  const float s = 2.0f / (float)ny, c = scale ? *scale : 1.0f;
 #pragma unroll
-  for (int d = 0; d < 3; ++d) atomicAdd(&g[3 * i + d], s * (x[3 * i + d] - y[3 * j + d]));
+  for (int d = 0; d < 3; ++d) atomicAdd(&g[3 * i + d], s * (x[3 * i + d] - y[3 * j + d]) * c);
 }
 
 __global__ void k_set_int(int32_t* __restrict__ p, int32_t v) { *p = v; }
@@ -760,18 +947,19 @@ int run_sample(const float* v, const float* vn, const int32_t* f, int64_t nf, co
   double* a = reinterpret_cast<double*>(static_cast<char*>(ws) + L.csum);
   double* bs = reinterpret_cast<double*>(static_cast<char*>(ws) + L.bs);
   const int nb = (int)((nf + kScanBlock - 1) / kScanBlock);
-  hipLaunchKernelGGL(k_face_area, dim3(nb256(nf)), dim3(256), 0, s, v, f, nf, w, a);
-  hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(256), 0, s, a, nf, bs);
-  hipLaunchKernelGGL(k_scan_tops, dim3(1), dim3(256), 0, s, bs, nb);
-  hipLaunchKernelGGL(k_scan_local, dim3(nb), dim3(256), 0, s, a, nf, bs);
-  if (m > 0) hipLaunchKernelGGL(k_sample, dim3(nb256(m)), dim3(256), 0, s, v, vn, f, nf, a, u, m, pts, nrm, face, bary);
+  hipLaunchKernelGGL(k_area_scan, dim3(nb), dim3(kScanBlock), 0, s, v, f, nf, w, a, bs);
+  const bool tops = nb <= kScanTops;
+  if (!tops) hipLaunchKernelGGL(k_scan_tops, dim3(1), dim3(256), 0, s, bs, nb);
+  if (m > 0)
+    hipLaunchKernelGGL(tops ? k_sample<true> : k_sample<false>, dim3((m + 63) / 64), dim3(64), 0, s, v, vn, f, nf, a, bs,
+                       nb, u, m, pts, nrm, face, bary);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
 int run_sample_backward(const int32_t* f, int64_t nv, const int32_t* face, const float* bary, const float* dp,
                         int64_t m, float* dv, hipStream_t s) {
   hipLaunchKernelGGL(k_fill0, dim3(256), dim3(256), 0, s, dv, 3 * nv);
-  if (m > 0) hipLaunchKernelGGL(k_sample_bwd, dim3(nb256(m)), dim3(256), 0, s, f, face, bary, dp, m, dv);
+  if (m > 0) hipLaunchKernelGGL(k_sample_bwd, dim3(nb256(3 * m)), dim3(256), 0, s, f, face, bary, dp, m, dv);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
@@ -791,7 +979,7 @@ NnLayout nn_layout(int64_t nx, int64_t ny) {
 size_t chamfer_ws(int64_t nx, int64_t ny) { return nn_layout(nx, ny).total; }
 
 int run_chamfer(const float* x, int64_t nx, const float* y, int64_t ny, int32_t* nnx, float* dx, int32_t* nny,
-                float* dy, double* loss, void* ws, hipStream_t s) {
+                float* dy, double* loss, float* loss32, void* ws, hipStream_t s) {
   const NnLayout L = nn_layout(nx, ny);
   char* b = static_cast<char*>(ws);
   int* cnt = reinterpret_cast<int*>(b + L.cnt);
@@ -801,9 +989,13 @@ int run_chamfer(const float* x, int64_t nx, const float* y, int64_t ny, int32_t*
   float4* by = reinterpret_cast<float4*>(b + L.box_y);
   const int64_t tx = (nx + kNnTile - 1) / kNnTile, ty = (ny + kNnTile - 1) / kNnTile;
   const int cb = L.cell_bits, nc = 1 << (3 * cb);
-  static_assert(kNnSmallTiles * kNnTile == 32768, "the small-cloud sort covers the clouds given 16^3 cells");
-  if (cb == kNnSmallBits && tx <= kNnSmallTiles && ty <= kNnSmallTiles) {
-    hipLaunchKernelGGL(k_nn_sort_small, dim3(2), dim3(1024), 0, s, x, nx, y, ny, cnt, sx, sy, bx, by);
+  static_assert(kNnSmall / kNnTile * kNnTile == 32768, "the small-cloud sort covers the clouds given 16^3 cells");
+  const bool small = cb == kNnSmallBits;
+  if (small) {
+    uint16_t *kx = reinterpret_cast<uint16_t*>(nnx), *ky = reinterpret_cast<uint16_t*>(nny);
+    hipLaunchKernelGGL(k_nn_keys, dim3(nb256(nx + ny)), dim3(256), 0, s, x, (int)nx, y, (int)ny, kx, ky);
+    hipLaunchKernelGGL(k_nn_sort, dim3(2 * kNnSortWgs), dim3(1024), 0, s, x, (int)nx, y, (int)ny, kx, ky, cnt, sx, sy, bx,
+                       by);
   } else {
     hipLaunchKernelGGL(k_nn_zero, dim3(64), dim3(256), 0, s, cnt, 2 * nc);
     hipLaunchKernelGGL(k_nn_count, dim3(nb256(nx + ny)), dim3(256), 0, s, x, nx, y, ny, cnt, cb);
@@ -811,17 +1003,19 @@ int run_chamfer(const float* x, int64_t nx, const float* y, int64_t ny, int32_t*
     hipLaunchKernelGGL(k_nn_scatter, dim3(nb256(nx + ny)), dim3(256), 0, s, x, nx, y, ny, cnt, sx, sy, cb);
     hipLaunchKernelGGL(k_nn_box, dim3(tx + ty), dim3(64), 0, s, sx, nx, sy, ny, tx, bx, by);
   }
-  const NnSide A{sx, nx, sy, by, cnt + nc, ny, nnx, dx};  // samples x against the target y
-  const NnSide B{sy, ny, sx, bx, cnt, nx, nny, dy};       // and back
-  hipLaunchKernelGGL(k_nn_query, dim3(tx + ty), dim3(kNnBlock), 0, s, A, B, tx, cb);
-  if (loss) hipLaunchKernelGGL(k_chamfer_loss, dim3(1), dim3(1024), 0, s, dx, nx, dy, ny, loss);
+  const NnSide A{sx, bx, nx, sy, by, cnt + nc, ny, nnx, dx};  // samples x against the target y
+  const NnSide B{sy, by, ny, sx, bx, cnt, nx, nny, dy};       // and back
+  hipLaunchKernelGGL(k_nn_query, dim3(tx + ty), dim3(kNnBlock), 0, s, A, B, tx, cb,
+                     small ? kNnFineBits - kNnSmallBits : 0);
+  if (loss || loss32)
+    hipLaunchKernelGGL(k_chamfer_loss, dim3(1), dim3(1024), 0, s, dx, nx, dy, ny, loss, loss32);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
 int run_chamfer_backward(const float* x, int64_t nx, const float* y, int64_t ny, const int32_t* nnx,
-                         const int32_t* nny, float* g, hipStream_t s) {
-  hipLaunchKernelGGL(k_chamfer_bwd_x, dim3(nb256(nx)), dim3(256), 0, s, x, nx, y, nnx, g);
-  hipLaunchKernelGGL(k_chamfer_bwd_y, dim3(nb256(ny)), dim3(256), 0, s, x, y, ny, nny, g);
+                         const int32_t* nny, const float* scale, float* g, hipStream_t s) {
+  hipLaunchKernelGGL(k_chamfer_bwd_x, dim3(nb256(nx)), dim3(256), 0, s, x, nx, y, nnx, scale, g);
+  hipLaunchKernelGGL(k_chamfer_bwd_y, dim3(nb256(ny)), dim3(256), 0, s, x, y, ny, nny, scale, g);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
@@ -885,7 +1079,7 @@ int run_components(const float* v, int64_t nv, const int32_t* f, int64_t nf, int
   // vertex index in it, whose own label never changes
   if (it == max_iters) return -5;
   if (w) {
-    hipLaunchKernelGGL(k_face_area, dim3(nb256(nf)), dim3(256), 0, s, v, f, nf, nullptr, area);
+    hipLaunchKernelGGL(k_face_area, dim3(nb256(nf)), dim3(256), 0, s, v, f, nf, area);
     hipLaunchKernelGGL(k_fill0d, dim3(256), dim3(256), 0, s, carea, nv);
     hipLaunchKernelGGL(k_comp_area, dim3(nb256(nf)), dim3(256), 0, s, f, nf, lab, area, carea);
     hipLaunchKernelGGL(k_comp_best, dim3(1), dim3(256), 0, s, carea, nv, best);

@@ -82,8 +82,8 @@ class SampleFunction(torch.autograd.Function):
         return dv, None, None
 
 
-def chamfer_raw(x, y):
-    """(loss as a 0-d double tensor, nn_x, d_x, nn_y, d_y)."""
+def chamfer_raw(x, y, dtype=torch.float64):
+    """(loss as a 0-d tensor of float64 or float32, nn_x, d_x, nn_y, d_y)."""
     dev = x.device
     L = _lib.lib()
     nx, ny = int(x.shape[0]), int(y.shape[0])
@@ -92,11 +92,23 @@ def chamfer_raw(x, y):
     dx = torch.empty((nx,), dtype=torch.float32, device=dev)
     nny = torch.empty((ny,), dtype=torch.int32, device=dev)
     dy = torch.empty((ny,), dtype=torch.float32, device=dev)
-    loss = torch.empty((), dtype=torch.float64, device=dev)
-    _lib.check(L.psr_chamfer(_ctx(dev).handle, _p(x.detach().contiguous()), nx, _p(y.contiguous()), ny, _p(nnx),
-                             _p(dx), _p(nny), _p(dy), _p(loss), _p(ws), ws.numel(), _st(dev)),
-               "psr_chamfer")
+    loss = torch.empty((), dtype=dtype, device=dev)
+    fn = L.psr_chamfer if dtype == torch.float64 else L.psr_chamfer_f32
+    _lib.check(fn(_ctx(dev).handle, _p(x.detach().contiguous()), nx, _p(y.contiguous()), ny, _p(nnx), _p(dx), _p(nny),
+                  _p(dy), _p(loss), _p(ws), ws.numel(), _st(dev)), "psr_chamfer")
     return loss, nnx, dx, nny, dy
+
+
+def _plain_scalar(g, dev):
+    """Address of g where the kernel may multiply by it, else None: a graph of the
+    backward needs the product as an operation of its own, and a batched, a
+    lazily negated or a zero tensor has no such memory."""
+    if torch.is_grad_enabled() or g.dtype != torch.float32 or g.device != dev or g.is_neg():
+        return None
+    try:
+        return g.data_ptr() or None
+    except RuntimeError:
+        return None
 
 
 class ChamferFunction(torch.autograd.Function):
@@ -105,19 +117,20 @@ class ChamferFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, y):
         x = x.contiguous()
-        loss, nnx, _, nny, _ = chamfer_raw(x, y)
+        loss, nnx, _, nny, _ = chamfer_raw(x, y, torch.float32)
         ctx.save_for_backward(x, y, nnx, nny)
-        return loss.to(torch.float32)
+        return loss
 
     @staticmethod
     def backward(ctx, g):
         x, y, nnx, nny = ctx.saved_tensors
         dev = x.device
         gx = torch.empty_like(x)
-        _lib.check(_lib.lib().psr_chamfer_backward(_ctx(dev).handle, _p(x), int(x.shape[0]), _p(y.contiguous()),
-                                                   int(y.shape[0]), _p(nnx), _p(nny), _p(gx), _st(dev)),
+        scale = _plain_scalar(g, dev)
+        _lib.check(_lib.lib().psr_chamfer_backward_scaled(_ctx(dev).handle, _p(x), int(x.shape[0]), _p(y.contiguous()),
+                                                          int(y.shape[0]), _p(nnx), _p(nny), scale, _p(gx), _st(dev)),
                    "psr_chamfer_backward")
-        return gx * g, None
+        return gx if scale else gx * g, None
 
 
 def components(verts, faces, largest: bool = True):
