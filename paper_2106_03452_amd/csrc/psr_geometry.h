@@ -45,9 +45,13 @@ __host__ __device__ constexpr int j0_block(int res) { return tile_j0(res) * plan
 // two bins per tile (floor column b1 inside the tile, or on its last column,
 // which also reaches the next tile): bin = b0 * 2 row_tiles(res) +
 // 2 (b1 / tile_rows(res)) + (b1 is the tile's last column).
+// At 256^3 a tile is 32 rows (256 threads, four workgroups per CU): fewer rows
+// without a point are transformed than with 64 (P1 39.5 -> 32.8 us, B1 29.8 ->
+// 23.1, B5 33.7 -> 28.5 with 100k points of a surface) for twice the bins (binning
+// +1 us). At 512^3 the bitmap of the tiles (8192 bits) is full with 32 rows.
 __host__ __device__ constexpr int tile_rows(int res) {
   // where a plane pass splits a plane of res <= 128 in two, bins must not be coarser than a part
-  return imin(imin(res, PSR_ROW_THREADS / plan_TPL(res / 2)),
+  return imin(imin(res, (res == 256 ? 256 : PSR_ROW_THREADS) / plan_TPL(res / 2)),
               (res >= PSR_PLANE_SPLIT_MIN && res <= 128) ? res / 2 : res);
 }
 __host__ __device__ constexpr int rows_block(int res) { return tile_rows(res) * plan_TPL(res / 2); }

@@ -95,12 +95,18 @@ __device__ __forceinline__ Ranges span_ranges(const int* __restrict__ off, int j
 // Workgroup -> (row tile T = j0 * row_tiles + tb, channel c < NC) of a row
 // pass over NC channels. The NC workgroups of a tile get ids equal mod 8, so
 // they run on the same XCD and its L2 serves their repeated reads of the
-// tile's point records. The tile count res * row_tiles is a multiple of 8.
+// tile's point records. The tile count res * row_tiles is a multiple of 8; the
+// tiles of successive eights rotate over the XCDs, because a tile's place in its
+// plane decides whether points reach it: with tile mod 8 as the XCD, those
+// that hold the middle of the planes had most of the work (P1 at 256^3 43.7 ->
+// 33.3 us, P2 37.5 -> 33.0, B1 30.4 -> 23.1, B4 31.8 -> 28.7, B5 36.3 -> 28.3; a
+// surface of 100k points).
 template <int NC>
 __device__ __forceinline__ void tile_of(int bid, int& T, int& c) {
   const int x = bid & 7, q = bid >> 3;
   c = q % NC;
-  T = (q / NC) * 8 + x;
+  const int u = q / NC;
+  T = u * 8 + ((x + u) & 7);
 }
 
 template <int RES>
@@ -131,6 +137,7 @@ __device__ __forceinline__ void b_init(int* __restrict__ counts, int n, SavedHea
 // bin it touched with one global atomic per bin: few global atomics per bin
 // even when a surface crowds the points into a few bins.
 constexpr int kBinChunk = 1024;
+constexpr int kBinThreads = 1024;  // with 256, zeroing and flushing the bins took half the time at 256^3 and 512^3
 
 // The record of point i (the coordinates wrapped into the periodic domain) and
 // its bin; bad: a coordinate or normal component is not finite (the fixed-point
@@ -181,16 +188,16 @@ __device__ __forceinline__ void b_bin(const float* __restrict__ pts, const float
                                       int64_t npoints, int* __restrict__ counts, PointRec* __restrict__ tmp, int2* __restrict__ colrank,
                                       SavedHeader* __restrict__ hdr, int bid) {
   constexpr int NB = num_bins(RES);
-  constexpr int PPT = kBinChunk / 256;
+  constexpr int PPT = kBinChunk / kBinThreads;
   __shared__ int hist[NB];
   const int t = threadIdx.x;
-  for (int e = t; e < NB; e += 256) hist[e] = 0;
+  for (int e = t; e < NB; e += kBinThreads) hist[e] = 0;
   __syncthreads();
   int mybin[PPT], myrank[PPT];
   bool anybad = false;
 #pragma unroll
   for (int u = 0; u < PPT; ++u) {
-    const int64_t i = (int64_t)bid * kBinChunk + u * 256 + t;
+    const int64_t i = (int64_t)bid * kBinChunk + u * kBinThreads + t;
     mybin[u] = -1;
     if (i >= npoints) continue;
     bool bad;
@@ -200,51 +207,16 @@ __device__ __forceinline__ void b_bin(const float* __restrict__ pts, const float
   }
   if (anybad) atomicOr(&hdr->flags, 1);
   __syncthreads();
-  for (int e = t; e < NB; e += 256) {
+  for (int e = t; e < NB; e += kBinThreads) {
     const int cnt = hist[e];
     hist[e] = cnt ? atomicAdd(&counts[e], cnt) : 0;
   }
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < PPT; ++u) {
-    const int64_t i = (int64_t)bid * kBinChunk + u * 256 + t;
+    const int64_t i = (int64_t)bid * kBinChunk + u * kBinThreads + t;
     if (mybin[u] >= 0) colrank[i] = make_int2(mybin[u], hist[mybin[u]] + myrank[u]);
   }
-}
-
-// Exclusive scan of n counts into off[0..n]: one workgroup of 1024 threads,
-// coalesced rounds of 1024 elements, wavefront shuffles + a carry.
-__device__ __forceinline__ void b_scan(const int* __restrict__ counts, int* __restrict__ off, int n, int bid) {
-  __shared__ int wsum[16];
-  const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-  int carry = 0;
-  for (int base = 0; base < n; base += 1024) {
-    const int i = base + t;
-    const int c = i < n ? counts[i] : 0;
-    int v = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int y = __shfl_up(v, d, 64);
-      if (lane >= d) v += y;
-    }
-    if (lane == 63) wsum[wid] = v;
-    __syncthreads();
-    if (wid == 0) {
-      int w = lane < 16 ? wsum[lane] : 0;
-#pragma unroll
-      for (int d = 1; d < 16; d <<= 1) {
-        const int y = __shfl_up(w, d, 64);
-        if (lane >= d) w += y;
-      }
-      if (lane < 16) wsum[lane] = w;
-    }
-    __syncthreads();
-    const int before = (wid ? wsum[wid - 1] : 0) + carry;
-    if (i < n) off[i] = before + v - c;
-    carry += wsum[15];
-    __syncthreads();
-  }
-  if (t == 0) off[n] = carry;
 }
 
 // Bitmap of the planes some point's corners reach (floor planes j0 - 1 and
@@ -311,11 +283,11 @@ __device__ __forceinline__ void b_scatter(const PointRec* __restrict__ tmp, cons
   sorted[off[cr.x] + cr.y] = tmp[i];
 }
 
-// Grids with at most kLdsBins bins skip the one-workgroup scan kernel: every
-// scatter workgroup forms the same exclusive prefix sum of the counts in LDS
-// (BLOCK threads, consecutive runs of bins per thread), and workgroup 0 also
-// publishes the offsets and the liveness bitmaps.
-constexpr int kLdsBins = 4096;
+// Every scatter workgroup forms the same exclusive prefix sum of the counts in
+// LDS (BLOCK threads, consecutive runs of bins per thread), and workgroup 0 also
+// publishes the offsets and the liveness bitmaps. (A scan by one workgroup and a
+// scatter took 27.8 us in two launches at 512^3, this 12.5.)
+constexpr int kScatterThreads = 1024;
 
 template <int NB, int BLOCK>
 __device__ __forceinline__ void scan_to_lds(const int* __restrict__ counts, int* soff) {
@@ -324,12 +296,21 @@ __device__ __forceinline__ void scan_to_lds(const int* __restrict__ counts, int*
   __shared__ int wtot[NW];
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   int v[PT], sum = 0;
+  if constexpr (NB % BLOCK == 0 && PT % 4 == 0) {
 #pragma unroll
-  for (int k = 0; k < PT; ++k) {
-    const int i = t * PT + k;
-    v[k] = i < NB ? counts[i] : 0;
-    sum += v[k];
+    for (int k = 0; k < PT; k += 4) {
+      const int4 c = reinterpret_cast<const int4*>(counts)[(t * PT + k) / 4];
+      v[k] = c.x, v[k + 1] = c.y, v[k + 2] = c.z, v[k + 3] = c.w;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+      const int i = t * PT + k;
+      v[k] = i < NB ? counts[i] : 0;
+    }
   }
+#pragma unroll
+  for (int k = 0; k < PT; ++k) sum += v[k];
   int x = sum;  // inclusive scan of the thread sums within the wavefront
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -623,7 +604,7 @@ __device__ __forceinline__ void b_splat_r2c(const PointRec* __restrict__ sorted,
   constexpr int64_t N3 = (int64_t)RES * RES * RES;
   __shared__ __align__(16) cf rows[rows_lds(RES) * LS];
   __shared__ cf stw[M];      // FFT table of length M
-  __shared__ cf rtw[M + 1];  // W_RES^k, k in [0, M], for the r2c post-processing
+  __shared__ cf rtw[M / 2 + 1];  // W_RES^k, k in [0, M/2], for the r2c post-processing
   float* rf = reinterpret_cast<float*>(rows);
   constexpr int NC = MODE == MODE_BWDH || MODE == MODE_BWDA ? 1 : 3;  // channels in the grid
   int T, c;
@@ -648,7 +629,7 @@ __device__ __forceinline__ void b_splat_r2c(const PointRec* __restrict__ sorted,
   }
   if constexpr (MODE != MODE_VOUT) {
     stage_table<BR>(stw, tw + M, M);
-    stage_table<BR>(rtw, tw + RES, M + 1);
+    stage_table<BR>(rtw, tw + RES, M / 2 + 1);
   }
 
   if constexpr (MODE == MODE_BWDA) {
@@ -808,10 +789,9 @@ __device__ __forceinline__ void b_axis1_fwd(const cf* __restrict__ in, cf* __res
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
   stage_table<cols_block(RES)>(stw, tw + RES, RES);
-  int b = bid;
-  const int tb = b % (RES / TC);
-  b /= RES / TC;
+  int b = bid / (RES / TC);
   const int k2 = b % H;
+  const int tb = (bid + k2) % (RES / TC);  // rotated over the XCDs like the row tiles
   // output channel; with MERGE the heavier channel-1 workgroups (two
   // transforms) come first in the grid so that they do not form its tail
   const int c = MERGE ? 1 - b / H : b / H;
@@ -1017,10 +997,9 @@ __device__ __forceinline__ void b_axis1_inv(const cf* __restrict__ in, cf* __res
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
   stage_table<cols_block(RES)>(stw, tw + RES, RES);
-  int b = bid;
-  const int tb = b % (RES / TC);
-  b /= RES / TC;
+  int b = bid / (RES / TC);
   const int k2 = b % H;
+  const int tb = (bid + k2) % (RES / TC);  // rotated over the XCDs like the row tiles
   // input channel; with SPLIT the heavier channel-1 workgroups (two
   // transforms, two outputs) come first in the grid
   const int c = SPLIT ? 1 - b / H : b / H;
@@ -1169,7 +1148,7 @@ __device__ __forceinline__ void b_c2r_gather(const cf* __restrict__ in,
   constexpr int TPL = plan_TPL(M), E = plan_E(M), LS = row_ls(M);
   __shared__ __align__(16) cf rows[rows_lds(RES) * LS];
   __shared__ cf stw[M];      // FFT table of length M
-  __shared__ cf rtw[M + 1];  // W_RES^k, k in [0, M], for the c2r pre-processing
+  __shared__ cf rtw[M / 2 + 1];  // W_RES^k, k in [0, M/2], for the c2r pre-processing (W^(M-k) = -conj W^k)
   const float* rf = reinterpret_cast<const float*>(rows);
   constexpr int NC = MODE == MODE_BWD ? 3 : 1;  // channels in the grid
   int T, c;
@@ -1187,7 +1166,7 @@ __device__ __forceinline__ void b_c2r_gather(const cf* __restrict__ in,
     if (MODE == MODE_BWD && total == 0) return;
   }
   stage_table<BR>(stw, tw + M, M);
-  stage_table<BR>(rtw, tw + RES, M + 1);
+  stage_table<BR>(rtw, tw + RES, M / 2 + 1);
   // the thread's point records are fetched now, under the grid loads
   constexpr int KR = 4;
   Recs<KR> recs;
@@ -1246,7 +1225,7 @@ __device__ __forceinline__ void b_c2r_gather(const cf* __restrict__ in,
       if (k != 0 && 2 * k != M) {
         const cf Ee{xm.x + xk.x, xm.y - xk.y};
         const cf Dd{xm.x - xk.x, xm.y + xk.y};
-        const cf w{twr[M - k].x, -twr[M - k].y};
+        const cf w{-twr[k].x, -twr[k].y};
         const cf Oo = cmul(Dd, w);
         rows[im] = cf{Ee.x - Oo.y, Ee.y + Oo.x};
       }
@@ -2029,7 +2008,7 @@ __global__ __launch_bounds__(256) void k_init(const Batch<MAXJ> B) {
 }
 
 template <int RES, int MAXJ>
-__global__ __launch_bounds__(256) void k_bin(const Batch<MAXJ> B) {
+__global__ __launch_bounds__(kBinThreads) void k_bin(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   b_bin<RES>(J.pts, J.nrm, J.P, w.counts, w.tmp, w.colrank, sv.hdr, bid);
 }
@@ -2052,34 +2031,20 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const Batch<MAXJ>
 }
 
 template <int RES, int MAXJ>
-__global__ __launch_bounds__(1024) void k_scan(const Batch<MAXJ> B) {
-  PSR_JOB(RES);
-  b_scan(w.counts, sv.off, num_bins(RES), bid);
-  b_live_planes<RES>(sv.off, sv.hdr);
-}
-
-template <int RES, int MAXJ>
-__global__ __launch_bounds__(256) void k_scatter(const Batch<MAXJ> B) {
-  PSR_JOB(RES);
-  b_scatter(w.tmp, w.colrank, sv.off, sv.sorted, J.P, bid);
-}
-
-template <int RES, int MAXJ>
-__global__ __launch_bounds__(256) void k_scan_scatter(const Batch<MAXJ> B) {
+__global__ __launch_bounds__(kScatterThreads) void k_scan_scatter(const Batch<MAXJ> B) {
   PSR_JOB(RES);
   constexpr int NB = num_bins(RES);
-  static_assert(NB <= kLdsBins, "bins fit in LDS");
   __shared__ int soff[NB + 1];
-  scan_to_lds<NB, 256>(w.counts, soff);
+  scan_to_lds<NB, kScatterThreads>(w.counts, soff);
   if (bid == 0) {
-    for (int e = threadIdx.x; e <= NB; e += 256) sv.off[e] = soff[e];
+    for (int e = threadIdx.x; e <= NB; e += kScatterThreads) sv.off[e] = soff[e];
     b_live_planes<RES>(soff, sv.hdr);
   }
   b_scatter(w.tmp, w.colrank, soff, sv.sorted, J.P, bid);
 }
 
-// the row passes at 256 and 512: two 512-thread workgroups per CU (LDS allows
-// them) need at most 128 VGPRs (B1 alone took 138, and ran one per CU)
+// the row passes at 256 and 512: the four 256-thread or two 512-thread
+// workgroups per CU that LDS allows need at most 128 VGPRs
 template <int RES, int MODE, int MAXJ>
 __global__ __launch_bounds__(rows_wg(RES)) __attribute__((amdgpu_waves_per_eu(RES >= 256 ? 4 : 1)))
 void k_splat_r2c(const Batch<MAXJ> B) {
@@ -2282,13 +2247,9 @@ static int seq_bin(Exec& x, const JobArg* J, int n) {
     }
   }
   rc |= launch<MAXJ>(x, k_init<RES, MAXJ>, 256, J, n, [](const JobArg&) { return G::init_blocks; });
-  rc |= launch<MAXJ>(x, k_bin<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, kBinChunk); });
-  if constexpr (num_bins(RES) <= kLdsBins) {
-    rc |= launch<MAXJ>(x, k_scan_scatter<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, 256); });
-  } else {
-    rc |= launch<MAXJ>(x, k_scan<RES, MAXJ>, 1024, J, n, [](const JobArg&) { return 1; });
-    rc |= launch<MAXJ>(x, k_scatter<RES, MAXJ>, 256, J, n, [](const JobArg& a) { return nblk(a.P, 256); });
-  }
+  rc |= launch<MAXJ>(x, k_bin<RES, MAXJ>, kBinThreads, J, n, [](const JobArg& a) { return nblk(a.P, kBinChunk); });
+  rc |= launch<MAXJ>(x, k_scan_scatter<RES, MAXJ>, kScatterThreads, J, n,
+                     [](const JobArg& a) { return nblk(a.P, kScatterThreads); });
   return rc;
 }
 
