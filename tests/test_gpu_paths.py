@@ -82,3 +82,134 @@ def test_chamfer_gradient_takes_the_factor_in_or_out(dev):
         assert np.abs(host(got) - k * ref).max() <= tol
     # d(sum(c x grad)) / dc; 9000 terms summed in float32
     assert dc[0] == 0 and abs(float(dc[1]) - ref.sum()) <= 9000 * tol
+
+
+def _cloud(kind, points, seed=0):
+    """Clouds that reach few planes and row tiles, or all of them."""
+    rng = np.random.default_rng(seed)
+    p = rng.random((points, 3))
+    if kind == "sheet":  # two neighbouring planes, at the domain's edge
+        p[:, 0] = 0.999 + 0.002 * p[:, 0]
+    elif kind == "rod":  # a few rows of every plane
+        p[:, 1] = 0.49 + 0.004 * p[:, 1]
+    elif kind == "ball":
+        p = 0.5 + 0.2 * (p - 0.5)
+    n = rng.standard_normal((points, 3))
+    return p.astype(np.float32), n.astype(np.float32)
+
+
+@pytest.mark.parametrize("res", [32, 64, 128])
+@pytest.mark.parametrize("points", [1, 1023, 1024, 1025, 32768, 32769, 131072])
+def test_two_launch_sort_equals_three(dev, res, points):
+    """Up to 131072 points are sorted in two launches. The splat is an exact sum,
+    so points with zero normals, as many as take the cloud to the other path,
+    leave the raster as it is, bit for bit. One point is not finite."""
+    from paper_2106_03452_amd import function as F
+    announce(f"sort {res}^3, {points} points")
+    p, n = _cloud("ball", points, points)
+    if points > 1:
+        p[points // 2, 1] = np.nan
+    more = 131073 - points
+    two = F.debug_splat(to_dev(p, dev), to_dev(n, dev), res)
+    three = F.debug_splat(to_dev(np.concatenate([p, _cloud("all", more)[0]]), dev),
+                          to_dev(np.concatenate([n, np.zeros((more, 3))]), dev), res)
+    assert torch.equal(two, three)
+    assert float(two.abs().max()) > 0
+
+
+@pytest.mark.parametrize("res", [8, 16, 32, 64, 128, 256, 512])
+@pytest.mark.parametrize("kind", ["one", "sheet", "rod", "ball", "all"])
+def test_nothing_unwritten_is_read(dev, res, kind):
+    """Planes and row tiles without a point are neither written nor read: the
+    solve and its gradients must not depend on what the buffers held before
+    (zeros, or bytes that read as NaN)."""
+    from paper_2106_03452_amd import _lib, function as F
+    announce(f"stale scratch {res}^3 {kind}")
+    p, n = (to_dev(a, dev) for a in _cloud(kind, 1 if kind == "one" else 3000, res))
+    P = p.shape[0]
+    g = torch.randn((res,) * 3, generator=torch.Generator(device=dev).manual_seed(res), device=dev)
+    out = []
+    for byte in (0, 255):
+        ws = torch.full((_lib.workspace_bytes(res, P),), byte, dtype=torch.uint8, device=dev)
+        stale = torch.full((_lib.saved_bytes(res, P),), byte, dtype=torch.uint8, device=dev)
+        del stale  # the allocator hands it out again as the saved state
+        chi, saved = F.forward(p, n, res, workspace=ws)
+        ws.fill_(byte)
+        out.append((chi, *F.backward(chi, saved, g, P, res, workspace=ws)))
+    for a, b in zip(*out):
+        assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("res,slabs", [(16, 16), (64, 1), (64, 8), (256, 4)])
+@pytest.mark.parametrize("kind", ["one", "sheet", "rod", "all"])
+def test_slab_solve_reads_nothing_unwritten(dev, res, slabs, kind):
+    from paper_2106_03452_amd import slab as S
+    announce(f"slab stale scratch {res}^3 / {slabs} {kind}")
+    p, n = (to_dev(a, dev) for a in _cloud(kind, 1 if kind == "one" else 3000, res))
+    out = []
+    for byte in (0, 255):
+        ws = torch.full((S.workspace_bytes(res, p.shape[0], slabs),), byte, dtype=torch.uint8, device=dev)
+        out.append(S.forward(p, n, res, slabs=slabs, workspace=ws)[0])
+    assert bool(torch.isfinite(out[0]).all()) and torch.equal(*out)
+
+
+@pytest.mark.parametrize("res", [32, 64, 128])
+@pytest.mark.parametrize("kind", ["sheet", "ball", "all"])
+def test_single_and_batched_solves_agree(dev, res, kind):
+    """A single solve up to 128^3 transforms s G and W apart and adds them in the
+    j0 pass, a batch transforms their sum: the same in exact arithmetic; both
+    round to float32 (the oracle tests' bound on either is 1e-5)."""
+    from paper_2106_03452_amd import batch as B, function as F
+    announce(f"single against batch {res}^3 {kind}")
+    jobs = []
+    for seed in (1, 2):
+        p, n = (to_dev(a, dev) for a in _cloud(kind, 2000 * seed, seed))
+        g = torch.randn((res,) * 3, generator=torch.Generator(device=dev).manual_seed(seed), device=dev)
+        jobs.append(B.Job(p, n, res, 2.0, g))
+    plan = B.BatchPlan(jobs)
+    for ws in plan.ws:
+        ws.fill_(255)
+    plan.run()
+    for j, (chi, dp, dn) in zip(jobs, plan.results()):
+        p, n = j.points.clone().requires_grad_(True), j.normals.clone().requires_grad_(True)
+        one = F.solve(p, n, res)
+        grads = torch.autograd.grad(one, (p, n), j.dchi)
+        for a, b in zip((chi, dp, dn), (one.detach(), *grads)):
+            assert float((a - b).norm()) <= 2e-5 * float(b.norm())
+
+
+@pytest.mark.parametrize("res", [8, 64, 128, 256])
+@pytest.mark.parametrize("kind", ["blobs", "empty", "full"])
+def test_sized_marching_cubes_equals_the_plain_call(dev, res, kind):
+    """The totals arrive before the mesh is written; capacities that are too small
+    give the same totals."""
+    import ctypes
+    from paper_2106_03452_amd import _lib, mesh as M
+    announce(f"sized marching cubes {res}^3 {kind}")
+    g = torch.Generator(device=dev).manual_seed(res)
+    x = torch.nn.functional.interpolate(torch.randn((1, 1, 4, 4, 4), generator=g, device=dev), size=(res,) * 3,
+                                        mode="trilinear")[0, 0].contiguous()
+    chi = {"blobs": x, "empty": torch.ones_like(x), "full": torch.randn((res,) * 3, generator=g, device=dev)}[kind]
+    L, ctx, dv = _lib.lib(), _lib.context(0), torch.device(dev)
+    stream = torch.cuda.current_stream(dv).cuda_stream
+    cap_v, cap_t = (3 * res ** 3, 5 * res ** 3) if kind == "full" else (64 * res * res, 128 * res * res)
+    got = []
+    for sized, vcap, tcap in ((False, cap_v, cap_t), (True, cap_v, cap_t), (True, 1, 1)):
+        state = torch.empty(M.state_bytes(res), dtype=torch.uint8, device=dv)
+        v, vn = torch.zeros((vcap, 3), device=dv), torch.zeros((vcap, 3), device=dv)
+        e = torch.zeros((vcap,), dtype=torch.int32, device=dv)
+        t = torch.zeros((tcap, 3), dtype=torch.int32, device=dv)
+        nv, nt, st = ctypes.c_int64(-1), ctypes.c_int64(-1), ctypes.c_int(-1)
+        tot = (ctypes.byref(nv), ctypes.byref(nt), ctypes.byref(st))
+        args = (ctx.handle, chi.data_ptr(), res, 0.0, v.data_ptr(), vn.data_ptr(), e.data_ptr(), vcap, t.data_ptr(), tcap,
+                state.data_ptr())
+        if sized:
+            _lib.check(L.psr_marching_cubes_sized(*args, *tot, stream), "sized")
+        else:
+            _lib.check(L.psr_marching_cubes(*args, stream), "plain")
+            _lib.check(L.psr_mc_counts(state.data_ptr(), stream, *tot), "counts")
+        got.append(((nv.value, nt.value, st.value), (v, vn, e, t)))
+    assert got[0][0] == got[1][0] == got[2][0] and got[0][0][2] == 0
+    assert (got[0][0][0] == 0) == (kind == "empty")
+    for a, b in zip(got[0][1], got[1][1]):
+        assert torch.equal(a, b)
