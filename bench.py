@@ -46,8 +46,8 @@ def half_spec_bytes(r: int) -> int:
 
 def tile_rows(r: int) -> int:
     """Rows of a binning tile (the library's row-pass geometry: 512-thread row
-    workgroups, 16 elements per thread of a half-length row)."""
-    return min(r, 512 // max(1, (r // 2) // 16))
+    workgroups, 256 at 256^3; 16 elements per thread of a half-length row)."""
+    return min(r, (256 if r == 256 else 512) // max(1, (r // 2) // 16))
 
 
 def live_fractions(points, r: int):
@@ -85,8 +85,8 @@ def stage_bytes(r: int, P: int, fp: float = 1.0, ft: float = 1.0) -> dict:
         "P1_splat_r2c": 32 * P + 3 * S * ft,           # sorted points in, 3 half-spectra of touched row tiles out
         "P2_fft_j1": 3 * S * ft + 2 * S * fp,          # touched tile segments of 3 channels in, v~_0 and merged W of live planes out
         # live planes of the 2 in, chi~ (after the k0 inverse) out; at 32-128 the plane pass hands over 3 channels
-        # (v~_0, kappa_1 v~_1, kappa_2 v~_2), read whole
-        "P3_fft_j0_spectral_ifft_j0": (3 * S if 32 <= r <= 128 else 2 * S * fp) + S,
+        # (v~_0, kappa_1 v~_1, kappa_2 v~_2)
+        "P3_fft_j0_spectral_ifft_j0": (3 if 32 <= r <= 128 else 2) * S * fp + S,
         "P4_ifft_j1": 2 * S,
         "P5_c2r_gather": S + N4 + 32 * P + 16 * slots * P,  # chi' written, gather partials
         "fwd_reduce": 64 * P + 16 * P,
@@ -95,15 +95,15 @@ def stage_bytes(r: int, P: int, fp: float = 1.0, ft: float = 1.0) -> dict:
         "B1a_reduce_r2c": 2 * N4 + S * (1 - ft),      # G and chi in (FP64 partials), H = sG spectra of point-free tiles out
         "B1_cotangent_r2c": N4 * ft + 32 * P + S * ft, # the tiles with points: G in, splat of W, spectra out
         "B2_fft_j1": 2 * S,
-        # 1 in (2 after a plane pass); kappa_0 channel and U out on live planes
-        "B3_fft_j0_conjop_ifft_j0": (2 * S if 32 <= r <= 128 else S) + 2 * S * fp,
+        # 1 in (after a plane pass W^ of the live planes too); kappa_0 channel and U out on live planes
+        "B3_fft_j0_conjop_ifft_j0": S + (S * fp if 32 <= r <= 128 else 0) + 2 * S * fp,
         "B4_ifft_j1": 2 * S * fp + 3 * S * ft,         # live planes in, touched tiles out
         "B5_c2r_gather": 3 * S * ft + 32 * P + 48 * slots * P,
         "bwd_finalize": 48 * slots * P + 16 * P + 32 * P + 24 * P,
         # plane passes (two axes per kernel; 32^3 to 256^3)
-        "P12_splat_r2c_fft_j1": 32 * P + 3 * S,        # sorted points in, v~_0, kappa_1 v~_1, kappa_2 v~_2 out
+        "P12_splat_r2c_fft_j1": 32 * P + 3 * S * fp,   # sorted points in, v~_0, kappa_1 v~_1, kappa_2 v~_2 of live planes out
         "P45_ifft_j1_c2r_gather": S + N4 + 32 * P + 16 * slots * P,
-        "B12_cotangent_r2c_fft_j1": 2 * N4 + 32 * P + 2 * S,  # G and chi in (FP64 sums), (sG)^ and W^ out
+        "B12_cotangent_r2c_fft_j1": 2 * N4 + 32 * P + S + S * fp,  # G and chi in (FP64 sums), (sG)^ and live W^ out
         "B45_ifft_j1_c2r_gather": 2 * S * fp + 32 * P + 48 * slots * P,  # upper bound: plane parts without points are skipped
     }
 
