@@ -40,9 +40,9 @@ constexpr int kScanBlock = 1024;
 // Waves per SIMD asked of the register allocator for S1: two of its 512-thread
 // workgroups fit a CU by LDS from 128 on, which needs at most 128 VGPRs.
 constexpr int slab_rows_waves(int res) { return res >= 128 ? 4 : 2; }
-// workgroups of S1 (two fit a CU): four times what runs at once, so that the
-// live tiles, which crowd together, spread evenly
+// workgroups of S1 (two fit a CU), and the most (tile, channel) items of one
 constexpr int kRowGrid = 2048;
+constexpr int kRowItems = 3 * 64 * kSlabMaxRes / kRowGrid + 8;
 
 // Ranges of sorted points whose corners reach rows [a0, a0 + TR) of plane j0:
 // points sorted by bin b0 * RES + b1, floor planes j0 - 1 and j0, floor rows
@@ -271,9 +271,10 @@ __global__ __launch_bounds__(256) void k_slab_scatter(SlabArgs a) {
 // field) -> r2c FFT along j2 -> A_g[c][j0 - g s], k2-tiled rows of r/2 + 1.
 // Row tiles that no point reaches are zero: they are not written, and S2 does
 // not read them (65 % of the 1M-point scene's tiles at 1024^3: S1 4.35 -> 2.76
-// ms, S2 5.63 -> 4.04 ms). A workgroup takes every gridDim.x-th (tile, channel)
-// item, so a dead item costs one test of the bitmap instead of a workgroup that
-// holds its LDS for a memory latency.
+// ms, S2 5.63 -> 4.04 ms). A workgroup takes every gridDim.x-th (live tile,
+// channel) item: it finds them from the planes' bitmaps once, so all have the
+// same number (2.78 -> 2.06 ms: with every tile an item and a test of the bitmap
+// each, the workgroups' shares of the live ones, which crowd together, differed).
 // ---------------------------------------------------------------------------
 template <int RES, bool LOAD>
 __global__ __launch_bounds__(slab_rows_block(RES)) __attribute__((amdgpu_waves_per_eu(slab_rows_waves(RES))))
@@ -283,28 +284,62 @@ void k_slab_rows_fwd(const SlabArgs a, int g) {
   __shared__ __align__(16) cf rows[TR * LS];
   __shared__ cf stw[M];      // FFT table of length M
   __shared__ cf rtw[M + 1];  // W_RES^k, k in [0, M], for the r2c post-processing
-  const int s = RES / a.G, items = 3 * s * NT;
+  const int s = RES / a.G;
   constexpr int TC = slab_cols(RES);
+  __shared__ int list[LOAD ? 1 : kRowItems];  // this workgroup's live items: 4 tile + channel, or -1
   stage_table<BR>(stw, a.tw + M, M);
   stage_table<BR>(rtw, a.tw + RES, M + 1);
-  for (int it = blockIdx.x; it < items; it += gridDim.x) {
-    // the three channels of a tile 8 items apart, so on one XCD (the grid is
-    // a multiple of 8 wherever it is smaller than the items): its L2 serves
+  int items = 3 * s * NT;
+  if constexpr (!LOAD) {
+    // inclusive sums of the planes' live tiles, in the rows' room
+    int* const pre = reinterpret_cast<int*>(rows);
+    constexpr int PER = (RES + BR - 1) / BR;
+    for (int e = threadIdx.x; e < s; e += BR) pre[e] = __popcll(a.live[g * s + e]);
+    __syncthreads();
+    for (int d = 1; d < s; d <<= 1) {
+      int v[PER];
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const int e = (int)threadIdx.x + k * BR;
+        v[k] = e < s ? pre[e] + (e >= d ? pre[e - d] : 0) : 0;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const int e = (int)threadIdx.x + k * BR;
+        if (e < s) pre[e] = v[k];
+      }
+      __syncthreads();
+    }
+    const int nlive = pre[s - 1];
+    // the three channels of a tile 8 items apart, so on one XCD (the grid is a
+    // multiple of 8 wherever it is smaller than the items): its L2 serves
     // their reads of the tile's point records
-    int T, c;
-    if ((s * NT) % 8 == 0) {
-      c = (it >> 3) % 3;
-      T = (it >> 3) / 3 * 8 + (it & 7);
-    } else {
-      T = it % (s * NT);
-      c = it / (s * NT);
+    items = 3 * ((nlive + 7) & ~7);
+    for (int i = threadIdx.x; blockIdx.x + (int64_t)i * gridDim.x < items; i += BR) {
+      const int it = blockIdx.x + i * gridDim.x, r = (it >> 3) / 3 * 8 + (it & 7);
+      int lo = 0, hi = s - 1;  // the plane that holds live tile r
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (pre[mid] > r) hi = mid;
+        else lo = mid + 1;
+      }
+      uint64_t w = a.live[g * s + lo];
+      for (int k = r - (lo > 0 ? pre[lo - 1] : 0); k > 0 && w; --k) w &= w - 1;
+      list[i] = r < nlive ? 4 * (lo * NT + __ffsll((unsigned long long)w) - 1) + (it >> 3) % 3 : -1;
+    }
+    __syncthreads();
+  }
+  for (int it = blockIdx.x, i = 0; it < items; it += gridDim.x, ++i) {
+    int T = it % (s * NT), c = it / (s * NT);
+    if constexpr (!LOAD) {
+      if (list[i] < 0) continue;
+      T = list[i] >> 2;
+      c = list[i] & 3;
     }
     const int j0l = T / NT, a0 = (T % NT) * TR, j0 = g * s + j0l;
     Ranges R{};
-    if constexpr (!LOAD) {
-      if (!((a.live[j0] >> (T % NT)) & 1)) continue;
-      R = slab_ranges<RES, TR>(a.off, j0, a0);
-    }
+    if constexpr (!LOAD) R = slab_ranges<RES, TR>(a.off, j0, a0);
     // k2-tiled plane: element (j1, k2) at ((k2 / TC) RES + j1) TC + k2 % TC; the
     // loops below run tile by tile, so each tile's TR rows are one contiguous run
     cf* const out = a.A + ((int64_t)(3 * g + c) * s + j0l) * RES * HP + (int64_t)a0 * TC;
