@@ -341,7 +341,7 @@ __device__ __forceinline__ void scan_to_lds(const int* __restrict__ counts, int*
 // few workgroups run, so the three kernels above remain for larger clouds and
 // for 256^3 (us, two against three launches: 32^3 / 3k points 7.5 against 9.4,
 // 128^3 / 20k 9.1 against 10.5, and one launch's gap; 256^3 / 100k 19.5 against
-// 19.7).
+// 17.5).
 constexpr int kSortBlocks = 32;  // at most one row per lane of a wavefront
 constexpr int kSortThreads = 1024;
 constexpr int kSortPer = 4;  // points per thread at most
@@ -486,9 +486,18 @@ __device__ __forceinline__ float3 bwd_scalars(const double2* __restrict__ blockp
   constexpr int NW = (BLOCK + 63) / 64, W = BLOCK < 64 ? BLOCK : 64;
   __shared__ double wsum[2][NW];
   double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < nb; i += BLOCK) {
-    a += blockpart[i].x;
-    b += blockpart[i].y;
+  // eight loads in flight: one after the other they were a third of a B1
+  // workgroup's time at 512^3 (B1 127.6 -> 110.1 us; 23.2 -> 21.5 at 256^3)
+  constexpr int K = 8;
+  for (int i = threadIdx.x; i < nb; i += K * BLOCK) {
+    double2 v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = blockpart[i + k * BLOCK < nb ? i + k * BLOCK : i];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      a += i + k * BLOCK < nb ? v[k].x : 0.0;
+      b += i + k * BLOCK < nb ? v[k].y : 0.0;
+    }
   }
 #pragma unroll
   for (int d = W / 2; d > 0; d >>= 1) {
