@@ -2409,7 +2409,7 @@ static int debug_splat_res(Exec& x, const JobArg& job) {
   auto c = [](int v) { return [v](const JobArg&) { return v; }; };
   int rc = 0;
   rc |= seq_bin<RES, 1>(x, &job, 1);
-  // the splat of the production path: plane passes at 64 and 128, row passes elsewhere
+  // the splat of the production path: plane passes from 32 to 128, row passes elsewhere
   if constexpr (use_plane(RES))
     rc |= launch<1>(x, k_plane_splat_dbg<RES, 1>, (plane_wg<RES, 1>()), &job, 1, c(3 * RES));
   else
