@@ -19,6 +19,8 @@ def _ptr(t: torch.Tensor | None) -> int | None:
 
 
 def _device_index(dev: torch.device) -> int:
+    if dev.type != "cuda":  # the address of a host tensor must not reach a kernel
+        raise ValueError(f"Expected a cuda device, but got: {dev}")
     return dev.index if dev.index is not None else torch.cuda.current_device()
 
 

@@ -2,8 +2,13 @@
 import ctypes
 
 import pytest
+import torch
 
 from paper_2106_03452_amd import _lib
+from paper_2106_03452_amd import function as F
+from paper_2106_03452_amd import mesh as M
+from paper_2106_03452_amd import optimize as O
+from paper_2106_03452_amd import slab as S
 
 
 @pytest.mark.parametrize("res,points", [(7, 10), (1024, 10), (64, 0)])
@@ -30,3 +35,39 @@ def test_calls_without_a_context_are_refused_before_any_device_work():
     assert L.psr_marching_cubes_sized(n, n, 32, 0.0, n, n, n, 10, n, 10, n, n, n, n, n) == _lib.PSR_EINVAL
     assert L.psr_chamfer_f32(n, n, 10, n, 10, n, n, n, n, n, n, 0, n) == _lib.PSR_EINVAL
     assert L.psr_chamfer_backward_scaled(n, n, 10, n, 10, n, n, n, n, n) == _lib.PSR_EINVAL
+
+
+@pytest.fixture
+def no_device(monkeypatch):
+    """A device 0 whose context the library refuses: a call that gets that far
+    raises PSRError and launches nothing, here and where there is a GPU."""
+    context = type("Context", (), {"handle": None})()
+    monkeypatch.setattr(_lib, "context", lambda device=0: context)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0, raising=False)
+
+
+def _host_calls():
+    v, f, u = torch.rand(9, 3), torch.arange(6, dtype=torch.int32).reshape(2, 3), torch.rand(5, 3)
+    x, y, grid = torch.rand(6, 3), torch.rand(7, 3), torch.rand(8, 8, 8)
+    raw = lambda n: torch.zeros(n, dtype=torch.uint8)
+    mesh = M.Mesh(v, f, v, torch.arange(9, dtype=torch.int32), raw(M.state_bytes(8)), 8, 0.0)
+    return {
+        "sample": lambda: O.sample_raw(v, f, u),
+        "sample layer": lambda: O.SampleFunction.apply(v, f, u),
+        "chamfer": lambda: O.chamfer_raw(x, y),
+        "chamfer layer": lambda: O.ChamferFunction.apply(x, y),
+        "components": lambda: O.components(v, f),
+        "mesh backward": lambda: M.marching_cubes_backward(grid, mesh, v),
+        "slab": lambda: S.forward_raw(x, x, 16, 2.0, 1, torch.empty(16, 16, 16), raw(48),
+                                      raw(S.workspace_bytes(16, 6, 1))),
+        "status": lambda: F.status(raw(4096)),
+        "scalars": lambda: F.scalars(raw(4096)),
+    }
+
+
+@pytest.mark.parametrize("call", list(_host_calls()))
+def test_host_tensors_are_refused(no_device, call):
+    """Their addresses mean nothing to a kernel: refused as torch.cuda does, before the library is called."""
+    with pytest.raises(ValueError, match="cuda device"):
+        _host_calls()[call]()
