@@ -46,18 +46,19 @@ def sample_raw(verts, faces, u, vnormals=None, face_weight=None):
     """(points, normals or None, face, bary) of the samples drawn with u [M, 3]."""
     dev = verts.device
     L = _lib.lib()
+    # copies of strided arguments have names, so that they live until the call
+    verts, faces, u = verts.detach().contiguous(), faces.contiguous(), u.contiguous()
+    vnormals = vnormals.contiguous() if vnormals is not None else None
+    face_weight = face_weight.contiguous() if face_weight is not None else None
     nv, nf, m = int(verts.shape[0]), int(faces.shape[0]), int(u.shape[0])
     ws = torch.empty(_size(L.psr_mesh_sample_workspace_bytes, nf), dtype=torch.uint8, device=dev)
     pts = torch.empty((m, 3), dtype=torch.float32, device=dev)
     nrm = torch.empty((m, 3), dtype=torch.float32, device=dev) if vnormals is not None else None
     face = torch.empty((m,), dtype=torch.int32, device=dev)
     bary = torch.empty((m, 3), dtype=torch.float32, device=dev)
-    _lib.check(L.psr_mesh_sample(_ctx(dev).handle, _p(verts.detach().contiguous()),
-                                 _p(vnormals.contiguous()) if vnormals is not None else None, nv,
-                                 _p(faces.contiguous()), nf,
-                                 _p(face_weight.contiguous()) if face_weight is not None else None,
-                                 _p(u.contiguous()), m, _p(pts), _p(nrm), _p(face), _p(bary), _p(ws),
-                                 ws.numel(), _st(dev)), "psr_mesh_sample")
+    _lib.check(L.psr_mesh_sample(_ctx(dev).handle, _p(verts), _p(vnormals), nv, _p(faces), nf, _p(face_weight), _p(u), m,
+                                 _p(pts), _p(nrm), _p(face), _p(bary), _p(ws), ws.numel(), _st(dev)),
+               "psr_mesh_sample")
     return pts, nrm, face, bary
 
 
@@ -75,9 +76,10 @@ class SampleFunction(torch.autograd.Function):
     def backward(ctx, dp):
         faces, face, bary = ctx.saved_tensors
         dev = faces.device
+        dp = dp.contiguous()
         dv = torch.empty((ctx.nv, 3), dtype=torch.float32, device=dev)
         _lib.check(_lib.lib().psr_mesh_sample_backward(_ctx(dev).handle, _p(faces), ctx.nv, _p(face), _p(bary),
-                                                       _p(dp.contiguous()), int(face.shape[0]), _p(dv), _st(dev)),
+                                                       _p(dp), int(face.shape[0]), _p(dv), _st(dev)),
                    "psr_mesh_sample_backward")
         return dv, None, None
 
@@ -86,6 +88,7 @@ def chamfer_raw(x, y, dtype=torch.float64):
     """(loss as a 0-d tensor of float64 or float32, nn_x, d_x, nn_y, d_y)."""
     dev = x.device
     L = _lib.lib()
+    x, y = x.detach().contiguous(), y.contiguous()
     nx, ny = int(x.shape[0]), int(y.shape[0])
     ws = torch.empty(_size(L.psr_chamfer_workspace_bytes, nx, ny), dtype=torch.uint8, device=dev)
     nnx = torch.empty((nx,), dtype=torch.int32, device=dev)
@@ -94,8 +97,8 @@ def chamfer_raw(x, y, dtype=torch.float64):
     dy = torch.empty((ny,), dtype=torch.float32, device=dev)
     loss = torch.empty((), dtype=dtype, device=dev)
     fn = L.psr_chamfer if dtype == torch.float64 else L.psr_chamfer_f32
-    _lib.check(fn(_ctx(dev).handle, _p(x.detach().contiguous()), nx, _p(y.contiguous()), ny, _p(nnx), _p(dx), _p(nny),
-                  _p(dy), _p(loss), _p(ws), ws.numel(), _st(dev)), "psr_chamfer")
+    _lib.check(fn(_ctx(dev).handle, _p(x), nx, _p(y), ny, _p(nnx), _p(dx), _p(nny), _p(dy), _p(loss), _p(ws),
+                  ws.numel(), _st(dev)), "psr_chamfer")
     return loss, nnx, dx, nny, dy
 
 
@@ -125,9 +128,10 @@ class ChamferFunction(torch.autograd.Function):
     def backward(ctx, g):
         x, y, nnx, nny = ctx.saved_tensors
         dev = x.device
+        y = y.contiguous()
         gx = torch.empty_like(x)
         scale = _plain_scalar(g, dev)
-        _lib.check(_lib.lib().psr_chamfer_backward_scaled(_ctx(dev).handle, _p(x), int(x.shape[0]), _p(y.contiguous()),
+        _lib.check(_lib.lib().psr_chamfer_backward_scaled(_ctx(dev).handle, _p(x), int(x.shape[0]), _p(y),
                                                           int(y.shape[0]), _p(nnx), _p(nny), scale, _p(gx), _st(dev)),
                    "psr_chamfer_backward")
         return gx if scale else gx * g, None
@@ -139,9 +143,10 @@ def components(verts, faces, largest: bool = True):
     L = _lib.lib()
     nv, nf = int(verts.shape[0]), int(faces.shape[0])
     ws = torch.empty(_size(L.psr_mesh_components_workspace_bytes, nv, nf), dtype=torch.uint8, device=dev)
+    verts, faces = verts.detach().contiguous(), faces.contiguous()
     lab = torch.empty((nv,), dtype=torch.int32, device=dev)
     w = torch.empty((nf,), dtype=torch.float32, device=dev) if largest else None
-    _lib.check(L.psr_mesh_components(_ctx(dev).handle, _p(verts.detach().contiguous()), nv, _p(faces.contiguous()),
+    _lib.check(L.psr_mesh_components(_ctx(dev).handle, _p(verts), nv, _p(faces),
                                      nf, _p(lab), _p(w), _p(ws), ws.numel(), _st(dev)),
                "psr_mesh_components")
     return lab, w

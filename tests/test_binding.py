@@ -1,5 +1,6 @@
 """Argument handling of the binding, without a device."""
 import ctypes
+import weakref
 
 import pytest
 import torch
@@ -71,3 +72,53 @@ def test_host_tensors_are_refused(no_device, call):
     """Their addresses mean nothing to a kernel: refused as torch.cuda does, before the library is called."""
     with pytest.raises(ValueError, match="cuda device"):
         _host_calls()[call]()
+
+
+class _HeldArguments:
+    """Stands in for the library in optimize: a call checks that every tensor
+    whose address it was given is still alive, and keeps its arguments."""
+
+    def __init__(self, monkeypatch):
+        self.refs, self.seen, real = [], [], _lib.lib()
+        def address(t):
+            if t is not None:
+                self.refs.append(weakref.ref(t))
+            return None if t is None else t.data_ptr()
+        class Library:
+            def __getattr__(lib, name):
+                return getattr(real, name) if name.endswith("_bytes") else lambda *args: self.call(name, args)
+        monkeypatch.setattr(O, "_p", address)
+        monkeypatch.setattr(O, "_st", lambda dev: 0)
+        monkeypatch.setattr(O, "_ctx", lambda dev: type("Context", (), {"handle": None})())
+        monkeypatch.setattr(O._lib, "lib", lambda: Library())
+
+    def call(self, name, args):
+        assert all(r() is not None for r in self.refs), f"{name}: an argument was freed before the call"
+        self.refs.clear()
+        self.seen.append((name, args))
+        return 0
+
+
+def _strided(t):
+    return t.t().contiguous().t()
+
+
+@pytest.mark.parametrize("call", ["sample", "sample backward", "chamfer", "chamfer backward", "components"])
+def test_copies_of_strided_arguments_live_until_the_call(monkeypatch, call):
+    """A copy freed while the next one is made can share its memory with it."""
+    held = _HeldArguments(monkeypatch)
+    v, f, u = _strided(torch.rand(9, 3)), _strided(torch.arange(9, dtype=torch.int32).reshape(3, 3)), _strided(torch.rand(9, 3))
+    x, y = _strided(torch.rand(7, 3)), _strided(torch.rand(7, 3))
+    if call == "sample":
+        O.sample_raw(v, f, u, vnormals=_strided(torch.rand(9, 3)), face_weight=torch.ones(6)[::2])
+    elif call == "sample backward":
+        p = O.SampleFunction.apply(v.requires_grad_(True), f, u)
+        torch.autograd.grad(p, v, _strided(torch.rand(9, 3)))
+    elif call == "chamfer":
+        O.chamfer_raw(x, y)
+    elif call == "chamfer backward":
+        loss = O.ChamferFunction.apply(x.requires_grad_(True), y)
+        torch.autograd.grad(loss, x)
+    else:
+        O.components(v, f)
+    assert len(held.seen) == (2 if "backward" in call else 1)
