@@ -67,6 +67,7 @@ class SampleFunction(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, verts, faces, u):
+        faces = faces.contiguous()  # the backward's scatter goes through the same rows
         pts, _, face, bary = sample_raw(verts, faces, u)
         ctx.save_for_backward(faces, face, bary)
         ctx.nv = int(verts.shape[0])

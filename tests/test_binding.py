@@ -122,3 +122,25 @@ def test_copies_of_strided_arguments_live_until_the_call(monkeypatch, call):
     else:
         O.components(v, f)
     assert len(held.seen) == (2 if "backward" in call else 1)
+
+
+def _ints(address, n):
+    return list((ctypes.c_int32 * n).from_address(address))
+
+
+@pytest.mark.parametrize("faces", ["transposed", "columns", "contiguous"])
+def test_sampling_backward_reads_the_faces_of_the_forward(monkeypatch, faces):
+    """The backward's scatter indexes the vertices through the faces: rows of a
+    strided array must reach it as the forward saw them."""
+    held = _HeldArguments(monkeypatch)
+    plain = torch.tensor([[0, 1, 2], [3, 4, 5], [6, 7, 8], [2, 4, 6]], dtype=torch.int32)
+    wide = torch.cat([plain, torch.full((4, 2), 1 << 30, dtype=torch.int32)], 1)
+    f = {"transposed": _strided(plain), "columns": wide[:, :3], "contiguous": plain}[faces]
+    rows = []
+    def call(name, args, base=held.call):
+        rows.append(_ints(args[4 if name == "psr_mesh_sample" else 1], 12))
+        return base(name, args)
+    monkeypatch.setattr(held, "call", call)
+    v = torch.rand(9, 3).requires_grad_(True)
+    torch.autograd.grad(O.SampleFunction.apply(v, f, torch.rand(5, 3)), v, torch.ones(5, 3))
+    assert rows == [plain.reshape(-1).tolist()] * 2

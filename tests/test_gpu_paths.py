@@ -84,6 +84,29 @@ def test_chamfer_gradient_takes_the_factor_in_or_out(dev):
     assert dc[0] == 0 and abs(float(dc[1]) - ref.sum()) <= 9000 * tol
 
 
+def test_strided_arguments_give_the_contiguous_results(dev):
+    """Equally sized strided clouds, and faces that are columns of a wider array."""
+    from paper_2106_03452_amd import optimize as O
+    announce("strided arguments of sampling and chamfer")
+    rng = np.random.default_rng(8)
+    x, y = (to_dev(rng.random((3000, 3)), dev) for _ in range(2))
+    v, u = (to_dev(rng.random((3000, 3)), dev) for _ in range(2))
+    f = torch.from_numpy(rng.integers(0, 3000, (5000, 3)).astype(np.int32)).to(dev)
+    wide = torch.cat([f, torch.full_like(f, 2999)], 1)
+    strided = lambda t: t.t().contiguous().t()
+    for a, b in zip(O.chamfer_raw(strided(x), strided(y)), O.chamfer_raw(x, y)):
+        assert torch.equal(a, b)
+    for a, b in zip(O.sample_raw(strided(v), wide[:, :3], strided(u), strided(y)), O.sample_raw(v, f, u, y)):
+        assert torch.equal(a, b)
+    grads = []
+    for faces, g in ((f, y), (wide[:, :3], strided(y)), (strided(f), y)):
+        w = v.clone().requires_grad_(True)
+        grads.append(torch.autograd.grad(O.SampleFunction.apply(w, faces, u), w, g)[0])
+    # a vertex gets about five terms of up to 1 by float atomics, in any order
+    for g in grads[1:]:
+        assert float((g - grads[0]).abs().max()) <= 1e-5
+
+
 def _cloud(kind, points, seed=0):
     """Clouds that reach few planes and row tiles, or all of them."""
     rng = np.random.default_rng(seed)
