@@ -101,13 +101,15 @@ struct psr_ctx {
   std::mutex kmu;
   std::vector<KTab> ktabs;
   // Mesh totals on their way to the host: device-visible host memory and an
-  // event, one pair per call in flight (psr_marching_cubes_sized), reused.
+  // event, one pair per call in flight (psr_marching_cubes_sized), reused. A
+  // linked list: giving a pair back allocates nothing, so it cannot throw.
   struct Totals {
-    psr::mc::McHeader* host;
-    hipEvent_t counted;
+    psr::mc::McHeader* host = nullptr;
+    hipEvent_t counted = nullptr;
+    Totals* next = nullptr;
   };
   std::mutex tmu;
-  std::vector<Totals> totals;
+  Totals* totals = nullptr;
 };
 
 namespace {
@@ -230,30 +232,38 @@ int point_source_table(psr_ctx* ctx, int res, float sigma, hipStream_t stream, c
   return PSR_OK;
 }
 
-// A pair of the context's pool, or a new one; false if it cannot be made.
-bool take_totals(psr_ctx* ctx, psr_ctx::Totals& t) {
+void free_totals(psr_ctx::Totals* t) {
+  if (t->counted) (void)hipEventDestroy(t->counted);
+  if (t->host) (void)hipHostFree(t->host);
+  delete t;
+}
+
+// A pair of the context's pool, or a new one; null if it cannot be made.
+psr_ctx::Totals* take_totals(psr_ctx* ctx) {
   {
     std::lock_guard<std::mutex> lk(ctx->tmu);
-    if (!ctx->totals.empty()) {
-      t = ctx->totals.back();
-      ctx->totals.pop_back();
-      return true;
+    if (psr_ctx::Totals* t = ctx->totals) {
+      ctx->totals = t->next;
+      return t;
     }
   }
+  psr_ctx::Totals* t = new (std::nothrow) psr_ctx::Totals();
+  if (!t) return nullptr;
   void* p = nullptr;
-  if (hipHostMalloc(&p, sizeof(psr::mc::McHeader), hipHostMallocCoherent) != hipSuccess) return false;
-  t.host = static_cast<psr::mc::McHeader*>(p);
-  if (hipEventCreateWithFlags(&t.counted, hipEventDisableTiming) != hipSuccess) {
-    (void)hipHostFree(p);
-    return false;
+  if (hipHostMalloc(&p, sizeof(psr::mc::McHeader), hipHostMallocCoherent) == hipSuccess) {
+    t->host = static_cast<psr::mc::McHeader*>(p);
+    if (hipEventCreateWithFlags(&t->counted, hipEventDisableTiming) == hipSuccess) return t;
+    t->counted = nullptr;
   }
-  return true;
+  free_totals(t);
+  return nullptr;
 }
 
 // The pool holds at most as many pairs as calls have run at once.
-void give_totals(psr_ctx* ctx, const psr_ctx::Totals& t) {
+void give_totals(psr_ctx* ctx, psr_ctx::Totals* t) {
   std::lock_guard<std::mutex> lk(ctx->tmu);
-  ctx->totals.push_back(t);
+  t->next = ctx->totals;
+  ctx->totals = t;
 }
 
 const char* const kStageNames[psr::NUM_STAGES] = {
@@ -325,9 +335,9 @@ int psr_ctx_destroy(psr_ctx* ctx) {
   delete ctx->timers;
   if (ctx->tw) (void)hipFree(ctx->tw);
   for (auto& k : ctx->ktabs) (void)hipFree(k.table);
-  for (auto& t : ctx->totals) {
-    (void)hipEventDestroy(t.counted);
-    (void)hipHostFree(t.host);
+  while (psr_ctx::Totals* t = ctx->totals) {
+    ctx->totals = t->next;
+    free_totals(t);
   }
   delete ctx;
   return PSR_OK;
@@ -601,18 +611,18 @@ int psr_marching_cubes_sized(psr_ctx* ctx, const float* chi, int res, float iso,
   if ((vcap > 0 && (!verts || !normals)) || (tcap > 0 && !tris)) return PSR_EINVAL;
   if (!aligned(state, 256) || !aligned(chi, 4)) return PSR_EINVAL;
   DeviceGuard g(ctx->device);
-  psr_ctx::Totals t;
-  if (!take_totals(ctx, t)) return PSR_ENOMEM;
+  psr_ctx::Totals* const t = take_totals(ctx);
+  if (!t) return PSR_ENOMEM;
   psr::mc::McOut out{verts, normals, edges, tris, vcap, tcap};
-  int rc = psr::mc::run_forward(res, chi, iso, psr::mc::state_view(state, res), out, stream, t.host, t.counted)
+  int rc = psr::mc::run_forward(res, chi, iso, psr::mc::state_view(state, res), out, stream, t->host, t->counted)
                ? PSR_EDEVICE
                : PSR_OK;
-  if (rc == PSR_OK && hipEventSynchronize(t.counted) != hipSuccess) rc = PSR_EDEVICE;
+  if (rc == PSR_OK && hipEventSynchronize(t->counted) != hipSuccess) rc = PSR_EDEVICE;
   if (rc != PSR_OK) {
     // a kernel of this call may still write the pair: it does not go back to the pool
     return rc;
   }
-  const psr::mc::McHeader h = *t.host;
+  const psr::mc::McHeader h = *t->host;
   give_totals(ctx, t);
   if (nverts) *nverts = h.nv;
   if (ntris) *ntris = h.nt;
