@@ -309,7 +309,8 @@ int psr_marching_cubes(psr_ctx* ctx, const float* chi, int res, float iso, float
 /* psr_marching_cubes and its totals in one call: *nverts, *ntris and *status
  * (each may be NULL) as psr_mc_counts gives them. The host waits only for the
  * counting half of the work; the vertices and triangles are written on `stream`
- * after the call returns. Not for stream capture (it waits). */
+ * after the call returns. A stream that is being captured is refused
+ * (PSR_EDEVICE, nothing recorded): the call waits. */
 int psr_marching_cubes_sized(psr_ctx* ctx, const float* chi, int res, float iso, float* verts, float* normals,
                              int32_t* edges, int64_t vcap, int32_t* tris, int64_t tcap, void* state, int64_t* nverts,
                              int64_t* ntris, int* status, hipStream_t stream);

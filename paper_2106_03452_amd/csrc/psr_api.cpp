@@ -110,6 +110,9 @@ struct psr_ctx {
   };
   std::mutex tmu;
   Totals* totals = nullptr;
+  // pairs of calls that failed after their launches, whose kernels may still
+  // write them: not used again, freed with the context
+  Totals* lost_totals = nullptr;
 };
 
 namespace {
@@ -259,11 +262,24 @@ psr_ctx::Totals* take_totals(psr_ctx* ctx) {
   return nullptr;
 }
 
-// The pool holds at most as many pairs as calls have run at once.
-void give_totals(psr_ctx* ctx, psr_ctx::Totals* t) {
+// To the pool, which holds at most as many pairs as calls have run at once, or
+// to the pairs that wait for the context's end.
+void give_totals(psr_ctx* ctx, psr_ctx::Totals* t, bool lost) {
   std::lock_guard<std::mutex> lk(ctx->tmu);
-  t->next = ctx->totals;
-  ctx->totals = t;
+  psr_ctx::Totals*& list = lost ? ctx->lost_totals : ctx->totals;
+  t->next = list;
+  list = t;
+}
+
+// Whether the stream records a graph. (An error is not this question's answer:
+// the launches that follow meet it themselves.)
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
 }
 
 const char* const kStageNames[psr::NUM_STAGES] = {
@@ -335,9 +351,12 @@ int psr_ctx_destroy(psr_ctx* ctx) {
   delete ctx->timers;
   if (ctx->tw) (void)hipFree(ctx->tw);
   for (auto& k : ctx->ktabs) (void)hipFree(k.table);
-  while (psr_ctx::Totals* t = ctx->totals) {
-    ctx->totals = t->next;
-    free_totals(t);
+  if (ctx->lost_totals) (void)hipDeviceSynchronize();
+  for (psr_ctx::Totals** list : {&ctx->totals, &ctx->lost_totals}) {
+    while (psr_ctx::Totals* t = *list) {
+      *list = t->next;
+      free_totals(t);
+    }
   }
   delete ctx;
   return PSR_OK;
@@ -611,6 +630,7 @@ int psr_marching_cubes_sized(psr_ctx* ctx, const float* chi, int res, float iso,
   if ((vcap > 0 && (!verts || !normals)) || (tcap > 0 && !tris)) return PSR_EINVAL;
   if (!aligned(state, 256) || !aligned(chi, 4)) return PSR_EINVAL;
   DeviceGuard g(ctx->device);
+  if (capturing(stream)) return PSR_EDEVICE;  // the wait below cannot be recorded
   psr_ctx::Totals* const t = take_totals(ctx);
   if (!t) return PSR_ENOMEM;
   psr::mc::McOut out{verts, normals, edges, tris, vcap, tcap};
@@ -618,12 +638,9 @@ int psr_marching_cubes_sized(psr_ctx* ctx, const float* chi, int res, float iso,
                ? PSR_EDEVICE
                : PSR_OK;
   if (rc == PSR_OK && hipEventSynchronize(t->counted) != hipSuccess) rc = PSR_EDEVICE;
-  if (rc != PSR_OK) {
-    // a kernel of this call may still write the pair: it does not go back to the pool
-    return rc;
-  }
-  const psr::mc::McHeader h = *t->host;
-  give_totals(ctx, t);
+  const psr::mc::McHeader h = rc == PSR_OK ? *t->host : psr::mc::McHeader{};
+  give_totals(ctx, t, rc != PSR_OK);
+  if (rc != PSR_OK) return rc;
   if (nverts) *nverts = h.nv;
   if (ntris) *ntris = h.nt;
   if (status) *status = h.status ? PSR_ETOOBIG : PSR_OK;

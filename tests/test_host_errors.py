@@ -59,3 +59,35 @@ assert rc == 0, rc
 ctx.close()
 assert (st.host_live, st.event_live) == (0, 0)
 """)
+
+
+def test_mesh_totals_of_failed_calls_are_freed_with_the_context(host_hip):
+    """A kernel of a failed call may still write its pair: kept from the pool,
+    and freed once the device is idle."""
+    _run(host_hip, """
+assert mesh() == 0
+st.fail_event_sync = 1
+for _ in range(3):
+    assert mesh() == _lib.PSR_EDEVICE
+st.fail_event_sync = 0
+live = st.host_live
+assert mesh() == 0 and mesh() == 0  # a new pair, reused
+assert st.host_live == live + 1, (st.host_live, live)
+ctx.close()
+assert (st.host_live, st.event_live, st.host_frees_unsynced) == (0, 0, 0), (st.host_live, st.event_live)
+""")
+
+
+def test_sized_call_under_capture_takes_nothing(host_hip):
+    """Refused as before, but before anything is recorded or taken: however
+    often it happens, nothing piles up."""
+    _run(host_hip, """
+st.capturing = 1
+for _ in range(50):
+    assert mesh() == _lib.PSR_EDEVICE
+assert st.launches == 0 and st.host_live == 0 and st.event_live == 0, (st.launches, st.host_live)
+st.capturing = 0
+assert mesh() == 0
+ctx.close()
+assert (st.host_live, st.event_live) == (0, 0)
+""")
