@@ -434,10 +434,12 @@ int psr_opt_step_workspace_bytes(int res, int64_t npoints, int64_t ntarget, int6
  * *loss (device double) receives the Chamfer loss; mesh_counts (host,
  * int64_t[2], may be NULL) the mesh's vertices and triangles. The same
  * kernels as the separate calls, in the same order. Waits once, for the
- * mesh size. Returns PSR_ETOOBIG with points, normals and
- * moments untouched when the mesh exceeds vcap or tcap (mesh_counts then
- * holds the sizes needed), PSR_EDEGENERATE when the mesh is empty. Calls
- * that overlap on one workspace race. */
+ * mesh size; the rest of the step runs on `stream` after the call returns
+ * and uses the workspace until then. Returns PSR_ETOOBIG with points, normals
+ * and moments untouched when the mesh exceeds vcap or tcap (mesh_counts then
+ * holds the sizes needed), PSR_EDEGENERATE when the mesh is empty; either
+ * after waiting for the stream, so that nothing uses the workspace any more.
+ * Calls that overlap on one workspace race. */
 int psr_opt_step(psr_ctx* ctx, float* points, float* normals, int64_t npoints, float* m_points, float* v_points,
                  float* m_normals, float* v_normals, int64_t t, float lr, float beta1, float beta2, float eps,
                  const float* target, int64_t ntarget, const float* u, int64_t nsamples, int res, float sigma,

@@ -855,8 +855,12 @@ int psr_opt_step(psr_ctx* ctx, float* points, float* normals, int64_t npoints, f
     mesh_counts[0] = nv;
     mesh_counts[1] = nt;
   }
-  if (st != PSR_OK || nv > vcap || nt > tcap) return PSR_ETOOBIG;
-  if (nv == 0 || nt == 0) return PSR_EDEGENERATE;
+  const bool too_big = st != PSR_OK || nv > vcap || nt > tcap;
+  if (too_big || nv == 0 || nt == 0) {
+    // the mesh is still being written: the step ends with its workspace idle
+    if (hipStreamSynchronize(stream) != hipSuccess) return PSR_EDEVICE;
+    return too_big ? PSR_ETOOBIG : PSR_EDEGENERATE;
+  }
   // forward chain: samples of the mesh, Chamfer loss (main Eq. 5)
   if ((rc = psr_mesh_sample(ctx, f32(L.verts), nullptr, nv, i32(L.tris), nt, nullptr, u, nsamples, f32(L.x), nullptr,
                             i32(L.face), f32(L.bary), b + L.sws, L.sws_bytes, stream)) != PSR_OK)

@@ -91,3 +91,21 @@ assert mesh() == 0
 ctx.close()
 assert (st.host_live, st.event_live) == (0, 0)
 """)
+
+
+@pytest.mark.parametrize("verts,tris,code", [(70000, 600, "PSR_ETOOBIG"), (300, 70000, "PSR_ETOOBIG"),
+                                             (0, 0, "PSR_EDEGENERATE")])
+def test_refused_optimisation_step_leaves_nothing_running(host_hip, verts, tris, code):
+    """A step that ends at its mesh's size returns with the workspace idle: its
+    caller makes a larger one or gives up, and may free this one."""
+    _run(host_hip, f"st.mesh_verts, st.mesh_tris, code = {verts}, {tris}, _lib.{code}" + """
+n = ctypes.c_size_t(0)
+assert L.psr_opt_step_workspace_bytes(32, 100, 100, 100, 65536, 65536, ctypes.byref(n)) == 0
+ws = ctypes.create_string_buffer(n.value + 256)
+w = (ctypes.addressof(ws) + 255) & ~255
+counts = (ctypes.c_int64 * 2)()
+rc = L.psr_opt_step(ctx.handle, at, at, 100, at, at, at, at, 1, 1e-3, 0.9, 0.999, 1e-8, at, 100, at, 100, 32, 2.0,
+                    65536, 65536, at, counts, w, n, None)
+assert rc == code and list(counts) == [st.mesh_verts, st.mesh_tris], rc
+assert st.launches > 0 and st.pending == 0, (st.launches, st.pending)
+""")
