@@ -44,14 +44,19 @@ def marching_cubes(chi: torch.Tensor, iso: float = 0.0, ctx: _lib.Context | None
     """Mesh of the level chi = iso of a (res, res, res) float32 CUDA grid.
 
     Runs the library call with a capacity guess and, if the mesh is larger,
-    once more with the exact sizes (the call waits for the mesh size, not for
-    the mesh)."""
+    once more with the exact sizes. The call waits for the mesh size, not for
+    the mesh: like the result of any operation, the mesh is complete for work
+    that follows on the current stream, and another stream or library has to
+    wait for this one first (an event, or a synchronisation)."""
     if not chi.is_cuda or chi.dtype != torch.float32 or chi.dim() != 3 or len(set(chi.shape)) != 1:
         raise ValueError("chi must be a cubic CUDA float32 grid")
-    chi = chi.detach().contiguous()
-    res = int(chi.shape[0])
     dev = chi.device
     ctx = ctx or _lib.context(_device_index(dev))
+    # read after the call returns: a grid that was allocated on another stream
+    # must not be handed out again before this stream is past it
+    chi.record_stream(torch.cuda.current_stream(dev))
+    chi = chi.detach().contiguous()
+    res = int(chi.shape[0])
     L = _lib.lib()
     state = torch.empty(state_bytes(res), dtype=torch.uint8, device=dev)
     vcap, tcap = capacity or (max(4096, 8 * res * res), max(8192, 16 * res * res))
@@ -114,5 +119,9 @@ class MarchingCubesFunction(torch.autograd.Function):
 
 
 def mesh(chi: torch.Tensor, iso: float = 0.0):
-    """(verts, faces, normals) of the level chi = iso; verts carry gradients to chi."""
+    """(verts, faces, normals) of the level chi = iso; verts carry gradients to chi.
+
+    The call returns once the mesh's size is known, while the mesh is still being
+    written on the current stream (see :func:`marching_cubes`): a consumer on
+    another stream, or outside PyTorch, waits for this stream first."""
     return MarchingCubesFunction.apply(chi, iso)

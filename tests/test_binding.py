@@ -144,3 +144,34 @@ def test_sampling_backward_reads_the_faces_of_the_forward(monkeypatch, faces):
     v = torch.rand(9, 3).requires_grad_(True)
     torch.autograd.grad(O.SampleFunction.apply(v, f, torch.rand(5, 3)), v, torch.ones(5, 3))
     assert rows == [plain.reshape(-1).tolist()] * 2
+
+
+class _OnDevice(torch.Tensor):
+    """A host tensor that passes for one of the device and notes the streams it is recorded on."""
+
+    streams = []
+    is_cuda = property(lambda self: True)
+
+    def record_stream(self, stream):
+        self.streams.append((self.data_ptr(), stream))
+
+
+@pytest.mark.parametrize("strided", [False, True])
+def test_mesh_holds_its_grid_until_the_stream_is_done(monkeypatch, strided):
+    """The call returns while the mesh is being written from the grid: a grid of
+    another stream must not be reused before this stream has read it."""
+    def sized(*args):
+        args[11]._obj.value, args[12]._obj.value, args[13]._obj.value = 4, 5, 0
+        return 0
+    monkeypatch.setattr(M, "_device_index", lambda dev: 0)
+    monkeypatch.setattr(M, "_stream", lambda dev: 0)
+    monkeypatch.setattr(M._lib, "context", lambda device: type("Context", (), {"handle": None})())
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev=None: "current")
+    M.state_bytes(8)
+    monkeypatch.setattr(M._lib, "lib", lambda: type("Library", (), {"psr_marching_cubes_sized": staticmethod(sized)}))
+    chi = torch.rand(8, 8, 8)
+    chi = (chi.permute(2, 1, 0) if strided else chi).as_subclass(_OnDevice)
+    _OnDevice.streams.clear()
+    mesh = M.marching_cubes(chi)
+    assert (mesh.verts.shape[0], mesh.faces.shape[0]) == (4, 5)
+    assert (chi.data_ptr(), "current") in _OnDevice.streams
