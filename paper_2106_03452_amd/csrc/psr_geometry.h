@@ -54,6 +54,11 @@ __host__ __device__ constexpr int tile_rows(int res) {
   return imin(imin(res, (res == 256 ? 256 : PSR_ROW_THREADS) / plan_TPL(res / 2)),
               (res >= PSR_PLANE_SPLIT_MIN && res <= 128) ? res / 2 : res);
 }
+// Plane passes: parts per plane (one workgroup each), as many chunks of rows as
+// the forward direction takes a plane in, and the FP64 sums that a single
+// backward's first pass leaves (one per plane and chunk) and its second adds.
+__host__ __device__ constexpr int plane_parts(int res) { return res >= PSR_PLANE_SPLIT_MIN ? 2 : 1; }
+__host__ __device__ constexpr int plane_sums(int res) { return res * plane_parts(res); }
 __host__ __device__ constexpr int rows_block(int res) { return tile_rows(res) * plan_TPL(res / 2); }
 // Workgroup size of the row passes. Up to 32 a row tile is the whole plane
 // and its transforms take one thread per row (res threads); the workgroup

@@ -976,7 +976,7 @@ __device__ __forceinline__ void b_bwd_axis0(const cf* __restrict__ in, cf* __res
       LiveBits<RES> lb;  // W is zero, and was not written, on the planes no point reaches
       lb.load(livebits);
       y.template fetch<true>(in + (int64_t)RES * H * RES + (int64_t)k2 * RES + a0, (int64_t)H * RES, lb);
-      x.axpy(bwd_scalars<j0_block(RES)>(bpart, RES, hdr, bs, bid == 0).z, y);
+      x.axpy(bwd_scalars<j0_block(RES)>(bpart, plane_sums(RES), hdr, bs, bid == 0).z, y);
     }
     x.put(rows);
     fft<RES, -1, false, true, false, LEAN>(h, rows + l * LS, lt, stw);
@@ -1303,7 +1303,7 @@ __host__ __device__ constexpr int plane_threads(int maxj) { return maxj == 1 ? 5
 template <int RES, int TMIN = 256>
 struct Plane {
   static constexpr int M = RES / 2, H = M + 1;
-  static constexpr int KP = RES >= PSR_PLANE_SPLIT_MIN ? 2 : 1;  // parts per plane
+  static constexpr int KP = plane_parts(RES);
   static constexpr int NCOL = M / KP;            // packed columns per part (forward) / per round (inverse)
   static constexpr int TPL = plan_TPL(RES);      // threads per j1 line
   static constexpr int BLOCK = NCOL * TPL;       // threads of the transforms
@@ -1416,6 +1416,8 @@ __device__ __forceinline__ void b_plane_fwd(const PointRec* __restrict__ sorted,
   constexpr int M = PL::M, H = PL::H, KP = PL::KP, NCOL = PL::NCOL, TPL = PL::TPL, RC = PL::RC;
   constexpr int NCHUNK = PL::NCHUNK, LSC = PL::LSC, BLOCK = PL::THREADS;
   constexpr int NSET = MODE == PF_BWDH ? 1 : (MODE == PF_BWDS ? 2 : 3);
+  static_assert(MODE != PF_BWDS || (RES * NCHUNK == plane_sums(RES) && plane_sums(RES) <= kRedBlocks),
+                "B3 adds a sum per plane and chunk");
   constexpr int VPC = 16 / NCHUNK;  // register elements filled per chunk
   constexpr int64_t CH = (int64_t)H * RES * RES;
   __shared__ __align__(16) cf buf[PL::SLOTS];
@@ -1994,7 +1996,7 @@ __host__ __device__ constexpr int norm_blocks(int res) {
 }
 // workgroups of the forward gather (P45 or P5), one FP64 sum each
 __host__ __device__ constexpr int gather_wgs(int res) {
-  return use_plane_p45(res) ? res * (res >= PSR_PLANE_SPLIT_MIN ? 2 : 1) : res * row_tiles(res);
+  return use_plane_p45(res) ? res * plane_parts(res) : res * row_tiles(res);
 }
 
 #define PSR_JOB(RES)                                                  \
