@@ -19,10 +19,16 @@ SampleLayout sample_layout(int64_t nfaces);
 // counting sort, the sorted points (x, y, z, original index bits) and the
 // bounding box of every tile of kNnTile sorted points.
 constexpr int kNnTile = 64;  // sorted points per tile
+// Clouds that the two-launch sort takes: its counts, positions and indices are
+// 16-bit, and its workgroups hold all keys, kNnSortPairs pairs per thread.
+constexpr int kNnSortPairs = 16;
+constexpr int kNnSmall = 2 * 1024 * kNnSortPairs;
+constexpr int kNnSmallBits = 4;  // 16^3 cell ends
+constexpr bool nn_small(int64_t nx, int64_t ny) { return nx <= kNnSmall && ny <= kNnSmall; }
 // 2^b cells per axis whose ends are kept: about four or more points per cell
-inline int nn_cell_bits(int64_t nx, int64_t ny) {
-  const int64_t n = nx > ny ? nx : ny;
-  return n <= 32768 ? 4 : (n <= 262144 ? 5 : 6);
+constexpr int nn_cell_bits(int64_t nx, int64_t ny) {
+  if (nn_small(nx, ny)) return kNnSmallBits;
+  return nx <= 262144 && ny <= 262144 ? 5 : 6;
 }
 struct NnLayout {
   int cell_bits;

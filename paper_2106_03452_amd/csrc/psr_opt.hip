@@ -350,11 +350,10 @@ __global__ __launch_bounds__(64) void k_nn_box(const float4* __restrict__ sx, in
 // as fine per axis as the cell ends kept for the search, go to the nn outputs,
 // which the search overwrites; one workgroup computing all of its cloud's keys
 // is bound by its own arithmetic (12 of 26 us for 20000 points).
-constexpr int kNnSmall = 32768;                           // indices and positions fit 16 bits
-constexpr int kNnSmallBits = 4;                           // 16^3 cell ends
-constexpr int kNnFineBits = kNnSmallBits + 1;             // 32^3 cells sorted
+constexpr int kNnFineBits = kNnSmallBits + 1;  // 32^3 cells sorted
 constexpr int kNnFineCells = 1 << (3 * kNnFineBits);
-constexpr int kNnSortWgs = 32;                            // workgroups per cloud
+constexpr int kNnSortWgs = 32;                 // workgroups per cloud
+static_assert(kNnSmall <= 0xffff && kNnFineCells <= 0xffff, "counts and positions, and keys with one to spare, in 16 bits");
 
 __global__ __launch_bounds__(256) void k_nn_keys(const float* __restrict__ x, int nx, const float* __restrict__ y,
                                                  int ny, uint16_t* __restrict__ kx, uint16_t* __restrict__ ky) {
@@ -393,7 +392,7 @@ __global__ __launch_bounds__(1024) void k_nn_sort(const float* __restrict__ x, i
                                                   const uint16_t* __restrict__ ky, int* __restrict__ cnt,
                                                   float4* __restrict__ sx, float4* __restrict__ sy,
                                                   float4* __restrict__ bx, float4* __restrict__ by) {
-  constexpr int PAIRS = kNnSmall / 2048;       // key pairs per thread
+  constexpr int PAIRS = kNnSortPairs;          // key pairs per thread
   constexpr int WORDS = kNnFineCells / 2048;   // words of two 16-bit counts per thread
   constexpr int PITCH = WORDS + 4;             // a thread's words, padded against bank conflicts
   static_assert(WORDS == 16 && PITCH % 4 == 0, "hist_at() and the 16-byte accesses");
@@ -989,8 +988,7 @@ int run_chamfer(const float* x, int64_t nx, const float* y, int64_t ny, int32_t*
   float4* by = reinterpret_cast<float4*>(b + L.box_y);
   const int64_t tx = (nx + kNnTile - 1) / kNnTile, ty = (ny + kNnTile - 1) / kNnTile;
   const int cb = L.cell_bits, nc = 1 << (3 * cb);
-  static_assert(kNnSmall / kNnTile * kNnTile == 32768, "the small-cloud sort covers the clouds given 16^3 cells");
-  const bool small = cb == kNnSmallBits;
+  const bool small = nn_small(nx, ny);
   if (small) {
     uint16_t *kx = reinterpret_cast<uint16_t*>(nnx), *ky = reinterpret_cast<uint16_t*>(nny);
     hipLaunchKernelGGL(k_nn_keys, dim3(nb256(nx + ny)), dim3(256), 0, s, x, (int)nx, y, (int)ny, kx, ky);

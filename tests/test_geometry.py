@@ -30,3 +30,15 @@ template <int R> constexpr bool agree() {
 }
 static_assert(agree<32>() && agree<64>() && agree<128>());
 """, f"-DPSR_PLANE_SPLIT_MIN={split}")
+
+
+def test_small_cloud_sort_takes_what_it_can_hold(tmp_path):
+    """The clouds that get the coarse cells are those the two-launch sort takes:
+    16-bit keys, counts and positions, and a pair of keys per thread and turn."""
+    _compiles(tmp_path, """#include "psr_opt.hip"
+using namespace psr::opt;
+static_assert(kNnSmall <= 65535 && kNnSmall == 2 * 1024 * kNnSortPairs && kNnFineCells <= 65535);
+static_assert(nn_cell_bits(kNnSmall, 1) == kNnSmallBits && nn_cell_bits(1, kNnSmall) == kNnSmallBits);
+static_assert(nn_cell_bits(kNnSmall + 1, 1) > kNnSmallBits && nn_cell_bits(1, kNnSmall + 1) > kNnSmallBits);
+static_assert(nn_small(kNnSmall, 1) && nn_small(1, kNnSmall) && !nn_small(kNnSmall + 1, 1) && !nn_small(1, kNnSmall + 1));
+""")
