@@ -700,28 +700,29 @@ __global__ __launch_bounds__(kNnBlock) __attribute__((amdgpu_waves_per_eu(1, 4))
     }
     publish();
   };
-  // the boxes of the first pass travel during the first scan
-  const int64_t tb = threadIdx.x < ntr ? threadIdx.x : 0;
-  const float4 blo = S.box[2 * tb], bhi = S.box[2 * tb + 1];
+  // a thread tests one tile per pass, whose box travels during the pass before
+  // (loaded where it is tested, a pass waited on memory: 1M against 1M points
+  // 4.91 ms, 1.58 now; 300k against 300k 0.54, 0.30 now)
+  static_assert(kNnCand == kNnBlock, "one tile per thread and pass");
+  int64_t tb = threadIdx.x < ntr ? threadIdx.x : 0;
+  float4 blo = S.box[2 * tb], bhi = S.box[2 * tb + 1];
   scan_tile(tile_point(s0 + w < ntr ? s0 + w : ntr - 1));
   __syncthreads();
   float bound = group_bound(reached());
   for (int64_t c0 = 0; c0 < ntr; c0 += kNnCand) {
     if (threadIdx.x == 0) ncand = 0;
     __syncthreads();
-    const int64_t c1 = c0 + kNnCand < ntr ? c0 + kNnCand : ntr;
-    for (int64_t t = c0 + threadIdx.x; t < c1; t += kNnBlock) {
-      if (t >= s0 && t <= s1) continue;
-      const bool first = t == threadIdx.x;
-      const float4 lo = first ? blo : S.box[2 * t], hi = first ? bhi : S.box[2 * t + 1];
-      const float lb = nn_boxbox_d2(ql, qh, lo, hi);
-      if (lb <= bound) {
-        const int k = atomicAdd(&ncand, 1);
-        cbox[k][0] = make_float4(lo.x, lo.y, lo.z, lb);
-        cbox[k][1] = make_float4(hi.x, hi.y, hi.z, __int_as_float((int)(t - c0)));
-        ckey[k] = ((unsigned long long)__float_as_uint(lb) << 32) | (uint32_t)k;
-      }
+    const int64_t t = c0 + threadIdx.x;
+    const float lb = nn_boxbox_d2(ql, qh, blo, bhi);
+    if (t < ntr && (t < s0 || t > s1) && lb <= bound) {
+      const int k = atomicAdd(&ncand, 1);
+      cbox[k][0] = make_float4(blo.x, blo.y, blo.z, lb);
+      cbox[k][1] = make_float4(bhi.x, bhi.y, bhi.z, __int_as_float((int)threadIdx.x));
+      ckey[k] = ((unsigned long long)__float_as_uint(lb) << 32) | (uint32_t)k;
     }
+    tb = t + kNnCand < ntr ? t + kNnCand : 0;
+    blo = S.box[2 * tb];
+    bhi = S.box[2 * tb + 1];
     __syncthreads();
     const int nc = ncand;
     // rank by counting the lesser keys (they differ: the slot is part of the key)
