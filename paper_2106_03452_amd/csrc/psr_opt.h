@@ -25,6 +25,12 @@ constexpr int kNnSortPairs = 16;
 constexpr int kNnSmall = 2 * 1024 * kNnSortPairs;
 constexpr int kNnSmallBits = 4;  // 16^3 cell ends
 constexpr bool nn_small(int64_t nx, int64_t ny) { return nx <= kNnSmall && ny <= kNnSmall; }
+// Clouds that one workgroup sorts in one launch, three points per thread: a
+// call takes 21.8 us at 1000 and 28.4 at 3000 points each, against 25.5 and 29.8
+// with the two-launch sort; at 4096 the one workgroup's key arithmetic has caught
+// up (33.0 against 32.4).
+constexpr int kNnOne = 3072;
+constexpr bool nn_one(int64_t nx, int64_t ny) { return nx <= kNnOne && ny <= kNnOne; }
 // 2^b cells per axis whose ends are kept: about four or more points per cell
 constexpr int nn_cell_bits(int64_t nx, int64_t ny) {
   if (nn_small(nx, ny)) return kNnSmallBits;

@@ -38,6 +38,8 @@ def test_small_cloud_sort_takes_what_it_can_hold(tmp_path):
     _compiles(tmp_path, """#include "psr_opt.hip"
 using namespace psr::opt;
 static_assert(kNnSmall <= 65535 && kNnSmall == 2 * 1024 * kNnSortPairs && kNnFineCells <= 65535);
+static_assert(kNnOne % 1024 == 0 && kNnOne <= kNnSmall && nn_one(kNnOne, kNnOne));
+static_assert(nn_cell_bits(kNnOne, kNnOne) == kNnSmallBits && !nn_one(kNnOne + 1, 1) && !nn_one(1, kNnOne + 1));
 static_assert(nn_cell_bits(kNnSmall, 1) == kNnSmallBits && nn_cell_bits(1, kNnSmall) == kNnSmallBits);
 static_assert(nn_cell_bits(kNnSmall + 1, 1) > kNnSmallBits && nn_cell_bits(1, kNnSmall + 1) > kNnSmallBits);
 static_assert(nn_small(kNnSmall, 1) && nn_small(1, kNnSmall) && !nn_small(kNnSmall + 1, 1) && !nn_small(1, kNnSmall + 1));

@@ -43,6 +43,13 @@ def test_small_cloud_sort_equals_the_general_one(dev, nx, ny, kind):
         assert torch.equal(s, g[:ny])
 
 
+@pytest.mark.parametrize("nx,ny", [(2, 1023), (1024, 1025), (2048, 3071), (3072, 3072), (3073, 100), (100, 3073)])
+@pytest.mark.parametrize("kind", ["uniform", "clustered"])
+def test_one_workgroup_sort_equals_the_general_one(dev, nx, ny, kind):
+    """Clouds of up to 3072 points are sorted in one launch."""
+    test_small_cloud_sort_equals_the_general_one(dev, nx, ny, kind)
+
+
 @pytest.mark.parametrize("nf", [1, 1023, 1024, 1025, 65537, (1 << 20) + 1025])
 def test_sampling_across_scan_blocks(dev, nf):
     """Running areas are kept per block of 1024 faces; above 1024 blocks the
