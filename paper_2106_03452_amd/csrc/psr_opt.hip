@@ -25,6 +25,9 @@ namespace opt {
 
 constexpr int kScanBlock = 1024;  // face areas per scan block
 constexpr int kScanTops = 1024;   // block sums that a sampling workgroup scans itself
+// samples up to which one wavefront, with the block sums scanned once for it, is
+// a workgroup (see k_sample)
+constexpr int64_t kSampleFew = 65536;
 
 __device__ __forceinline__ double face_area(const float* __restrict__ v, const int32_t* __restrict__ f, int64_t i) {
   const int64_t i0 = f[3 * i], i1 = f[3 * i + 1], i2 = f[3 * i + 2];
@@ -42,15 +45,22 @@ __global__ __launch_bounds__(256) void k_face_area(const float* __restrict__ v, 
   if (i < nf) a[i] = face_area(v, f, i);
 }
 
-// inclusive scan over the workgroup's WAVES wavefronts; sh holds WAVES values
-template <int WAVES>
-__device__ __forceinline__ double block_incl_scan(double v, double* sh, double& total) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+// inclusive scan over the wavefront
+__device__ __forceinline__ double wave_incl_scan(double v) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const double u = __shfl_up(v, d, 64);
     if (lane >= d) v += u;
   }
+  return v;
+}
+
+// inclusive scan over the workgroup's WAVES wavefronts; sh holds WAVES values
+template <int WAVES>
+__device__ __forceinline__ double block_incl_scan(double v, double* sh, double& total) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  v = wave_incl_scan(v);
   if (lane == 63) sh[wid] = v;
   __syncthreads();
   double before = 0.0, tot = 0.0;
@@ -102,35 +112,41 @@ __global__ __launch_bounds__(256) void k_scan_tops(double* __restrict__ bs, int 
 }
 
 // One sample per thread: the first face whose running area exceeds u0 times the
-// total, by its scan block first (TOPS: each wavefront scans the block sums in
-// LDS; else they are scanned already), then by binary search within the block.
+// total, by its scan block first (TOPS: the workgroup's first wavefront scans the
+// block sums in LDS; else they are scanned already), then by binary search within
+// the block.
 // Cache lines of running areas fetched across the chip bound it: searches in
 // rounds of 3, 7 or 31 independent loads have fewer rounds and touch more lines
 // (8.0, 9.8 and 18.8 us for 20000 samples of 20000 faces; this 6.9).
-template <bool TOPS>
-__global__ __launch_bounds__(64) void k_sample(const float* __restrict__ v, const float* __restrict__ vn,
+// Up to kSampleFew samples a workgroup is one wavefront, so that few samples are
+// spread over the chip; beyond, with TOPS, four share the scan and its 8 KB of
+// LDS (3M samples of 12 faces 39.7 -> 29.0 us, 300k of 1M faces 63.5 -> 51.4;
+// equal at 100k. Without TOPS there is nothing to share: 200k of 2M faces 52.1
+// with one wavefront, 54.9 with four).
+template <bool TOPS, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_sample(const float* __restrict__ v, const float* __restrict__ vn,
                                                 const int32_t* __restrict__ f, int64_t nf,
                                                 const double* __restrict__ csum, const double* __restrict__ bs, int nb,
                                                 const float* __restrict__ u, int64_t m, float* __restrict__ pts,
                                                 float* __restrict__ nrm, int32_t* __restrict__ face,
                                                 float* __restrict__ bary) {
   __shared__ double top[TOPS ? kScanTops + 1 : 1];
-  __shared__ double sh[1];
-  const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
   if (i < m) u0 = u[3 * i], u1 = u[3 * i + 1], u2 = u[3 * i + 2];
   const double* pre = bs;
   if (TOPS) {
-    double carry = 0.0;
-    for (int c = 0; c < nb; c += 64) {
-      const int b = c + (int)threadIdx.x;
-      const double s = b < nb ? bs[b] : 0.0;
-      double tot;
-      const double inc = block_incl_scan<1>(s, sh, tot);
-      if (b < nb) top[b] = carry + (inc - s);
-      carry += tot;
+    if (threadIdx.x < 64) {
+      double carry = 0.0;
+      for (int c = 0; c < nb; c += 64) {
+        const int b = c + (int)threadIdx.x;
+        const double s = b < nb ? bs[b] : 0.0;
+        const double inc = wave_incl_scan(s);
+        if (b < nb) top[b] = carry + (inc - s);
+        carry += __shfl(inc, 63, 64);
+      }
+      if (threadIdx.x == 0) top[nb] = carry;
     }
-    if (threadIdx.x == 0) top[nb] = carry;
     __syncthreads();
     pre = top;
   }
@@ -1028,9 +1044,12 @@ int run_sample(const float* v, const float* vn, const int32_t* f, int64_t nf, co
   hipLaunchKernelGGL(k_area_scan, dim3(nb), dim3(kScanBlock), 0, s, v, f, nf, w, a, bs);
   const bool tops = nb <= kScanTops;
   if (!tops) hipLaunchKernelGGL(k_scan_tops, dim3(1), dim3(256), 0, s, bs, nb);
-  if (m > 0)
-    hipLaunchKernelGGL(tops ? k_sample<true> : k_sample<false>, dim3((m + 63) / 64), dim3(64), 0, s, v, vn, f, nf, a, bs,
-                       nb, u, m, pts, nrm, face, bary);
+  if (tops && m > kSampleFew)
+    hipLaunchKernelGGL((k_sample<true, 256>), dim3((m + 255) / 256), dim3(256), 0, s, v, vn, f, nf, a, bs, nb, u, m, pts,
+                       nrm, face, bary);
+  else if (m > 0)
+    hipLaunchKernelGGL((tops ? k_sample<true, 64> : k_sample<false, 64>), dim3((m + 63) / 64), dim3(64), 0, s, v, vn, f,
+                       nf, a, bs, nb, u, m, pts, nrm, face, bary);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 

@@ -91,6 +91,22 @@ def test_chamfer_gradient_takes_the_factor_in_or_out(dev):
     assert dc[0] == 0 and abs(float(dc[1]) - ref.sum()) <= 9000 * tol
 
 
+@pytest.mark.parametrize("nf", [12, 1025, (1 << 20) + 1025])
+def test_many_samples_equal_few(dev, nf):
+    """Above 65536 samples four wavefronts are a workgroup; a sample depends on
+    its own random numbers only, so the two kernels give the same ones, bit for bit."""
+    from paper_2106_03452_amd import optimize as O
+    announce(f"many samples of {nf} faces")
+    rng = np.random.default_rng(nf)
+    v, n = (to_dev(rng.random((nf + 2, 3)), dev) for _ in range(2))
+    f = torch.from_numpy((np.arange(nf)[:, None] + np.arange(3)).astype(np.int32)).to(dev)
+    u = to_dev(rng.random((65536 + 257, 3)), dev)
+    many = O.sample_raw(v, f, u, n)
+    for part in (slice(0, 65536), slice(65536 - 64, None)):
+        for a, b in zip(many, O.sample_raw(v, f, u[part], n)):
+            assert torch.equal(a[part], b)
+
+
 def test_strided_arguments_give_the_contiguous_results(dev):
     """Equally sized strided clouds, and faces that are columns of a wider array."""
     from paper_2106_03452_amd import optimize as O
