@@ -40,7 +40,13 @@ constexpr int kScanBlock = 1024;
 // Waves per SIMD asked of the register allocator for S1: two of its 512-thread
 // workgroups fit a CU by LDS from 128 on, which needs at most 128 VGPRs.
 constexpr int slab_rows_waves(int res) { return res >= 128 ? 4 : 2; }
-// workgroups of S1 (two fit a CU), and the most (tile, channel) items of one
+// Whether S2 and S3 hold down their registers (see opaque()): at 512 and 1024,
+// where that is two workgroups per CU instead of one (S2 and S3 at 512^3, one
+// slab, every tile live: 1117 and 937 us without, 643 and 580 with). Below, what
+// is recomputed only takes time (256^3 87 and 71 us without, 91 and 73 with; 16^3
+// per slab of two planes 8.5 and 9.8 without, 10.4 and 11.3 with).
+constexpr bool slab_lean(int res) { return res >= 512; }
+// workgroups of S1 with a list (two fit a CU), and the most (tile, channel) items of one
 constexpr int kRowGrid = 2048;
 constexpr int kRowItems = 3 * 64 * kSlabMaxRes / kRowGrid + 8;
 
@@ -271,12 +277,15 @@ __global__ __launch_bounds__(256) void k_slab_scatter(SlabArgs a) {
 // field) -> r2c FFT along j2 -> A_g[c][j0 - g s], k2-tiled rows of r/2 + 1.
 // Row tiles that no point reaches are zero: they are not written, and S2 does
 // not read them (65 % of the 1M-point scene's tiles at 1024^3: S1 4.35 -> 2.76
-// ms, S2 5.63 -> 4.04 ms). A workgroup takes every gridDim.x-th (live tile,
+// ms, S2 5.63 -> 4.04 ms). LIST: a workgroup takes every gridDim.x-th (live tile,
 // channel) item: it finds them from the planes' bitmaps once, so all have the
 // same number (2.78 -> 2.06 ms: with every tile an item and a test of the bitmap
 // each, the workgroups' shares of the live ones, which crowd together, differed).
+// Where kRowGrid workgroups cover every item there is nothing to share out: one
+// item each, without the list and with addresses that stay in registers (256^3 in
+// 8 slabs, every tile live, 18.6 us per slab against 23.6; 16^3 10.4 against 13.2).
 // ---------------------------------------------------------------------------
-template <int RES, bool LOAD>
+template <int RES, bool LOAD, bool LIST>
 __global__ __launch_bounds__(slab_rows_block(RES)) __attribute__((amdgpu_waves_per_eu(slab_rows_waves(RES))))
 void k_slab_rows_fwd(const SlabArgs a, int g) {
   constexpr int M = RES / 2, H = M + 1, HP = slab_hp(RES), TR = slab_rows(RES), NT = RES / TR;
@@ -286,11 +295,12 @@ void k_slab_rows_fwd(const SlabArgs a, int g) {
   __shared__ cf rtw[M + 1];  // W_RES^k, k in [0, M], for the r2c post-processing
   const int s = RES / a.G;
   constexpr int TC = slab_cols(RES);
-  __shared__ int list[LOAD ? 1 : kRowItems];  // this workgroup's live items: 4 tile + channel, or -1
+  constexpr bool LOOP = LIST || LOAD;
+  __shared__ int list[LIST ? kRowItems : 1];  // this workgroup's live items: 4 tile + channel, or -1
   stage_table<BR>(stw, a.tw + M, M);
   stage_table<BR>(rtw, a.tw + RES, M + 1);
   int items = 3 * s * NT;
-  if constexpr (!LOAD) {
+  if constexpr (LIST) {
     // inclusive sums of the planes' live tiles, in the rows' room
     int* const pre = reinterpret_cast<int*>(rows);
     constexpr int PER = (RES + BR - 1) / BR;
@@ -332,7 +342,7 @@ void k_slab_rows_fwd(const SlabArgs a, int g) {
   }
   for (int it = blockIdx.x, i = 0; it < items; it += gridDim.x, ++i) {
     int T = it % (s * NT), c = it / (s * NT);
-    if constexpr (!LOAD) {
+    if constexpr (LIST) {
       if (list[i] < 0) continue;
       T = list[i] >> 2;
       c = list[i] & 3;
@@ -340,18 +350,19 @@ void k_slab_rows_fwd(const SlabArgs a, int g) {
     const int j0l = T / NT, a0 = (T % NT) * TR, j0 = g * s + j0l;
     Ranges R{};
     if constexpr (!LOAD) R = slab_ranges<RES, TR>(a.off, j0, a0);
+    if (!LOAD && !LIST && R.total == 0) return;
     // k2-tiled plane: element (j1, k2) at ((k2 / TC) RES + j1) TC + k2 % TC; the
     // loops below run tile by tile, so each tile's TR rows are one contiguous run
     cf* const out = a.A + ((int64_t)(3 * g + c) * s + j0l) * RES * HP + (int64_t)a0 * TC;
-    // everything per item is computed anew (LEAN): hoisted out of the item
-    // loop the addresses spilled, and each transform waited on 40 reloads
-    // (10.5 us of an item's 31 instead of 3)
-    fill_rows<RES, TR, BR, LOAD ? 2 : 0, true>(rows, a.sorted, R, a.field, make_float3(1.0f, 0.0f, 1.0f), j0, a0, c);
-    const int t = opaque_v(threadIdx.x);
+    // with several items, everything is computed anew for each (LEAN): hoisted
+    // out of the item loop the addresses spilled, and each transform waited on
+    // 40 reloads (10.5 us of an item's 31 instead of 3)
+    fill_rows<RES, TR, BR, LOAD ? 2 : 0, LOOP>(rows, a.sorted, R, a.field, make_float3(1.0f, 0.0f, 1.0f), j0, a0, c);
+    const int t = LOOP ? opaque_v(threadIdx.x) : threadIdx.x;
     {
       cf reg[E];
       const int l = t / TPL;
-      fft<M, -1, false, false, false, true>(reg, rows + l * LS, t % TPL, stw, row_swz(M, l));
+      fft<M, -1, false, false, false, LOOP>(reg, rows + l * LS, t % TPL, stw, row_swz(M, l));
     }
     // X[k] = E_k + W_r^k O_k with E = (Z_k + Z*_{M-k})/2, O = (Z_k - Z*_{M-k})/(2i);
     // k and k + 1 (k even) per thread, one 16-byte store (of a last pair k = M,
@@ -373,6 +384,7 @@ void k_slab_rows_fwd(const SlabArgs a, int g) {
       }
       *reinterpret_cast<float4*>(out + ((int64_t)kt * RES + l) * TC + kk) = make_float4(o[0], o[1], o[2], o[3]);
     }
+    if constexpr (!LOOP) return;
     __syncthreads();  // the rows are zeroed for the next item
   }
 }
@@ -389,6 +401,7 @@ __global__ __launch_bounds__(slab_cols_block(RES)) __attribute__((amdgpu_waves_p
 void k_slab_fft_j1(const SlabArgs a, const BlockPtrs dst, int g) {
   constexpr int H = RES / 2 + 1, HP = slab_hp(RES), TC = slab_cols(RES), NKT = HP / TC;
   constexpr int TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES), BC = slab_cols_block(RES);
+  constexpr bool LEAN = slab_lean(RES);
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
   __shared__ cf* dp[kMaxSlabs];
@@ -420,25 +433,25 @@ void k_slab_fft_j1(const SlabArgs a, const BlockPtrs dst, int g) {
     return;
   }
   if (oc == 0) {
-    load_cols<RES, TC, true>(rows, [&](int n) { return src + (int64_t)n * TC; }, nvalid, keep);
-    fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
+    load_cols<RES, TC, LEAN>(rows, [&](int n) { return src + (int64_t)n * TC; }, nvalid, keep);
+    fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
   } else {
     cf acc[E];
-    load_cols<RES, TC, true>(rows, [&](int n) { return src + 2 * CH + (int64_t)n * TC; }, nvalid, keep);
-    fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
+    load_cols<RES, TC, LEAN>(rows, [&](int n) { return src + 2 * CH + (int64_t)n * TC; }, nvalid, keep);
+    fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
     const float k2f = kappa_odd(k2a + l, RES);
 #pragma unroll
     for (int v = 0; v < E; ++v) acc[v] = cscale(reg[v], k2f);
-    load_cols<RES, TC, true>(rows, [&](int n) { return src + CH + (int64_t)n * TC; }, nvalid, keep);
-    fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
-    const LineK<RES, true> k1(lt);
+    load_cols<RES, TC, LEAN>(rows, [&](int n) { return src + CH + (int64_t)n * TC; }, nvalid, keep);
+    fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
+    const LineK<RES, LEAN> k1(lt);
 #pragma unroll
     for (int v = 0; v < E; ++v) {
       const float k1f = k1.odd(v);
       reg[v] = cf{acc[v].x + k1f * reg[v].x, acc[v].y + k1f * reg[v].y};
     }
   }
-  store_cols<RES, TC, true>(
+  store_cols<RES, TC, LEAN>(
       rows, reg, l, lt,
       [&](int n) { return dp[n >> lq] + (((int64_t)(oc * s + j0l) * NKT + kt) * q + (n & (q - 1))) * TC; },
       nvalid);
@@ -455,6 +468,7 @@ __global__ __launch_bounds__(slab_cols_block(RES)) __attribute__((amdgpu_waves_p
 void k_slab_pencil_j0(const SlabArgs a, const BlockPtrs src, const BlockPtrs dst, int h) {
   constexpr int M = RES / 2, H = M + 1, HP = slab_hp(RES), TC = slab_cols(RES), NKT = HP / TC;
   constexpr int TPL = plan_TPL(RES), E = plan_E(RES), LS = lstride(RES), BC = slab_cols_block(RES);
+  constexpr bool LEAN = slab_lean(RES);
   __shared__ cf rows[TC * LS];
   __shared__ cf stw[RES];
   __shared__ float g1[M + 1];  // the Gaussian is even in k
@@ -469,20 +483,20 @@ void k_slab_pencil_j0(const SlabArgs a, const BlockPtrs src, const BlockPtrs dst
   const int k1 = h * q + k1l;
   const int l = threadIdx.x / TPL, lt = threadIdx.x % TPL;
   cf acc[E], reg[E];
-  load_cols<RES, TC, true>(
+  load_cols<RES, TC, LEAN>(
       rows, [&](int n) { return bp[n >> ls] + (((int64_t)(n & (s - 1)) * NKT + kt) * q + k1l) * TC; }, nvalid);
-  fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
-  scale_odd<RES, true>(acc, reg, lt);
-  load_cols<RES, TC, true>(
+  fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
+  scale_odd<RES, LEAN>(acc, reg, lt);
+  load_cols<RES, TC, LEAN>(
       rows, [&](int n) { return bp[n >> ls] + (((int64_t)(s + (n & (s - 1))) * NKT + kt) * q + k1l) * TC; },
       nvalid);
   for (int e = threadIdx.x; e < a.G; e += BC) bp[e] = dst.p[e];  // the loads are done; seen after the next barrier
-  fft<RES, -1, false, true, false, true>(reg, rows + l * LS, lt, stw);
+  fft<RES, -1, false, true, false, LEAN>(reg, rows + l * LS, lt, stw);
   {
     const int k2 = imin(k2a + l, M);  // padding lines are zero; any finite factor will do
     const float g12 = gauss_at<RES>(g1, k1) * g1[k2];
     const float q12 = kappa_of(k1, RES) * kappa_of(k1, RES) + kappa_of(k2, RES) * kappa_of(k2, RES);
-    const LineK<RES, true> k0(lt);
+    const LineK<RES, LEAN> k0(lt);
 #pragma unroll
     for (int v = 0; v < E; ++v) {
       const float F = spectral_F<RES>(g1, k0, v, g12, q12);
@@ -490,8 +504,8 @@ void k_slab_pencil_j0(const SlabArgs a, const BlockPtrs src, const BlockPtrs dst
       reg[v] = cf{-F * x.y, F * x.x};  // i F sum
     }
   }
-  fft<RES, +1, true, true, false, true>(reg, rows + l * LS, lt, stw);
-  store_cols<RES, TC, true>(
+  fft<RES, +1, true, true, false, LEAN>(reg, rows + l * LS, lt, stw);
+  store_cols<RES, TC, LEAN>(
       rows, reg, l, lt, [&](int n) { return bp[n >> ls] + (((int64_t)(n & (s - 1)) * NKT + kt) * q + k1l) * TC; },
       nvalid);
 }
@@ -715,8 +729,13 @@ int slab_sequence(Exec& x, const SlabArgs& a) {
   x.begin(STAGE_S1);
   const unsigned rb = (unsigned)imin(3 * s * NT, kRowGrid);
   for (int g = 0; g < G; ++g) {
-    if (load) hipLaunchKernelGGL((k_slab_rows_fwd<RES, true>), dim3(rb), dim3(BR), 0, st, a, g);
-    else hipLaunchKernelGGL((k_slab_rows_fwd<RES, false>), dim3(rb), dim3(BR), 0, st, a, g);
+    if (load) {
+      hipLaunchKernelGGL((k_slab_rows_fwd<RES, true, false>), dim3(rb), dim3(BR), 0, st, a, g);
+    } else if (3 * s * NT <= kRowGrid) {
+      hipLaunchKernelGGL((k_slab_rows_fwd<RES, false, false>), dim3(rb), dim3(BR), 0, st, a, g);
+    } else if constexpr (3 * RES * NT > kRowGrid) {
+      hipLaunchKernelGGL((k_slab_rows_fwd<RES, false, true>), dim3(rb), dim3(BR), 0, st, a, g);
+    }
   }
   x.end(STAGE_S1);
 

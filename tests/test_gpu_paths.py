@@ -199,6 +199,25 @@ def test_slab_solve_reads_nothing_unwritten(dev, res, slabs, kind):
     assert bool(torch.isfinite(out[0]).all()) and torch.equal(*out)
 
 
+@pytest.mark.parametrize("res,slabs", [(256, (1, 2, 64)), (512, (2, 8, 16, 64)), (1024, (1, 8, 64))])
+@pytest.mark.parametrize("kind", ["one", "rod", "all"])
+def test_large_slab_solves_do_not_depend_on_the_slabs(dev, res, slabs, kind):
+    """Few slabs share out lists of live row tiles, many take a tile per workgroup;
+    the largest grids have 8-column tiles and planes of 16 or 64 row tiles, up to
+    all of them live and up to 96 items on a workgroup's list. The same grid bit
+    for bit, whatever the workspace held."""
+    from paper_2106_03452_amd import slab as S
+    announce(f"slab counts {res}^3 {slabs} {kind}")
+    p, n = (to_dev(a, dev) for a in _cloud(kind, {"one": 1, "rod": 3000, "all": 300000}[kind], res))
+    out = []
+    for k, g in enumerate(slabs):
+        ws = torch.full((S.workspace_bytes(res, p.shape[0], g),), 255 * (k % 2), dtype=torch.uint8, device=dev)
+        out.append(S.forward(p, n, res, slabs=g, workspace=ws)[0])
+        del ws
+        assert bool(torch.isfinite(out[0]).all()) and torch.equal(out[0], out[-1])
+        del out[1:]
+
+
 @pytest.mark.parametrize("res", [32, 64, 128])
 @pytest.mark.parametrize("kind", ["sheet", "ball", "all"])
 def test_single_and_batched_solves_agree(dev, res, kind):
