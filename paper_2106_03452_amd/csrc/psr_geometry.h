@@ -60,11 +60,12 @@ __host__ __device__ constexpr int tile_rows(int res) {
 __host__ __device__ constexpr int plane_parts(int res) { return res >= PSR_PLANE_SPLIT_MIN ? 2 : 1; }
 __host__ __device__ constexpr int plane_sums(int res) { return res * plane_parts(res); }
 __host__ __device__ constexpr int rows_block(int res) { return tile_rows(res) * plan_TPL(res / 2); }
-// Workgroup size of the row passes. Up to 32 a row tile is the whole plane
-// and its transforms take one thread per row (res threads); the workgroup
-// is widened to 256 threads for the loops over the plane's points and
-// samples, the threads beyond the rows transforming scratch rows.
-__host__ __device__ constexpr int rows_wg(int res) { return res <= 32 ? 256 : rows_block(res); }
+// Workgroup size of the row passes (8 and 16, 256 and 512; the plane passes run
+// between). At 8 and 16 a row tile is the whole plane and its transforms take one
+// thread per row; the workgroup is widened to 256 threads for the loops over the
+// plane's points and samples, the threads beyond the rows transforming scratch
+// rows.
+__host__ __device__ constexpr int rows_wg(int res) { return res <= 16 ? 256 : rows_block(res); }
 // LDS rows of a row-pass workgroup: the tile's rows plus the scratch rows
 __host__ __device__ constexpr int rows_lds(int res) {
   return rows_wg(res) / plan_TPL(res / 2) > tile_rows(res) ? rows_wg(res) / plan_TPL(res / 2) : tile_rows(res);

@@ -1695,17 +1695,19 @@ __device__ __forceinline__ void b_plane_inv(const cf* __restrict__ in, float* __
 // FP64 reductions and normalisation (main Eq. 4)
 // ---------------------------------------------------------------------------
 
-// grad f_i (FP32) of one point from its partials; .w = f_i
+// grad f_i (FP32) of one point from its partials, in .x to .z; f_i (FP64) is
+// added to acc where the gather has not summed it
 template <int RES>
-__device__ __forceinline__ float4 point_grad(const float4* __restrict__ part, int64_t npoints, int64_t s) {
+__device__ __forceinline__ float4 point_grad(const float4* __restrict__ part, int64_t npoints, int64_t s, double& acc) {
   const float4 q0 = part[s], q1 = part[npoints + s];
   if constexpr (gather_slots(RES) == 2) {
-    return make_float4(q0.y + q1.y, q0.z + q1.z, q0.w + q1.w, q0.x + q1.x);
+    static_assert(fold_reduce(RES), "the gather sums f_i");
+    return make_float4(q0.y + q1.y, q0.z + q1.z, q0.w + q1.w, 0.0f);
   } else {
     const float4 q2 = part[2 * npoints + s], q3 = part[3 * npoints + s];
-    const double f = ((double)q0.x + (double)q1.x) + ((double)q2.x + (double)q3.x);
+    if constexpr (!fold_reduce(RES)) acc += ((double)q0.x + (double)q1.x) + ((double)q2.x + (double)q3.x);
     return make_float4((q0.y + q1.y) + (q2.y + q3.y), (q0.z + q1.z) + (q2.z + q3.z), (q0.w + q1.w) + (q2.w + q3.w),
-                       (float)f);
+                       0.0f);
   }
 }
 
@@ -1716,9 +1718,7 @@ __device__ __forceinline__ void b_fwd_point_reduce(const float4* __restrict__ pa
   __shared__ double sh[256];
   double acc = 0.0;
   for (int64_t s = (int64_t)bid * blockDim.x + threadIdx.x; s < npoints; s += (int64_t)nblocks * blockDim.x) {
-    gradf[s] = point_grad<RES>(part, npoints, s);
-    acc += ((double)part[s].x + (double)part[npoints + s].x) +
-           ((double)part[2 * npoints + s].x + (double)part[3 * npoints + s].x);
+    gradf[s] = point_grad<RES>(part, npoints, s, acc);
   }
   const double tot = block_sum(acc, sh);
   if (threadIdx.x == 0) blockpart[bid] = tot;
@@ -2162,8 +2162,9 @@ __global__ __launch_bounds__(256) void k_normalize(const Batch<MAXJ> B) {
   constexpr int NBL = norm_blocks(RES);
   if constexpr (fold_reduce(RES)) {
     if (bid >= NBL) {
+      double unused = 0.0;
       for (int64_t s = (int64_t)(bid - NBL) * 256 + threadIdx.x; s < J.P; s += (int64_t)(nbl - NBL) * 256)
-        sv.gradf[s] = point_grad<RES>(w.part, J.P, s);
+        sv.gradf[s] = point_grad<RES>(w.part, J.P, s, unused);
       return;
     }
   }
