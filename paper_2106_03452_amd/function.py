@@ -19,9 +19,12 @@ def _ptr(t: torch.Tensor | None) -> int | None:
 
 
 def _device_index(dev: torch.device) -> int:
-    if dev.type != "cuda":  # the address of a host tensor must not reach a kernel
-        raise ValueError(f"Expected a cuda device, but got: {dev}")
-    return dev.index if dev.index is not None else torch.cuda.current_device()
+    index = dev.index
+    if index is None:  # so for every host tensor, whose address must not reach a kernel
+        if dev.type != "cuda":
+            raise ValueError(f"Expected a cuda device, but got: {dev}")
+        index = torch.cuda.current_device()
+    return index
 
 
 def _stream(dev: torch.device) -> int:

@@ -206,6 +206,8 @@ class NativeStep:
     workspace, sized for a mesh cap that grows when a mesh exceeds it."""
 
     def __init__(self, dev, npoints: int, ntarget: int, nsamples: int, res: int):
+        if dev.type != "cuda":
+            raise ValueError(f"Expected a cuda device, but got: {dev}")
         self.dev, self.P, self.T, self.S, self.res = dev, int(npoints), int(ntarget), int(nsamples), int(res)
         self.vcap, self.tcap = max(4096, 8 * res * res), max(8192, 16 * res * res)
         self.counts = (ctypes.c_int64 * 2)()

@@ -62,6 +62,7 @@ def _host_calls():
         "mesh backward": lambda: M.marching_cubes_backward(grid, mesh, v),
         "slab": lambda: S.forward_raw(x, x, 16, 2.0, 1, torch.empty(16, 16, 16), raw(48),
                                       raw(S.workspace_bytes(16, 6, 1))),
+        "step": lambda: O.NativeStep(torch.device("cpu", 0), 10, 10, 10, 8)(x, x, [x] * 4, 1, 1e-3, y, u, 2.0),
         "status": lambda: F.status(raw(4096)),
         "scalars": lambda: F.scalars(raw(4096)),
     }
